@@ -402,7 +402,7 @@ int dgmg_get_face_params(const dgmg_handle* h, double* theta, double* omega);
  * backward: gradient of L = (1/B) sum_b sum_o (Y_bo - T_bo)^2 with respect to
  *   the parameters into grad [PARAMS] (overwritten), from the X, Y, work of the
  *   matching forward call; scratch holds B (2 HIDDEN + OUT) floats.  Sums over
- *   the batch run in sample order (reproducible).
+ *   the batch run in a fixed order (reproducible).
  * adam: one Adam step (Kingma and Ba) on n parameters at step t >= 1:
  *   m = b1 m + (1 - b1) g, v = b2 v + (1 - b2) g^2,
  *   p -= lr (m / (1 - b1^t)) / (sqrt(v / (1 - b2^t)) + eps).

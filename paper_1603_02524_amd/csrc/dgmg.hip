@@ -15,6 +15,7 @@
 #include "../../include/dgmg.h"
 #include "kernels.hpp"
 #include "kernels_big.hpp"
+#include "kernels_fdm3.hpp"
 #include "setup.hpp"
 
 using namespace dgmg;
@@ -449,6 +450,7 @@ struct dgmg_batch {
   struct Launch {
     int kind = 0, dim = 3, f32 = 0, t[4] = {0, 0, 0, 0};
     int ng = 0, ntot = 0;
+    PatchBuf pb;  // patch solves: the layout with the longest strips of the launch
     size_t desc_off = 0, starts_off = 0;
     std::vector<std::function<int()>> fns;
     std::vector<int> fn_grid;  // the grid of each of fns
@@ -620,6 +622,26 @@ void carve_level(Carver& cv, const LevelHost& h, LevelDev<T>& d, Upload* up) {
       }
     return t;
   };
+  // the patch matrices padded as in LDS
+  auto images = [](const std::vector<double>& S, int n) {
+    const size_t nb = S.size() / ((size_t)n * n);
+    const int q = fdm3_pitch<T>(n);
+    const size_t im = fdm3_image<T>(n);
+    std::vector<double> t(nb * im, 0.0);
+    for (size_t b = 0; b < nb; ++b)
+      for (int i = 0; i < n; ++i)
+        for (int j = 0; j < n; ++j) t[b * im + (size_t)i * q + j] = S[b * n * n + (size_t)i * n + j];
+    return t;
+  };
+  // offsets of the positions of a whole direction from those of its patches (patches
+  // that hold the same position agree on it)
+  auto positions = [](const std::vector<int>& off, int len, int step) {
+    const int np = (int)(off.size() / len);
+    std::vector<int> t((size_t)(np - 1) * step + len);
+    for (int p = 0; p < np; ++p)
+      for (int o = 0; o < len; ++o) t[(size_t)p * step + o] = off[(size_t)p * len + o];
+    return t;
+  };
   d.dim = h.dim;
   d.se = h.se ? 1 : 0;
   d.P = h.P;
@@ -656,22 +678,52 @@ void carve_level(Carver& cv, const LevelHost& h, LevelDev<T>& d, Upload* up) {
         dd.lam_fc = put(s.lam_fc);
         dd.w_fc = put(s.w_fc);
       }
-      dd.goff_ec = put_int(offsets(k, s.N, s.n_ec, false));
-      if (!h.se) dd.goff_fc = put_int(offsets(k, s.nf, s.n_fc, true));
+      const std::vector<int> oec = offsets(k, s.N, s.n_ec, false);
+      const std::vector<int> ofc = h.se ? std::vector<int>() : offsets(k, s.nf, s.n_fc, true);
+      dd.goff_ec = put_int(oec);
+      if (!h.se) dd.goff_fc = put_int(ofc);
+      if (h.dim == 3) {  // tables of the in-LDS patch solve
+        const int step = h.se ? h.P : h.NP;
+        dd.img_ec = put(images(s.S_ec, s.n_ec));
+        dd.gp_ec = put_int(positions(oec, s.n_ec, step));
+        if (!h.se) {
+          dd.img_fc = put(images(s.S_fc, s.n_fc));
+          dd.gp_fc = put_int(positions(ofc, s.n_fc, step));
+        }
+      }
     }
   }
 }
 
-// Patch-buffer elements needed by one sweep with normal direction nd on a level.
+void sweep_shape(const LevelHost& lv, int nd, int np[3], int& NA, int& NL) {
+  np[0] = np[1] = np[2] = 1;
+  for (int d = 0; d < lv.dim; ++d) np[d] = (d == nd) ? lv.dir[d].nf : lv.dir[d].N;
+  NL = lv.NP + 2 * lv.NO;
+  NA = nd < 0 ? NL : 2 * lv.P;
+}
+
+// Patch-buffer layout of a sweep with normal direction nd on a level.
+template <class T>
+PatchBuf sweep_buf(const LevelHost& lv, int nd, bool whole = true) {
+  int np[3], NA, NL;
+  sweep_shape(lv, nd, np, NA, NL);
+  const int step = lv.se ? lv.P : lv.NP;
+  return lv.dim == 3 ? Kern<T, 3>::patch_buf(lv.NP, nd, NA, NL, np, step, whole)
+                     : Kern<T, 2>::patch_buf(lv.NP, nd, NA, NL, np, step, whole);
+}
+
+// Patch-buffer elements needed by one sweep with normal direction nd on a level
+// (the larger of the two precisions' layouts, and of the layout for single patches).
 size_t sweep_patch_elems(const LevelHost& lv, int nd) {
-  size_t np = 1, ts = 1;
-  for (int d = 0; d < lv.dim; ++d) {
-    const Dir1D& s = lv.dir[d];
-    const bool fc = d == nd;
-    np *= fc ? s.nf : s.N;
-    ts *= fc ? s.n_fc : s.n_ec;
-  }
-  return np * ts;
+  int np[3], NA, NL;
+  sweep_shape(lv, nd, np, NA, NL);
+  int len[3] = {1, 1, 1};
+  for (int d = 0; d < lv.dim; ++d) len[d] = d == nd ? NA : NL;
+  size_t most = (size_t)np[0] * np[1] * np[2] * len[0] * len[1] * len[2];
+  for (const PatchBuf& pb : {sweep_buf<double>(lv, nd), sweep_buf<float>(lv, nd)})
+    most = std::max(most, (size_t)np[0] * ((np[1] + pb.K - 1) / pb.K) * np[2] * len[0] * len[2] *
+                              ((size_t)(pb.K - 1) * pb.step + len[1]));
+  return most;
 }
 
 void layout(dgmg_handle* h, char* base, Upload* up) {
@@ -801,13 +853,6 @@ int k_apply(dgmg_handle* h, int l, int mode, const T* x, const T* f, T* y, doubl
   return check_hip(h, "apply");
 }
 
-void sweep_shape(const LevelHost& lv, int nd, int np[3], int& NA, int& NL) {
-  np[0] = np[1] = np[2] = 1;
-  for (int d = 0; d < lv.dim; ++d) np[d] = (d == nd) ? lv.dir[d].nf : lv.dir[d].N;
-  NL = lv.NP + 2 * lv.NO;
-  NA = nd < 0 ? NL : 2 * lv.P;
-}
-
 template <class T>
 int k_fdm(dgmg_handle* h, int l, int nd, const T* r, int waves) {
   const LevelDev<T>& L = LD<T>(h, l);
@@ -815,8 +860,9 @@ int k_fdm(dgmg_handle* h, int l, int nd, const T* r, int waves) {
   sweep_shape(h->lv[l], nd, np, NA, NL);
   T* pb = (T*)h->patch;
   const PatchLat all;
-  int rc = L.dim == 3 ? Kern<T, 3>::fdm(L, nd, NA, NL, r, pb, np[0], np[1], np[2], waves, all, h->stream)
-                      : Kern<T, 2>::fdm(L, nd, NA, NL, r, pb, np[0], np[1], np[2], waves, all, h->stream);
+  const PatchBuf lay = sweep_buf<T>(h->lv[l], nd);
+  int rc = L.dim == 3 ? Kern<T, 3>::fdm(L, nd, NA, NL, r, pb, np[0], np[1], np[2], lay, waves, all, h->stream)
+                      : Kern<T, 2>::fdm(L, nd, NA, NL, r, pb, np[0], np[1], np[2], lay, waves, all, h->stream);
   if (rc) return fail(h, DGMG_EUNSUPPORTED, "no patch-solve kernel for this tile");
   return DGMG_OK;
 }
@@ -872,13 +918,14 @@ int k_sweep(dgmg_handle* h, int l, int nd, T* u, const T* f, T* r, bool u_zero =
   rc = check_hip(h, "patch solve");
   if (rc) return rc;
   T* pb = (T*)h->patch;
+  const PatchBuf lay = sweep_buf<T>(lv, nd);
   // u == 0 on entry: the overlap sum is assigned (no fill of u beforehand, no read of it)
   if (L.se)
-    rc = L.dim == 3 ? Kern<T, 3>::se_combine(L, NA, pb, u, u_zero, h->stream)
-                    : Kern<T, 2>::se_combine(L, NA, pb, u, u_zero, h->stream);
+    rc = L.dim == 3 ? Kern<T, 3>::se_combine(L, NA, pb, u, lay, u_zero, h->stream)
+                    : Kern<T, 2>::se_combine(L, NA, pb, u, lay, u_zero, h->stream);
   else
-    rc = L.dim == 3 ? Kern<T, 3>::combine(L, nd, NA, NL, pb, u, np[0], np[1], np[2], u_zero, h->stream)
-                    : Kern<T, 2>::combine(L, nd, NA, NL, pb, u, np[0], np[1], np[2], u_zero, h->stream);
+    rc = L.dim == 3 ? Kern<T, 3>::combine(L, nd, NA, NL, pb, u, np[0], np[1], np[2], lay, u_zero, h->stream)
+                    : Kern<T, 2>::combine(L, nd, NA, NL, pb, u, np[0], np[1], np[2], lay, u_zero, h->stream);
   if (rc) return fail(h, DGMG_EUNSUPPORTED, "no combine kernel for this order");
   return check_hip(h, "combine");
 }
@@ -903,6 +950,7 @@ int k_msweep(dgmg_handle* h, int l, int nd, T* u, const T* f, T* r, bool reverse
   const auto& cls = h->mcls[l][kind];
   if (u_zero) k_fill_v<T>(h, u, lv.n_dof);
   T* pb = (T*)h->patch;
+  const PatchBuf lay = sweep_buf<T>(lv, nd, false);
   const int nc = (int)cls.size();
   for (int i = 0; i < nc; ++i) {
     const dgmg_handle::MultClass& c = cls[reverse ? nc - 1 - i : i];
@@ -911,11 +959,13 @@ int k_msweep(dgmg_handle* h, int l, int nd, T* u, const T* f, T* r, bool reverse
     if (rc) return rc;
     const T* res = first ? f : r;
     rc = L.dim == 3
-             ? Kern<T, 3>::fdm(L, nd, NA, NL, res, pb, c.n[0], c.n[1], c.n[2], h->waves[l][kind], c.lat, h->stream)
-             : Kern<T, 2>::fdm(L, nd, NA, NL, res, pb, c.n[0], c.n[1], c.n[2], h->waves[l][kind], c.lat, h->stream);
+             ? Kern<T, 3>::fdm(L, nd, NA, NL, res, pb, c.n[0], c.n[1], c.n[2], lay, h->waves[l][kind], c.lat,
+                               h->stream)
+             : Kern<T, 2>::fdm(L, nd, NA, NL, res, pb, c.n[0], c.n[1], c.n[2], lay, h->waves[l][kind], c.lat,
+                               h->stream);
     if (rc) return fail(h, DGMG_EUNSUPPORTED, "no patch-solve kernel for this multiplicative sweep");
-    rc = L.dim == 3 ? Kern<T, 3>::mult_update(L, nd, NA, NL, c.lat, c.n[0], c.n[1], c.n[2], pb, u, h->stream)
-                    : Kern<T, 2>::mult_update(L, nd, NA, NL, c.lat, c.n[0], c.n[1], c.n[2], pb, u, h->stream);
+    rc = L.dim == 3 ? Kern<T, 3>::mult_update(L, nd, NA, NL, c.lat, c.n[0], c.n[1], c.n[2], lay, pb, u, h->stream)
+                    : Kern<T, 2>::mult_update(L, nd, NA, NL, c.lat, c.n[0], c.n[1], c.n[2], lay, pb, u, h->stream);
     if (rc) return fail(h, DGMG_EUNSUPPORTED, "multiplicative update");
   }
   return check_hip(h, "multiplicative sweep");
@@ -2030,6 +2080,7 @@ struct BStep {
   std::vector<int> key;
   int kind = BK_FN, dim = 3, f32 = 0, t[4] = {0, 0, 0, 0};
   int grid = 0, nblk = 0;
+  PatchBuf pb;
   std::vector<char> args;
   std::function<int()> fn;
 };
@@ -2140,14 +2191,23 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
         }
         int np[3], NA, NL;
         sweep_shape(lv, nd, np, NA, NL);
-        FdmArgs<T> fa;
-        fa.L = Lv;
-        fa.r = uz ? f[l] : rl;
-        fa.out = patch;
-        fa.npx = np[0];
-        fa.npy = np[1];
-        fa.npz = np[2];
-        step({major, depthkey, s, i, 1}, BK_FDM, lv.dim, {nd, NA, NL}, np[0] * np[1] * np[2], arg_bytes(fa));
+        const PatchBuf lay = sweep_buf<T>(lv, nd);
+        const T* res = uz ? f[l] : rl;
+        std::vector<char> fargs;
+        if (lv.dim == 3) {
+          fargs = arg_bytes(fdm3_args(Lv, nd, res, patch, np[0], np[1], np[2], lay, PatchLat{}));
+        } else {
+          FdmArgs<T> fa;
+          fa.L = Lv;
+          fa.r = res;
+          fa.out = patch;
+          fa.npx = np[0];
+          fa.npy = np[1];
+          fargs = arg_bytes(fa);
+        }
+        step({major, depthkey, s, i, 1}, BK_FDM, lv.dim, {nd, NA, NL},
+             np[0] * ((np[1] + lay.K - 1) / lay.K) * np[2], std::move(fargs));
+        out.back().pb = lay;
         CombArgs<T> ca;
         ca.L = Lv;
         ca.buf = patch;
@@ -2158,6 +2218,7 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
         ca.npx = np[0];
         ca.npy = np[1];
         ca.npz = np[2];
+        ca.pb = lay;
         ca.nblk = lv.dim == 3 ? Kern<T, 3>::combine_blocks_of(lv.NP, lv.n_elem)
                               : Kern<T, 2>::combine_blocks_of(lv.NP, lv.n_elem);
         ca.assign = uz ? 1 : 0;
@@ -2334,6 +2395,8 @@ int batch_plan(dgmg_batch* b, bool fill) {
         st[0] = 0;
         for (size_t k = i; k < j; ++k) st[k - i + 1] = st[k - i] + v[k].nblk;
         ln.ntot = st[ln.ng];
+        for (size_t k = i; k < j; ++k)
+          if (k == i || (v[k].pb.K - 1) * v[k].pb.step > (ln.pb.K - 1) * ln.pb.step) ln.pb = v[k].pb;
       }
       b->plan[ph].push_back(std::move(ln));
       i = j;
@@ -2362,7 +2425,8 @@ template <class T, int DIM>
 int run_launch_t(dgmg_batch* b, const dgmg_batch::Launch& ln, hipStream_t s) {
   switch (ln.kind) {
     case BK_APPLY: return Kern<T, DIM>::apply_batch(ln.t[0], ln.t[1], blist<ApplyArgs<T>>(b, ln), ln.ntot, s);
-    case BK_FDM: return Kern<T, DIM>::fdm_batch(ln.t[0], ln.t[1], ln.t[2], blist<FdmArgs<T>>(b, ln), ln.ntot, 0, s);
+    case BK_FDM: return Kern<T, DIM>::fdm_batch(ln.t[0], ln.t[1], ln.t[2], blist<FdmArgs<T>>(b, ln),
+                                                  blist<Fdm3Args<T>>(b, ln), ln.ntot, ln.pb, 0, s);
     case BK_COMB: return Kern<T, DIM>::combine_batch(ln.t[0], ln.t[1], blist<CombArgs<T>>(b, ln), ln.ntot, s);
     case BK_XFER:
       return Kern<T, DIM>::transfer_batch(ln.t[0], ln.t[1], ln.t[2] != 0, blist<XferArgs<T>>(b, ln), ln.ntot, s);

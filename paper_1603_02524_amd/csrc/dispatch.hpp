@@ -4,6 +4,7 @@
 
 #include "kernels.hpp"
 #include "kernels_big.hpp"
+#include "kernels_fdm3.hpp"
 #include "kernels_se.hpp"
 #include "kernels_gen.hpp"
 
@@ -79,32 +80,63 @@ bool Kern<T, DIM>::fdm_in_lds(int NA, int NL) {
 }
 
 template <class T, int DIM>
+PatchBuf Kern<T, DIM>::patch_buf(int NP, int nd, int NA, int NL, const int* np, int step, bool whole) {
+  PatchBuf pb;
+  if constexpr (DIM == 3) {
+#define DGMG_CASE(A, B)                                            \
+  if (NA == A && NL == B) {                                        \
+    if constexpr (fdm_lds_total<T, A, B, DIM>() <= LDS_BYTES) {    \
+      pb.swp = 1;                                                  \
+      pb.step = step;                                              \
+      if (whole && order_compiled(NP)) pb.K = fdm3_strip<T>(A, B, nd, np, step); \
+    }                                                              \
+    return pb;                                                     \
+  }
+    DGMG_FDM_LIST(DGMG_CASE)
+#undef DGMG_CASE
+  }
+  return pb;
+}
+
+template <class T, int DIM>
 int Kern<T, DIM>::fdm(const LevelDev<T>& L, int nd, int NA, int NL, const T* r, T* out, int npx,
-                      int npy, int npz, int waves, const PatchLat& lat, hipStream_t s) {
+                      int npy, int npz, const PatchBuf& pb, int waves, const PatchLat& lat, hipStream_t s) {
   const bool whole = lat.start[0] == 0 && lat.start[1] == 0 && lat.start[2] == 0 && lat.stride[0] == 1 &&
                      lat.stride[1] == 1 && lat.stride[2] == 1;
-#define DGMG_CASE(A, B)                                                                   \
-  if (NA == A && NL == B) {                                                               \
-    if constexpr (DIM == 3 && fdm_lds_total<T, A, B, DIM>() > LDS_BYTES)                  \
-      return whole ? fdm_big_launch<T, A, B>(L, nd, r, out, npx, npy, npz, s) : -4;       \
-    else                                                                                  \
-      return fdm_launch_t<T, DIM, A, B>(L, nd, r, out, npx, npy, npz, waves, lat, s);     \
+  if (pb.K > 1 && !whole) return -4;
+  FdmArgs<T> a2;
+  Fdm3Args<T> a3;
+  if constexpr (DIM == 3) {
+    a3 = fdm3_args(L, nd, r, out, npx, npy, npz, pb, lat);
+  } else {
+    a2.L = L;
+    a2.r = r;
+    a2.out = out;
+    a2.npx = npx;
+    a2.npy = npy;
+    a2.lat = lat;
+  }
+#define DGMG_CASE(A, B)                                                                        \
+  if (NA == A && NL == B) {                                                                    \
+    if constexpr (DIM == 3 && fdm_lds_total<T, A, B, DIM>() > LDS_BYTES)                       \
+      return whole ? fdm_big_launch<T, A, B>(L, nd, r, out, npx, npy, npz, s) : -4;            \
+    else if constexpr (DIM == 3)                                                               \
+      return fdm3_go<T, A, B, false>(nd, a3, BatchList<Fdm3Args<T>>{}, a3.nblk, s);            \
+    else                                                                                       \
+      return fdm_go<T, DIM, A, B, false>(nd, a2, BatchList<FdmArgs<T>>{}, npx * npy, waves, s); \
   }
   DGMG_FDM_LIST(DGMG_CASE)
-#undef DGMG_CASE
   if constexpr (DIM == 2) {
-#define DGMG_CASE(A, B) \
-  if (NA == A && NL == B) return fdm_launch_t<T, DIM, A, B>(L, nd, r, out, npx, npy, npz, waves, lat, s);
     DGMG_FDM_LIST_2D(DGMG_CASE)
-#undef DGMG_CASE
   }
+#undef DGMG_CASE
   return gen_fdm_launch<T>(L, nd, NA, NL, r, out, npx, npy, npz, lat, s);  // run-time tile
 }
 
 template <class T, int DIM>
 int Kern<T, DIM>::mult_update(const LevelDev<T>& L, int nd, int NA, int NL, const PatchLat& lat, int npx,
-                              int npy, int npz, const T* buf, T* u, hipStream_t s) {
-  return mult_update_launch<T, DIM>(L, nd, NA, NL, lat, npx, npy, npz, buf, u, s);
+                              int npy, int npz, const PatchBuf& pb, const T* buf, T* u, hipStream_t s) {
+  return mult_update_launch<T, DIM>(L, nd, NA, NL, lat, npx, npy, npz, pb.swp, buf, u, s);
 }
 
 template <class T, int DIM>
@@ -167,14 +199,20 @@ int Kern<T, DIM>::apply_batch(int NP, int mode, const BatchList<ApplyArgs<T>>& b
 }
 
 template <class T, int DIM>
-int Kern<T, DIM>::fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>& bl, int ntot, int waves,
+int Kern<T, DIM>::fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>& bl,
+                            const BatchList<Fdm3Args<T>>& bl3, int ntot, const PatchBuf& pb, int waves,
                             hipStream_t s) {
+  Fdm3Args<T> a3;
+  a3.K = pb.K;
+  a3.step = pb.step;
 #define DGMG_CASE(A, B)                                                          \
   if (NA == A && NL == B) {                                                      \
     if constexpr (DIM == 3 && fdm_lds_total<T, A, B, DIM>() > LDS_BYTES)         \
       return -4;                                                                 \
+    else if constexpr (DIM == 3)                                                 \
+      return fdm3_go<T, A, B, true>(nd, a3, bl3, ntot, s);                       \
     else                                                                         \
-      return fdm_batch_launch<T, DIM, A, B>(nd, bl, ntot, waves, s);             \
+      return fdm_go<T, DIM, A, B, true>(nd, FdmArgs<T>{}, bl, ntot, waves, s);   \
   }
   DGMG_FDM_LIST(DGMG_CASE)
 #undef DGMG_CASE
@@ -209,13 +247,13 @@ int Kern<T, DIM>::transfer_batch(int NPF, int NPC, bool restrict_, const BatchLi
 
 template <class T, int DIM>
 int Kern<T, DIM>::combine(const LevelDev<T>& L, int nd, int NA, int NL, const T* buf, T* u, int npx,
-                          int npy, int npz, bool assign, hipStream_t s) {
+                          int npy, int npz, const PatchBuf& pb, bool assign, hipStream_t s) {
   switch (L.NP) {
 #define DGMG_CASE(NP) \
-  case NP: return combine_launch_t<T, DIM, NP>(L, nd, NA, NL, buf, u, npx, npy, npz, assign, s);
+  case NP: return combine_launch_t<T, DIM, NP>(L, nd, NA, NL, buf, u, npx, npy, npz, pb, assign, s);
     DGMG_NP_LIST(DGMG_CASE)
 #undef DGMG_CASE
-    default: return gen_combine_launch<T>(L, nd, NA, NL, buf, u, npx, npy, assign, s);
+    default: return gen_combine_launch<T>(L, nd, NA, NL, buf, u, npx, npy, pb.swp, assign, s);
   }
 }
 
@@ -247,8 +285,9 @@ int Kern<T, DIM>::se_apply(const LevelDev<T>& L, int mode, const T* x, const T* 
 }
 
 template <class T, int DIM>
-int Kern<T, DIM>::se_combine(const LevelDev<T>& L, int NA, const T* buf, T* u, bool assign, hipStream_t s) {
-  return se_combine_launch<T, DIM>(L, NA, buf, u, assign, s);
+int Kern<T, DIM>::se_combine(const LevelDev<T>& L, int NA, const T* buf, T* u, const PatchBuf& pb, bool assign,
+                             hipStream_t s) {
+  return se_combine_launch<T, DIM>(L, NA, buf, u, pb, assign, s);
 }
 
 template <class T, int DIM>

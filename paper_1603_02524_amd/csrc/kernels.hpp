@@ -50,6 +50,13 @@ struct DirDev {
   // Dirichlet domain): N * n_ec and nf * n_fc
   const int* goff_ec = nullptr;
   const int* goff_fc = nullptr;
+  // 3D tiles solved in LDS: the matrices S in the padded form of fdm3_image, and the
+  // offsets of all positions of the direction in order (patch p's position o at
+  // p step + o, step = the distance of consecutive patches)
+  const T* img_ec = nullptr;
+  const T* img_fc = nullptr;
+  const int* gp_ec = nullptr;
+  const int* gp_fc = nullptr;
 };
 
 template <class T>
@@ -75,6 +82,32 @@ struct PatchLat {
   int start[3] = {0, 0, 0};
   int stride[3] = {1, 1, 1};
 };
+
+// Layout of the patch buffer.  K > 1: strips of K patches along direction 1 whose
+// tiles, `step` planes apart, are summed where they overlap (one tile of
+// (K - 1) step + len planes per strip); K is a power of two.  swp: tiles are stored plane by plane of
+// direction 1, [o1][o2][o0], instead of [o2][o1][o0].
+struct PatchBuf {
+  int K = 1, step = 0, swp = 0;
+};
+
+// A len x len matrix in LDS: rows padded with zeros to the operands' blocks, and a
+// pitch of 2 (mod 16) so that the four rows and four columns of an operand block lie
+// on distinct banks, read as M or as its transpose.  The patch matrices are kept in
+// device memory in this form (fdm3_image values each): a block copies them in 16-byte
+// pieces without index arithmetic.
+template <class T>
+constexpr int fdm3_rows(int len) {
+  return sizeof(T) == 8 ? (len + 3) / 4 * 4 : (len + 15) / 16 * 16;
+}
+template <class T>
+constexpr int fdm3_pitch(int len) {
+  return fdm3_rows<T>(len) + 2;
+}
+template <class T>
+constexpr int fdm3_image(int len) {
+  return fdm3_rows<T>(len) * fdm3_pitch<T>(len);
+}
 
 // Work list of a batched launch: one kernel over the work of many grids.  The
 // launch's logical blocks are split into consecutive ranges, range g
@@ -575,33 +608,12 @@ int apply_batch_launch(int mode, const BatchList<ApplyArgs<T>>& bl, int ntot, hi
 }
 
 // ================================================================ FDM patch solve
-// Patch-solve code choices: the eigenvalue scaling by reciprocal estimate and
-// Newton steps instead of IEEE division, and for rows exactly 16 long the
-// gather / scatter in 16-lane row groups (no index division, per-column table
-// values in registers).
-#ifndef DGMG_FDM_DIV_NR
-#define DGMG_FDM_DIV_NR 1
-#endif
-#ifndef DGMG_FDM_GATHER2D
-#define DGMG_FDM_GATHER2D 1
-#endif
-// Matrix operands of consecutive passes in two register sets used in turn
-// (the next pass's matrix loads while the current pass runs).
-#ifndef DGMG_FDM_PING
-#define DGMG_FDM_PING 1
-#endif
-// FP64: the forward and backward passes of tile dimension 2 fused (the scaled
-// forward results feed the backward product from registers).
-#ifndef DGMG_FDM_FUSE2
-#define DGMG_FDM_FUSE2 1
-#endif
-
 // v / d for d > 0 of moderate magnitude (sums of patch eigenvalues): hardware
-// reciprocal estimate, Newton-Raphson refinement of 1/d, then one residual
-// correction of the quotient (within an ulp or two of the rounded quotient).
+// reciprocal estimate (FP64: to about 2^-26, refined by one Newton-Raphson step), then
+// one residual correction of the quotient, which squares the estimate's error again
+// (within an ulp of the rounded quotient).
 __device__ __forceinline__ double div_nr(double v, double d) {
   double r = __builtin_amdgcn_rcp(d);
-  r = fma(fma(-d, r, 1.0), r, r);
   r = fma(fma(-d, r, 1.0), r, r);
   const double q = v * r;
   return fma(fma(-d, q, v), r, q);
@@ -612,8 +624,8 @@ __device__ __forceinline__ float div_nr(float v, float d) {
   const float q = v * r;
   return fmaf(fmaf(-d, q, v), r, q);
 }
-// One patch per block.  The LDS tile keeps the normal direction fastest:
-// tile[(l2 * NL + l1) * NAP + a], NAP = NA rounded up to an odd pitch so that
+// 2D tiles (3D tiles: kernels_fdm3.hpp), one patch per block.  The LDS tile keeps the
+// normal direction fastest: tile[l1 * NAP + a], NAP = NA rounded up to an odd pitch so that
 // the lines of the fastest pass spread over the LDS banks.  NA = 2P for a
 // face-centred patch (the element-centred size otherwise), NL = NP + 2 N_O.
 // Each contraction pass runs on the matrix cores: the lines of the tile are the
@@ -633,16 +645,11 @@ constexpr int fdm_tile_padded() {
 }
 // Lines up to this length are contracted on the VALU, longer ones on the
 // matrix cores (fdm_pass_any).
-#ifndef DGMG_FDM_VALU_MAXLEN
-#define DGMG_FDM_VALU_MAXLEN 9
-#endif
+constexpr int FDM_VALU_MAXLEN = 9;
 // Default block size of a patch solve (the autotuner may choose another): a
-// thread per line of the longest pass, at most 256; 3D tiles whose passes all
-// run on the matrix cores take 4 waves, the size the autotuner picks for them
-// (16 x 13 x 13, 13^3, 11^3 in FP64 and FP32).
+// thread per line of the longest pass, at most 256.
 template <int NA, int NL, int DIM>
 constexpr int fdm_threads() {
-  if (DIM == 3 && NA > DGMG_FDM_VALU_MAXLEN && NL > DGMG_FDM_VALU_MAXLEN) return 256;
   return imin(256, round64(imax(ipow(NL, DIM - 1), NA * ipow(NL, DIM - 2))));
 }
 template <class T, int NA, int NL, int DIM>
@@ -699,20 +706,6 @@ template <class T, int LEN>
 struct BOp {
   static constexpr int KS = (LEN + 3) / 4, NB = (LEN + 15) / 16;
   T b[NB][KS];
-  // the matrix of another length with the same register shape (KS, NB)
-  template <int LEN2>
-  __device__ __forceinline__ void load_as(const T* __restrict__ Bm) {
-    static_assert((LEN2 + 3) / 4 == KS && (LEN2 + 15) / 16 == NB, "register shapes differ");
-    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const int k = 4 * ks + lk, j = nb * 16 + li;
-        const T v = Bm[imin(k, LEN2 - 1) * LEN2 + imin(j, LEN2 - 1)];
-        b[nb][ks] = (k < LEN2 && j < LEN2) ? v : T(0);
-      }
-  }
   __device__ __forceinline__ void load(const T* __restrict__ Bm) {
     const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
 #pragma unroll
@@ -743,14 +736,9 @@ struct NoPost {
 // results of lines past the set are discarded), and stores of rows j >= LEN or
 // of lines past the set go to the lane's slot of `trash` (64 values, dead
 // storage) instead of being masked.
-template <class T, int NA, int NL, int DIM, int TD, class Post = NoPost, int BLEN = (TD == 0 ? NA : NL),
-          bool TAIL = false>
+template <class T, int NA, int NL, int DIM, int TD, class Post>
 __device__ __forceinline__ void fdm_pass(T* __restrict__ tile, T* __restrict__ trash,
-                                         const BOp<T, BLEN>& B, Post post = Post(),
-                                         const T* __restrict__ tail = nullptr) {
-  static_assert(BOp<T, BLEN>::KS == BOp<T, TD == 0 ? NA : NL>::KS &&
-                    BOp<T, BLEN>::NB == BOp<T, TD == 0 ? NA : NL>::NB,
-                "operand register shape");
+                                         const BOp<T, TD == 0 ? NA : NL>& B, Post post) {
   // Product D = B^T V^T: the A operand is B^T (held as B.b), the B operand the
   // lines; lane (li, lk) then owns output column li = its own line, rows
   // j = 16 nb + row(lk, r), so results go back along the line it loaded.
@@ -774,24 +762,11 @@ __device__ __forceinline__ void fdm_pass(T* __restrict__ tile, T* __restrict__ t
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb] = typename M::acc_t{0, 0, 0, 0};
 #pragma unroll
-    for (int ks = 0; ks < (TAIL ? KS - 1 : KS); ++ks) {
+    for (int ks = 0; ks < KS; ++ks) {
       const int k = imin(4 * ks + lk, LEN - 1);
       const T a = tile[base + k * STRIDE];
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) acc[nb] = M::op(B.b[nb][ks], a, acc[nb]);
-    }
-    if constexpr (TAIL) {
-      // LEN = 4 (KS - 1) + 1: the last contraction index is alone in its group
-      // of four, so it is added on the VALU as a rank-one update (tail = row
-      // LEN - 1 of B in LDS) instead of a fourth product that is 3/4 padding
-      const T at = tile[base + (LEN - 1) * STRIDE];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int j = imin(nb * 16 + M::row(lk, r), LEN - 1);
-          acc[nb][r] = __builtin_fma(tail[j], at, acc[nb][r]);
-        }
     }
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
@@ -803,84 +778,6 @@ __device__ __forceinline__ void fdm_pass(T* __restrict__ tile, T* __restrict__ t
         T* dst = ok ? tile + base + jc * STRIDE : trash + lane;
         *dst = post(lc, jc, acc[nb][r]);
       }
-  }
-}
-
-// The last forward and the first backward contraction of tile dimension 2
-// in one pass (FP64, lines of 5 to 16): a line block's forward results,
-// scaled by post(line, j, value), stay in registers as the operand of the
-// backward product instead of going through the tile and a barrier.  The f64
-// result layout makes this possible: lane (li, lk) ends the forward product
-// holding rows j = lk + 4r of its line li, which are exactly the contraction
-// indices k = 4 ks + lk (ks = r) it supplies to the next product.  Rows
-// j >= LEN are set to 0 (the backward matrix is zero there as well).  TAIL
-// as in fdm_pass, for both products (tail, tailb: the last rows of the
-// forward and backward matrices).
-template <int NA, int NL, int DIM, class Post, int BLEN, bool TAIL>
-__device__ __forceinline__ void fdm_pass_fused2(double* __restrict__ tile, double* __restrict__ trash,
-                                                const BOp<double, BLEN>& Bf, const BOp<double, BLEN>& Bb,
-                                                Post post, const double* __restrict__ tail,
-                                                const double* __restrict__ tailb) {
-  using T = double;
-  constexpr int TD = 2;
-  constexpr int LEN = NL;
-  constexpr int LINES = NA * ipow(NL, DIM - 2);
-  constexpr int STRIDE = fdm_pitch<NA>() * NL;
-  constexpr int KS = BOp<T, LEN>::KS, NB = BOp<T, LEN>::NB, MB = (LINES + 15) / 16;
-  static_assert(DIM == 3 && NB == 1 && KS >= 2, "lines of 5 to 16 values");
-  static_assert(BOp<T, BLEN>::KS == KS && BOp<T, BLEN>::NB == NB, "operand register shape");
-  using M = Mfma<T>;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nw = blockDim.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  for (int mb = wave; mb < MB; mb += nw) {
-    const int line = mb * 16 + li;
-    const bool lv = line < LINES;
-    const int lc = imin(line, LINES - 1);
-    const int base = fdm_line_base<NA, NL, TD>(lc);
-    typename M::acc_t acc = typename M::acc_t{0, 0, 0, 0};
-#pragma unroll
-    for (int ks = 0; ks < (TAIL ? KS - 1 : KS); ++ks) {
-      const int k = imin(4 * ks + lk, LEN - 1);
-      acc = M::op(Bf.b[0][ks], tile[base + k * STRIDE], acc);
-    }
-    if constexpr (TAIL) {
-      const T at = tile[base + (LEN - 1) * STRIDE];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int j = imin(M::row(lk, r), LEN - 1);
-        acc[r] = __builtin_fma(tail[j], at, acc[r]);
-      }
-    }
-    typename M::acc_t out = typename M::acc_t{0, 0, 0, 0};
-    T v[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = M::row(lk, r);  // = 4 r + lk: the next product's contraction index
-      const T sv = post(lc, imin(j, LEN - 1), acc[r]);
-      v[r] = j < LEN ? sv : T(0);
-    }
-#pragma unroll
-    for (int r = 0; r < (TAIL ? KS - 1 : KS); ++r) out = M::op(Bb.b[0][r], v[r], out);
-    if constexpr (TAIL) {
-      // the last contraction index LEN - 1 = 4 (KS - 1) + 0 is held by lane
-      // (li, 0) in register KS - 1: broadcast it to the line's four lanes,
-      // rank-one update
-      const T at = __shfl(v[KS - 1], li, 64);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int j = imin(M::row(lk, r), LEN - 1);
-        out[r] = __builtin_fma(tailb[j], at, out[r]);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = M::row(lk, r);
-      const bool ok = lv && j < LEN;
-      const int jc = imin(j, LEN - 1);
-      T* dst = ok ? tile + base + jc * STRIDE : trash + lane;
-      *dst = out[r];
-    }
   }
 }
 
@@ -944,7 +841,7 @@ __device__ __forceinline__ void fdm_pass_valu(T* __restrict__ tile, const T* __r
 }
 
 // Contraction pass of tile dimension TD on the unit that suits its length:
-// lines up to DGMG_FDM_VALU_MAXLEN long go to the VALU (the matrix-core form
+// lines up to FDM_VALU_MAXLEN long go to the VALU (the matrix-core form
 // would pad a length-9 line to 12 x 16, 42 % useful work), longer ones to the
 // matrix cores (measured on an MI355X: length 13 lateral passes on the VALU made
 // the 16 x 13 x 13 patch solve 9 % slower, every pass on the VALU 35 %).
@@ -952,69 +849,54 @@ template <class T, int NA, int NL, int DIM, int TD, class Post = NoPost>
 __device__ __forceinline__ void fdm_pass_any(T* __restrict__ tile, T* __restrict__ trash, const T* __restrict__ Bm,
                                              const T* __restrict__ BTm, Post post = Post()) {
   constexpr int LEN = TD == 0 ? NA : NL;
-  constexpr bool VALU = LEN <= DGMG_FDM_VALU_MAXLEN;
+  constexpr bool VALU = LEN <= FDM_VALU_MAXLEN;
   if constexpr (VALU) fdm_pass_valu<T, NA, NL, DIM, TD, Post>(tile, BTm, post);
   else fdm_pass<T, NA, NL, DIM, TD, Post>(tile, trash, Bm, post);
 }
 
 // Tile geometry of one sweep kind, all compile-time: ND = normal direction of a
 // face-centred patch (-1: element-centred).  Grid-natural order has direction 0
-// fastest with lengths L0, L1, L2; the LDS tile keeps the normal direction
-// fastest: tile[(l2 NL + l1) NAP + a].
+// fastest with lengths L0, L1; the LDS tile keeps the normal direction
+// fastest: tile[l1 NAP + a].
 template <int DIM, int ND, int NA, int NL>
 struct FdmShape {
   static constexpr int L0 = ND == 0 ? NA : NL;
   static constexpr int L1 = ND == 1 ? NA : NL;
-  static constexpr int L2 = DIM == 3 ? (ND == 2 ? NA : NL) : 1;
-  static constexpr int TS = L0 * L1 * L2;
-  static constexpr int NROW = L1 * L2;  // rows of the grid-natural order (fixed o1, o2)
+  static constexpr int TS = L0 * L1;
+  static constexpr int NROW = L1;  // rows of the grid-natural order
   static constexpr int NAP = fdm_pitch<NA>();
   // tile stride of direction 0 (the normal / fastest tile dimension unless ND > 0)
   static constexpr int C0 = ND <= 0 ? 1 : NAP;
   // grid direction of tile dimension t (t = 0: the normal / fastest one)
-  static constexpr int gd(int t) {
-    return ND <= 0 ? t : (t == 0 ? ND : (t <= ND ? t - 1 : t));
-  }
-  static __device__ __forceinline__ int tpos(int o0, int o1, int o2) {
-    const int o[3] = {o0, o1, o2};
-    return ((DIM == 3 ? o[gd(2)] * NL : 0) + o[gd(1)]) * NAP + o[gd(0)];
-  }
-  static __device__ __forceinline__ void split(int q, int& o0, int& o1, int& o2) {
-    o0 = q % L0;
-    const int rest = q / L0;
-    o1 = DIM == 3 ? rest % L1 : rest;
-    o2 = DIM == 3 ? rest / L1 : 0;
+  static constexpr int gd(int t) { return ND <= 0 ? t : 1 - t; }
+  static __device__ __forceinline__ int tpos(int o0, int o1) {
+    const int o[2] = {o0, o1};
+    return o[gd(1)] * NAP + o[gd(0)];
   }
 };
 
-// Minimum waves per SIMD asked of the compiler: 6 for the 16 x 13 x 13 tile
-// (P = 8 face-centred patches), so that its register use stays within 80 and
-// six 4-wave blocks fit a CU, as its LDS allows; no constraint otherwise.
-template <int NA, int NL>
-constexpr int fdm_min_waves() {
-  return NA == 16 && NL == 13 ? 6 : 1;
-}
 template <class T>
 struct FdmArgs {
   LevelDev<T> L;
   const T* r = nullptr;  // residual (level vector)
-  T* out = nullptr;      // weighted corrections, one tile per patch of the launch
-  int npx = 1, npy = 1, npz = 1;
+  T* out = nullptr;      // weighted corrections, one tile per patch (strip) of the launch
+  int npx = 1, npy = 1;
   PatchLat lat;
 };
 
 // BATCH: the arguments come from the work list bl (ntot logical blocks in all)
 template <class T, int DIM, int NA, int NL, int ND, bool BATCH = false>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(fdm_min_waves<NA, NL>()))) fdm_kernel(FdmArgs<T> a0, BatchList<FdmArgs<T>> bl, int ntot) {
+__global__ void __launch_bounds__(512) fdm_kernel(FdmArgs<T> a0, BatchList<FdmArgs<T>> bl, int ntot) {
+  static_assert(DIM == 2, "3D tiles: fdm3_kernel");
   using S = FdmShape<DIM, ND, NA, NL>;
   constexpr int TS = S::TS;
   constexpr int NMAX = imax(NA, NL);
   constexpr int GU = 4;  // elements gathered per thread before their LDS stores (loads in flight)
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* tile = reinterpret_cast<T*>(smem_raw);
-  __shared__ int goff[3][NMAX];  // offsets into the level vector (< 2^31 unknowns), -1 outside
-  __shared__ T wv[3][NMAX];
-  __shared__ T lv[3][NMAX];
+  __shared__ int goff[2][NMAX];  // offsets into the level vector (< 2^31 unknowns), -1 outside
+  __shared__ T wv[2][NMAX];
+  __shared__ T lv[2][NMAX];
   // rowoff is dead once the gather is done: the contraction passes use it as
   // their store trash (64 values)
   __shared__ __align__(8) int rowoff[imax(S::NROW, 64 * (int)sizeof(T) / (int)sizeof(int))];
@@ -1029,23 +911,22 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(fdm_mi
     pid = batch_pick(bl, b, sargs);
     ap = sargs;
   } else {
-    pid = xcd_block(a0.npx * a0.npy * (DIM == 3 ? a0.npz : 1));
+    pid = xcd_block(a0.npx * a0.npy);
     if (pid < 0) return;
     ap = &a0;
   }
   const LevelDev<T>& L = ap->L;
   const T* __restrict__ r = ap->r;
   T* __restrict__ out = ap->out;
-  const int npx = ap->npx, npy = ap->npy;
+  const int npx = ap->npx;
   const PatchLat& lat = ap->lat;
   if (inactive(L.active)) return;
   const int tid = threadIdx.x, nth = blockDim.x;
-  int p[3];
+  int p[2];
   p[0] = lat.start[0] + lat.stride[0] * (pid % npx);
-  p[1] = lat.start[1] + lat.stride[1] * ((pid / npx) % npy);
-  p[2] = DIM == 3 ? lat.start[2] + lat.stride[2] * (pid / (npx * npy)) : 0;
-  const int* go[3] = {nullptr, nullptr, nullptr};
-  const T* wg[3] = {nullptr, nullptr, nullptr};
+  p[1] = lat.start[1] + lat.stride[1] * (pid / npx);
+  const int* go[2] = {nullptr, nullptr};
+  const T* wg[2] = {nullptr, nullptr};
 #pragma unroll
   for (int d = 0; d < DIM; ++d) {
     const DirDev<T>& dd = L.dir[d];
@@ -1060,19 +941,16 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(fdm_mi
       lv[d][o] = lam[o];
     }
   }
-  // per row (o1, o2) of the grid-natural order: its offset in the level vector
-  // (-1 outside a Dirichlet domain) and its tile position (its weight w1 w2 is
-  // formed from the per-direction tables at the scatter)
+  // per row of the grid-natural order: its offset in the level vector (-1 outside a
+  // Dirichlet domain) and its tile position
   for (int rw = tid; rw < S::NROW; rw += nth) {
-    const int o1 = DIM == 3 ? rw % S::L1 : rw, o2 = DIM == 3 ? rw / S::L1 : 0;
-    const int g1 = go[1][o1], g2 = DIM == 3 ? go[2][o2] : 0;
-    rowoff[rw] = (g1 | g2) < 0 ? -1 : g1 + g2;
-    rowpos[rw] = S::tpos(0, o1, o2);
+    rowoff[rw] = go[1][rw];
+    rowpos[rw] = S::tpos(0, rw);
   }
   // 1D matrices of each tile dimension: forward t_j = sum_k S_kj r_k uses S,
   // backward u_k = sum_j S_kj t_j uses S^T (both row-major)
-  const T* fwd[3] = {nullptr, nullptr, nullptr};
-  const T* bwd[3] = {nullptr, nullptr, nullptr};
+  const T* fwd[2] = {nullptr, nullptr};
+  const T* bwd[2] = {nullptr, nullptr};
 #pragma unroll
   for (int t = 0; t < DIM; ++t) {
     const int d = S::gd(t);
@@ -1085,31 +963,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(fdm_mi
       bwd[t] = dd.ST_ec + (int64_t)p[d] * NL * NL;
     }
   }
-  // two operand register sets used in turn (3D, every pass on the matrix cores,
-  // both lengths with the same register shape)
-  constexpr bool PING = DGMG_FDM_PING && DIM == 3 && NA > DGMG_FDM_VALU_MAXLEN &&
-                        NL > DGMG_FDM_VALU_MAXLEN && BOp<T, NA>::KS == BOp<T, NL>::KS &&
-                        BOp<T, NA>::NB == BOp<T, NL>::NB;
-  BOp<T, NA> P, Q;
-  // FP64 with lateral lines of at most 16: the dimension-2 passes fused
-  constexpr bool FUSE2 = DGMG_FDM_FUSE2 && PING && sizeof(T) == 8 && NL <= 16;
-  // FP64 lateral lines with NL = 1 (mod 4): the last row of each of their
-  // four matrices in LDS for the rank-one tail of those passes (in FP32 the
-  // 16x16x4 product costs half as much and the tail measured slower)
-  constexpr bool TAILK = PING && NL % 4 == 1 && sizeof(T) == 8;
-  __shared__ T sBt[TAILK ? 4 : 1][TAILK ? NL : 1];
-  if constexpr (TAILK) {
-    const T* rows[4] = {fwd[1], fwd[2], bwd[2], bwd[1]};
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-      for (int j = tid; j < NL; j += nth) sBt[m][j] = rows[m][(NL - 1) * NL + j];
-  }
-  if constexpr (PING) P.load(fwd[0]);
   __syncthreads();
   // gather R_s r in grid-natural order (coalesced global reads); GU loads are
   // issued before their LDS stores; positions outside a Dirichlet domain read
   // r[0] and store 0
-  constexpr bool G2D = DGMG_FDM_GATHER2D && S::L0 == 16;  // shorter rows would idle lanes (measured slower)
+  constexpr bool G2D = S::L0 == 16;  // shorter rows would idle lanes (measured slower)
   if constexpr (G2D) {
     // lanes in groups of 16 along direction 0 (o0 = tid % 16), rows in steps of nth / 16
     const int o0 = tid & 15, rstep = nth >> 4;
@@ -1157,78 +1015,32 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(fdm_mi
   __syncthreads();
   T* trash = reinterpret_cast<T*>(rowoff);
   // the last forward pass divides each result by the sum of the 1D eigenvalues
-  // of its tile position: line = a + NA l1 (3D; a in 2D), j = l2 (3D; l1 in 2D)
+  // of its tile position: line = a, j = l1
   const auto scale = [&](int line, int j, T v) -> T {
     const int a = line % NA;
-    T den = lv[S::gd(0)][a] + lv[S::gd(1)][DIM == 3 ? line / NA : j];
-    if (DIM == 3) den += lv[S::gd(2)][j];
-    if constexpr (DGMG_FDM_DIV_NR) return div_nr(v, den);
-    else return v / den;
+    return div_nr(v, lv[S::gd(0)][a] + lv[S::gd(1)][j]);
   };
-  if constexpr (PING) {
-    // every pass on the matrix cores with one register shape: the next pass's
-    // matrix is loaded into the idle set while the current pass runs
-    Q.template load_as<NL>(fwd[1]);
-    fdm_pass<T, NA, NL, DIM, 0, NoPost, NA>(tile, trash, P);
-    __syncthreads();
-    P.template load_as<NL>(fwd[2]);
-    fdm_pass<T, NA, NL, DIM, 1, NoPost, NA, TAILK>(tile, trash, Q, NoPost(), sBt[0]);
-    __syncthreads();
-    Q.template load_as<NL>(bwd[2]);
-    if constexpr (FUSE2) {
-      // forward and backward along dimension 2 in one pass (no tile round trip)
-      fdm_pass_fused2<NA, NL, DIM, decltype(scale), NA, TAILK>(tile, trash, P, Q, scale, sBt[1], sBt[2]);
-      P.template load_as<NL>(bwd[1]);
-      __syncthreads();
-    } else {
-      fdm_pass<T, NA, NL, DIM, 2, decltype(scale), NA, TAILK>(tile, trash, P, scale, sBt[1]);
-      __syncthreads();
-      P.template load_as<NL>(bwd[1]);
-      fdm_pass<T, NA, NL, DIM, 2, NoPost, NA, TAILK>(tile, trash, Q, NoPost(), sBt[2]);
-      __syncthreads();
-    }
-    Q.template load_as<NA>(bwd[0]);
-    fdm_pass<T, NA, NL, DIM, 1, NoPost, NA, TAILK>(tile, trash, P, NoPost(), sBt[3]);
-    __syncthreads();
-    fdm_pass<T, NA, NL, DIM, 0, NoPost, NA>(tile, trash, Q);
-    __syncthreads();
-  } else {
-    fdm_pass_any<T, NA, NL, DIM, 0>(tile, trash, fwd[0], bwd[0]);
-    __syncthreads();
-    if constexpr (DIM == 3) {
-      fdm_pass_any<T, NA, NL, DIM, 1>(tile, trash, fwd[1], bwd[1]);
-      __syncthreads();
-      fdm_pass_any<T, NA, NL, DIM, 2>(tile, trash, fwd[2], bwd[2], scale);
-    } else {
-      fdm_pass_any<T, NA, NL, DIM, 1>(tile, trash, fwd[1], bwd[1], scale);
-    }
-    __syncthreads();
-    if constexpr (DIM == 3) {
-      fdm_pass_any<T, NA, NL, DIM, 2>(tile, trash, bwd[2], fwd[2]);
-      __syncthreads();
-    }
-    fdm_pass_any<T, NA, NL, DIM, 1>(tile, trash, bwd[1], fwd[1]);
-    __syncthreads();
-    fdm_pass_any<T, NA, NL, DIM, 0>(tile, trash, bwd[0], fwd[0]);
-    __syncthreads();
-  }
-  // weighted result w_s (.) Delta u_s in grid-natural order; row weight w1 w2
-  const auto row_w = [&](int rw) -> T {
-    if constexpr (DIM == 3) return wv[1][rw % S::L1] * wv[2][rw / S::L1];
-    else return wv[1][rw];
-  };
+  fdm_pass_any<T, NA, NL, DIM, 0>(tile, trash, fwd[0], bwd[0]);
+  __syncthreads();
+  fdm_pass_any<T, NA, NL, DIM, 1>(tile, trash, fwd[1], bwd[1], scale);
+  __syncthreads();
+  fdm_pass_any<T, NA, NL, DIM, 1>(tile, trash, bwd[1], fwd[1]);
+  __syncthreads();
+  fdm_pass_any<T, NA, NL, DIM, 0>(tile, trash, bwd[0], fwd[0]);
+  __syncthreads();
+  // weighted result w_s (.) Delta u_s in grid-natural order
   T* dst = out + (int64_t)pid * TS;
   if constexpr (G2D) {
     const int o0 = tid & 15, rstep = nth >> 4;
     if (o0 < S::L0) {
       const T w0 = wv[0][o0];
       const int pc = o0 * S::C0;
-      for (int rw = tid >> 4; rw < S::NROW; rw += rstep) dst[rw * S::L0 + o0] = (w0 * row_w(rw)) * tile[rowpos[rw] + pc];
+      for (int rw = tid >> 4; rw < S::NROW; rw += rstep) dst[rw * S::L0 + o0] = (w0 * wv[1][rw]) * tile[rowpos[rw] + pc];
     }
   } else {
     for (int q = tid; q < TS; q += nth) {
       const int o0 = q % S::L0, rw = q / S::L0;
-      dst[q] = (wv[0][o0] * row_w(rw)) * tile[rowpos[rw] + o0 * S::C0];
+      dst[q] = (wv[0][o0] * wv[1][rw]) * tile[rowpos[rw] + o0 * S::C0];
     }
   }
 }
@@ -1256,31 +1068,8 @@ int fdm_go(int nd, const FdmArgs<T>& a, const BatchList<FdmArgs<T>>& bl, int nlo
   }
   if (nd == 0) fdm_launch_nd<T, DIM, NA, NL, 0, BATCH>(a, bl, nlog, th, shm, s);
   else if (nd == 1) fdm_launch_nd<T, DIM, NA, NL, 1, BATCH>(a, bl, nlog, th, shm, s);
-  else if constexpr (DIM == 3) fdm_launch_nd<T, DIM, NA, NL, 2, BATCH>(a, bl, nlog, th, shm, s);
   else return -4;
   return 0;
-}
-
-template <class T, int DIM, int NA, int NL>
-int fdm_launch_t(const LevelDev<T>& L, int nd, const T* r, T* out, int npx, int npy, int npz,
-                 int waves, const PatchLat& lat, hipStream_t s) {
-  FdmArgs<T> a;
-  a.L = L;
-  a.r = r;
-  a.out = out;
-  a.npx = npx;
-  a.npy = npy;
-  a.npz = npz;
-  a.lat = lat;
-  const int npatch = npx * npy * (DIM == 3 ? npz : 1);
-  return fdm_go<T, DIM, NA, NL, false>(nd, a, BatchList<FdmArgs<T>>{}, npatch, waves, s);
-}
-
-// One launch over the patch solves of many grids (same tile and normal): ntot
-// logical blocks, one per patch, grid g's patches in the range of bl.
-template <class T, int DIM, int NA, int NL>
-int fdm_batch_launch(int nd, const BatchList<FdmArgs<T>>& bl, int ntot, int waves, hipStream_t s) {
-  return fdm_go<T, DIM, NA, NL, true>(nd, FdmArgs<T>{}, bl, ntot, waves, s);
 }
 
 // ================================================================ multiplicative update
@@ -1292,7 +1081,7 @@ int fdm_batch_launch(int nd, const BatchList<FdmArgs<T>>& bl, int ntot, int wave
 // Dirichlet domain are skipped.
 template <class T, int DIM>
 __global__ void __launch_bounds__(256) mult_update_kernel(LevelDev<T> L, int nd, int NA, int NL, PatchLat lat,
-                                                          int npx, int npy, const T* __restrict__ buf,
+                                                          int npx, int npy, int swp, const T* __restrict__ buf,
                                                           T* __restrict__ u) {
   if (inactive(L.active)) return;
   const int pid = blockIdx.x;
@@ -1311,7 +1100,7 @@ __global__ void __launch_bounds__(256) mult_update_kernel(LevelDev<T> L, int nd,
   const T* src = buf + (int64_t)pid * ts;
   for (int q = threadIdx.x; q < ts; q += blockDim.x) {
     const int o0 = q % len[0], rw = q / len[0];
-    const int o1 = rw % len[1], o2 = rw / len[1];
+    const int o1 = swp ? rw / len[2] : rw % len[1], o2 = swp ? rw % len[2] : rw / len[1];
     const int g0 = go[0][o0], g1 = go[1][o1], g2 = DIM == 3 ? go[2][o2] : 0;
     if ((g0 | g1 | g2) < 0) continue;
     u[g0 + g1 + g2] += src[q];
@@ -1320,11 +1109,11 @@ __global__ void __launch_bounds__(256) mult_update_kernel(LevelDev<T> L, int nd,
 
 template <class T, int DIM>
 int mult_update_launch(const LevelDev<T>& L, int nd, int NA, int NL, const PatchLat& lat, int npx, int npy,
-                       int npz, const T* buf, T* u, hipStream_t s) {
+                       int npz, int swp, const T* buf, T* u, hipStream_t s) {
   const int npatch = npx * npy * (DIM == 3 ? npz : 1);
   if (npatch <= 0) return 0;
-  hipLaunchKernelGGL((mult_update_kernel<T, DIM>), dim3(npatch), dim3(256), 0, s, L, nd, NA, NL, lat, npx, npy, buf,
-                     u);
+  hipLaunchKernelGGL((mult_update_kernel<T, DIM>), dim3(npatch), dim3(256), 0, s, L, nd, NA, NL, lat, npx, npy, swp,
+                     buf, u);
   return 0;
 }
 
@@ -1355,6 +1144,7 @@ struct CombArgs {
   T* u = nullptr;
   int nd = -1, NA = 0, NL = 0;
   int npx = 1, npy = 1, npz = 1;
+  PatchBuf pb;
   int nblk = 0;
   int assign = 0;
 };
@@ -1396,9 +1186,11 @@ __global__ void __launch_bounds__(256) combine_kernel(CombArgs<T> a0, BatchList<
   const int N1 = L.dir[0].N, N2 = L.dir[1].N, NO = L.NO;
   int len[3] = {1, 1, 1};
   for (int d = 0; d < DIM; ++d) len[d] = (d == nd) ? NA : NL;
-  const int64_t TS = (int64_t)len[0] * len[1] * len[2];
-  const int64_t pst[3] = {1, npx, (int64_t)npx * npy};
-  const int64_t ost[3] = {1, len[0], (int64_t)len[0] * len[1]};
+  const int K = ap->pb.K, step = ap->pb.step, swp = ap->pb.swp;
+  const int nsy = (npy + K - 1) / K;
+  const int64_t TS = (int64_t)len[0] * ((K - 1) * step + len[1]) * len[2];
+  const int64_t pst[3] = {1, npx, (int64_t)npx * nsy};
+  const int64_t ost[3] = {1, swp ? (int64_t)len[0] * len[2] : len[0], swp ? len[0] : (int64_t)len[0] * len[1]};
   for (int q = tid; q < ne * DIM * NP; q += nth) {
     const int el = q / (DIM * NP), rem = q - el * DIM * NP, d = rem / NP, i = rem - d * NP;
     const int e = e0 + el;
@@ -1414,6 +1206,16 @@ __global__ void __launch_bounds__(256) combine_kernel(CombArgs<T> a0, BatchList<
       if (i < NO && (dd.periodic || md > 0)) { cp[c] = (md - 1 + N) % N; co[c++] = NP + NO + i; }
       cp[c] = md; co[c++] = i + NO;
       if (i >= NP - NO && (dd.periodic || md < N - 1)) { cp[c] = (md + 1) % N; co[c++] = i - NP + NO; }
+    }
+    if (d == 1 && K > 1) {  // strips: patches of one strip meet in one plane of its summed tile
+      int n = 0;
+      for (int k = 0; k < c; ++k) {
+        const int st = cp[k] >> __builtin_ctz(K), pl = (cp[k] & (K - 1)) * step + co[k];
+        bool same = false;
+        for (int j = 0; j < n; ++j) same = same || (cp[j] == st && co[j] == pl);
+        if (!same) { cp[n] = st; co[n++] = pl; }
+      }
+      c = n;
     }
     ccnt[el][d][i] = c;
     for (int k = 0; k < MAXC; ++k) cadr[el][d][i][k] = k < c ? cp[k] * pst[d] * TS + co[k] * ost[d] : 0;
@@ -1472,7 +1274,7 @@ inline int combine_maxc(int NP, int NO) { return 2 * NO > NP ? 3 : 2; }
 
 template <class T, int DIM, int NP>
 int combine_launch_t(const LevelDev<T>& L, int nd, int NA, int NL, const T* buf, T* u, int npx,
-                     int npy, int npz, bool assign, hipStream_t s) {
+                     int npy, int npz, const PatchBuf& pb, bool assign, hipStream_t s) {
   CombArgs<T> a;
   a.L = L;
   a.buf = buf;
@@ -1483,6 +1285,7 @@ int combine_launch_t(const LevelDev<T>& L, int nd, int NA, int NL, const T* buf,
   a.npx = npx;
   a.npy = npy;
   a.npz = npz;
+  a.pb = pb;
   a.nblk = combine_blocks<DIM, NP>(L.n_elem);
   a.assign = assign ? 1 : 0;
   if (combine_maxc(NP, L.NO) == 3)
@@ -1655,6 +1458,9 @@ int transfer_batch_launch(bool restrict_, const BatchList<XferArgs<T>>& bl, int 
 }
 
 // ================================================================ dispatch (instantiated per T, DIM)
+template <class T>
+struct Fdm3Args;  // kernels_fdm3.hpp
+
 template <class T, int DIM>
 struct Kern {
   // scratch: apply_big_scratch(n_elem, NP) elements (3D levels with NP = 33 only).
@@ -1665,10 +1471,14 @@ struct Kern {
   // lat: the patches of this launch (all of them: PatchLat{}); large tiles
   // (3D P = 32) take only the whole partition
   static int fdm(const LevelDev<T>& L, int nd, int NA, int NL, const T* r, T* out, int npx, int npy,
-                 int npz, int waves, const PatchLat& lat, hipStream_t s);
+                 int npz, const PatchBuf& pb, int waves, const PatchLat& lat, hipStream_t s);
+  // patch-buffer layout of a level's sweep (np patches per direction, `step` node
+  // positions apart along direction 1); whole = false: a launch over some of the
+  // patches (strips of one patch)
+  static PatchBuf patch_buf(int NP, int nd, int NA, int NL, const int* np, int step, bool whole);
   // u += the unweighted corrections of one patch-solve launch (disjoint patches)
   static int mult_update(const LevelDev<T>& L, int nd, int NA, int NL, const PatchLat& lat, int npx, int npy,
-                         int npz, const T* buf, T* u, hipStream_t s);
+                         int npz, const PatchBuf& pb, const T* buf, T* u, hipStream_t s);
   // Batched launches (work lists over many grids, see BatchList): the same
   // kernels as above with per-grid arguments.  Block counts per grid:
   // apply_blocks, one per patch, combine_blocks, xfer_blocks.  -4 where the
@@ -1678,7 +1488,10 @@ struct Kern {
   static int xfer_blocks_of(int NPF, int n_elem);
   static bool mode3_ok(const LevelDev<T>& L);
   static int apply_batch(int NP, int mode, const BatchList<ApplyArgs<T>>& bl, int ntot, hipStream_t s);
-  static int fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>& bl, int ntot, int waves, hipStream_t s);
+  // pb: the longest strip of the launch's grids
+  // (arguments: bl in 2D, bl3 in 3D)
+  static int fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>& bl, const BatchList<Fdm3Args<T>>& bl3,
+                       int ntot, const PatchBuf& pb, int waves, hipStream_t s);
   static int combine_batch(int NP, int maxc, const BatchList<CombArgs<T>>& bl, int ntot, hipStream_t s);
   static int transfer_batch(int NPF, int NPC, bool restrict_, const BatchList<XferArgs<T>>& bl, int ntot,
                             hipStream_t s);
@@ -1689,13 +1502,14 @@ struct Kern {
   static bool fdm_in_lds(int NA, int NL);
   // assign: u = the overlap sum (u is zero on entry) instead of u += it
   static int combine(const LevelDev<T>& L, int nd, int NA, int NL, const T* buf, T* u, int npx,
-                     int npy, int npz, bool assign, hipStream_t s);
+                     int npy, int npz, const PatchBuf& pb, bool assign, hipStream_t s);
   // tmp: scratch of transfer_big_scratch(n_elem, NP, NPc) elements (3D levels with NP = 33 only)
   static int transfer(const LevelDev<T>& Lf, bool restrict_, const T* in, T* out, T* tmp, hipStream_t s);
   // Continuous spectral-element levels (lattice vectors, kernels_se.hpp).
   // ebuf: element-major scratch of n_elem * NP^DIM elements.  Modes 0 and 1.
   static int se_apply(const LevelDev<T>& L, int mode, const T* x, const T* f, T* y, T* ebuf, hipStream_t s);
-  static int se_combine(const LevelDev<T>& L, int NA, const T* buf, T* u, bool assign, hipStream_t s);
+  static int se_combine(const LevelDev<T>& L, int NA, const T* buf, T* u, const PatchBuf& pb, bool assign,
+                        hipStream_t s);
   // ebuf (restriction only): n_elem * NPc^DIM elements
   static int se_transfer(const LevelDev<T>& Lf, const LevelDev<T>& Lc, bool restrict_, const T* in, T* out,
                          T* ebuf, hipStream_t s);

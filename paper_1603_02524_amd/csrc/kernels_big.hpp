@@ -552,8 +552,7 @@ __global__ void __launch_bounds__(256) fdm_big_b(LevelDev<T> L, T* __restrict__ 
     const int o2 = e / N0, o0 = e - o2 * N0;
     const int i = o2 * PT + o0;
     const T den = l0[o0] + l1 + l2[o2];
-    if constexpr (DGMG_FDM_DIV_NR) pl[i] = div_nr(pl[i], den);  // Newton-refined reciprocal
-    else pl[i] = pl[i] / den;
+    pl[i] = div_nr(pl[i], den);  // Newton-refined reciprocal
   }
   __syncthreads();
   mfma_lines_cols<T, N2>(pl, N0, 1, PT, q.ST[2]);

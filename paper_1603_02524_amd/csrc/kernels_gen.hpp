@@ -176,7 +176,7 @@ __global__ void __launch_bounds__(256) gen_fdm_kernel(LevelDev<T> L, int nd, int
 template <class T>
 __global__ void __launch_bounds__(256) gen_combine_kernel(LevelDev<T> L, int nd, int NA, int NL,
                                                           const T* __restrict__ buf, T* __restrict__ u, int npx,
-                                                          int npy, int assign) {
+                                                          int npy, int swp, int assign) {
   if (inactive(L.active)) return;
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= L.n_dof) return;
@@ -186,7 +186,7 @@ __global__ void __launch_bounds__(256) gen_combine_kernel(LevelDev<T> L, int nd,
   for (int d = 0; d < dim; ++d) len[d] = d == nd ? NA : NL;
   const int64_t TS = (int64_t)len[0] * len[1] * len[2];
   const int64_t pst[3] = {1, npx, (int64_t)npx * npy};
-  const int64_t ost[3] = {1, len[0], (int64_t)len[0] * len[1]};
+  const int64_t ost[3] = {1, swp ? (int64_t)len[0] * len[2] : len[0], swp ? len[0] : (int64_t)len[0] * len[1]};
   int cnt[3] = {1, 1, 1};
   int64_t adr[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
   for (int d = 0; d < dim; ++d) {
@@ -299,9 +299,9 @@ int gen_fdm_launch(const LevelDev<T>& L, int nd, int NA, int NL, const T* r, T* 
 
 template <class T>
 int gen_combine_launch(const LevelDev<T>& L, int nd, int NA, int NL, const T* buf, T* u, int npx, int npy,
-                       bool assign, hipStream_t s) {
+                       int swp, bool assign, hipStream_t s) {
   hipLaunchKernelGGL((gen_combine_kernel<T>), dim3(gen_node_blocks(L.n_dof)), dim3(256), 0, s, L, nd, NA, NL, buf, u,
-                     npx, npy, assign ? 1 : 0);
+                     npx, npy, swp, assign ? 1 : 0);
   return 0;
 }
 

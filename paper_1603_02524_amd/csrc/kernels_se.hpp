@@ -485,8 +485,8 @@ __global__ void __launch_bounds__(256) se_dss_kernel(LevelDev<T> L, const T* __r
 // once (empty ones masked off); sum order direction 3, 2, 1 candidates, each
 // in increasing patch index.
 template <class T, int DIM, int MAXC>
-__global__ void __launch_bounds__(256) se_combine_kernel(LevelDev<T> L, int NA, const T* __restrict__ buf,
-                                                         T* __restrict__ u, int assign) {
+__global__ void __launch_bounds__(256) se_combine_kernel(LevelDev<T> L, int NA, PatchBuf pb,
+                                                         const T* __restrict__ buf, T* __restrict__ u, int assign) {
   if (inactive(L.active)) return;
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= L.n_dof) return;
@@ -522,8 +522,21 @@ __global__ void __launch_bounds__(256) se_combine_kernel(LevelDev<T> L, int NA, 
       }
     }
   }
-  const int N1 = L.dir[0].N, N2 = L.dir[1].N;
-  const int64_t TS = DIM == 3 ? (int64_t)NA * NA * NA : (int64_t)NA * NA;
+  const int N1 = L.dir[0].N, N2 = (L.dir[1].N + pb.K - 1) / pb.K;  // strips along direction 1
+  const int ny = (pb.K - 1) * pb.step + NA;                        // planes of a strip
+  const int64_t TS = DIM == 3 ? (int64_t)NA * NA * ny : (int64_t)NA * ny;
+  if constexpr (MAXC == 2 && DIM == 3) {
+    if (pb.K > 1) {  // strips (only where at most two patches overlap): two patches of one strip share a plane
+      const int sh = __builtin_ctz(pb.K);
+#pragma unroll
+      for (int k = 0; k < MAXC; ++k) {
+        const int m = pm[1][k];
+        pm[1][k] = m >> sh;
+        tp[1][k] += (m & (pb.K - 1)) * pb.step;
+      }
+      if (cnt[1] == 2 && pm[1][0] == pm[1][1] && tp[1][0] == tp[1][1]) cnt[1] = 1;
+    }
+  }
   T v[CZ][MAXC][MAXC];
 #pragma unroll
   for (int c = 0; c < CZ; ++c)
@@ -534,7 +547,9 @@ __global__ void __launch_bounds__(256) se_combine_kernel(LevelDev<T> L, int NA, 
         const bool ok = a < cnt[0] && b < cnt[1] && c < cnt[2];
         const int64_t pid = pm[0][a] + (int64_t)N1 * (pm[1][b] + (int64_t)N2 * pm[2][c]);
         T t = T(0);
-        if (ok) t = buf[pid * TS + ((int64_t)tp[2][c] * NA + tp[1][b]) * NA + tp[0][a]];
+        if (ok)
+          t = buf[pid * TS + (pb.swp ? ((int64_t)tp[1][b] * NA + tp[2][c]) * NA : ((int64_t)tp[2][c] * NA + tp[1][b]) * NA) +
+                  tp[0][a]];
         v[c][b][a] = t;
       }
   T s = T(0);
@@ -698,13 +713,14 @@ int se_apply_launch(const LevelDev<T>& L, int mode, const T* x, const T* f, T* y
 }
 
 template <class T, int DIM>
-int se_combine_launch(const LevelDev<T>& L, int NA, const T* buf, T* u, bool assign, hipStream_t s) {
+int se_combine_launch(const LevelDev<T>& L, int NA, const T* buf, T* u, const PatchBuf& pb, bool assign,
+                      hipStream_t s) {
   if (2 * L.NO < L.P)
-    hipLaunchKernelGGL((se_combine_kernel<T, DIM, 2>), dim3(se_node_blocks(L.n_dof)), dim3(256), 0, s, L, NA, buf, u,
-                       assign ? 1 : 0);
+    hipLaunchKernelGGL((se_combine_kernel<T, DIM, 2>), dim3(se_node_blocks(L.n_dof)), dim3(256), 0, s, L, NA, pb, buf,
+                       u, assign ? 1 : 0);
   else
-    hipLaunchKernelGGL((se_combine_kernel<T, DIM, 3>), dim3(se_node_blocks(L.n_dof)), dim3(256), 0, s, L, NA, buf, u,
-                       assign ? 1 : 0);
+    hipLaunchKernelGGL((se_combine_kernel<T, DIM, 3>), dim3(se_node_blocks(L.n_dof)), dim3(256), 0, s, L, NA, pb, buf,
+                       u, assign ? 1 : 0);
   return 0;
 }
 

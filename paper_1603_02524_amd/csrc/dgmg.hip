@@ -15,6 +15,7 @@
 #include "../../include/dgmg.h"
 #include "kernels.hpp"
 #include "kernels_big.hpp"
+#include "kernels_coarse.hpp"
 #include "kernels_fdm3.hpp"
 #include "setup.hpp"
 
@@ -241,15 +242,6 @@ __global__ void __launch_bounds__(VEC_THREADS) k_mass(LevelDev<double> L, const 
 // ---------------------------------------------------------------- coarse solve (global FDM, P = 1)
 // One pass of the global fast-diagonalisation along direction d on the
 // element-major P = 1 vector: out = (S_d^T or S_d) applied along d.
-struct CoarseDev {
-  int dim;
-  int se;     // 1: continuous lattice vector (nl[d] nodes per direction)
-  int nl[3];
-  int N[3];
-  const double* S[3];    // G_d x G_d row-major
-  const double* lam[3];  // G_d
-};
-
 template <bool FWD, bool SCALE>
 __global__ void __launch_bounds__(VEC_THREADS) k_coarse_pass(CoarseDev C, int d, const double* __restrict__ in,
                                                              double* __restrict__ out, int64_t n,
@@ -450,7 +442,8 @@ struct dgmg_batch {
   struct Launch {
     int kind = 0, dim = 3, f32 = 0, t[4] = {0, 0, 0, 0};
     int ng = 0, ntot = 0;
-    PatchBuf pb;  // patch solves: the layout with the longest strips of the launch
+    PatchBuf pb;       // patch solves: the layout with the longest strips of the launch
+    size_t shmem = 0;  // coarse solves: the largest LDS of the launch's grids
     size_t desc_off = 0, starts_off = 0;
     std::vector<std::function<int()>> fns;
     std::vector<int> fn_grid;  // the grid of each of fns
@@ -1060,9 +1053,9 @@ int coarse_fdm(dgmg_handle* h, const double* f0, double* u0) {
   const unsigned nb = (unsigned)((n + VEC_THREADS - 1) / VEC_THREADS);
   const int dim = l0.dim;
   const double* src = f0;
-  bool periodic_all = true;
-  for (int d = 0; d < dim; ++d) periodic_all = periodic_all && l0.dir[d].periodic;
-  if (periodic_all) {  // make f0 orthogonal to the constants (Euclidean mean)
+  bool per_all = true;
+  for (int d = 0; d < dim; ++d) per_all = per_all && l0.dir[d].periodic;
+  if (per_all) {  // make f0 orthogonal to the constants (Euclidean mean)
     hipLaunchKernelGGL(k_copy, dim3(vec_blocks(n)), dim3(VEC_THREADS), 0, h->stream, f0, h->c_f, n, h->active);
     k_mean_sub(h, h->c_f, n);
     src = h->c_f;
@@ -1093,26 +1086,80 @@ int coarse_fdm(dgmg_handle* h, const double* f0, double* u0) {
     in = out;
     k ^= 1;
   }
-  if (periodic_all) k_mean_sub(h, u0, n);  // mean-free (minimum-norm) representative
+  if (per_all) k_mean_sub(h, u0, n);  // mean-free (minimum-norm) representative
   return check_hip(h, "coarse solve");
 }
 
+bool periodic_all(const dgmg_handle* h) {
+  const LevelHost& l0 = h->lv[0];
+  bool all = true;
+  for (int d = 0; d < l0.dim; ++d) all = all && l0.dir[d].periodic;
+  return all;
+}
+// The one-block form of the coarse solve applies.
+bool coarse_in_block(const dgmg_handle* h) { return coarse_block_shmem(h->cdev) <= COARSE_LDS; }
+
 template <class T>
-int k_coarse(dgmg_handle* h, const T* f0, T* u0);
-template <>
-int k_coarse<double>(dgmg_handle* h, const double* f0, double* u0) { return coarse_fdm(h, f0, u0); }
-template <>
-int k_coarse<float>(dgmg_handle* h, const float* f0, float* u0) {
-  const int64_t n = h->lv[0].n_dof;
-  // FP64 copies: input in the level-0 residual buffer (sized for doubles), result
-  // in the patch buffer (c_a, c_b and c_f are used by coarse_fdm)
-  double* tmp_in = (double*)h->buf[0].r;
-  double* res = (double*)h->patch;
-  hipLaunchKernelGGL((k_convert<float, double>), dim3(vec_blocks(n)), dim3(VEC_THREADS), 0, h->stream, f0, tmp_in, n, h->active);
-  int rc = coarse_fdm(h, tmp_in, res);
-  if (rc) return rc;
-  hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_blocks(n)), dim3(VEC_THREADS), 0, h->stream, res, u0, n, h->active);
-  return check_hip(h, "coarse convert");
+CoarseArgs<T> coarse_args(const dgmg_handle* h, const T* f0, T* u0) {
+  CoarseArgs<T> a;
+  a.C = h->cdev;
+  a.f = f0;
+  a.u = u0;
+  a.active = h->active;
+  a.mean = periodic_all(h) ? 1 : 0;
+  return a;
+}
+
+// Dynamic LDS above the default limit.
+template <class K>
+void allow_shmem(K kernel, size_t bytes) {
+  if (bytes > 65536) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+// u_0 = A_0^+ f_0, computed in FP64 whatever T.
+template <class T>
+int k_coarse(dgmg_handle* h, const T* f0, T* u0) {
+  const CoarseDev& C = h->cdev;
+  // the same bits either way; the three launches take over where the rate of one unit
+  // costs more than two launches (one block / planes: 1680 unknowns 15.5 us / three
+  // launches of 4.5 us, 3375 unknowns 26.4 / 15.5 us)
+  const bool planes = C.dim == 3 && !periodic_all(h) && coarse_planes_shmem(C) <= COARSE_LDS &&
+                      coarse_columns_shmem(C) <= COARSE_LDS;
+  if (coarse_in_block(h) && !(planes && h->lv[0].n_dof > 2048)) {
+    const size_t shm = coarse_block_shmem(C);
+    allow_shmem(coarse_block_kernel<T, false>, shm);
+    hipLaunchKernelGGL((coarse_block_kernel<T, false>), dim3(1), dim3(COARSE_THREADS), shm, h->stream,
+                       coarse_args<T>(h, f0, u0), BatchList<CoarseArgs<T>>{});
+    return check_hip(h, "coarse solve");
+  }
+  if (planes) {
+    const int G2 = coarse_nodes(C, 2), cols = coarse_nodes(C, 0) * coarse_nodes(C, 1);
+    const size_t sp = coarse_planes_shmem(C), sc = coarse_columns_shmem(C);
+    allow_shmem(coarse_planes_kernel<T, true>, sp);
+    allow_shmem(coarse_planes_kernel<T, false>, sp);
+    allow_shmem(coarse_columns_kernel, sc);
+    hipLaunchKernelGGL((coarse_planes_kernel<T, true>), dim3(G2), dim3(256), sp, h->stream, C, f0, h->c_a, (T*)nullptr,
+                       h->active);
+    hipLaunchKernelGGL(coarse_columns_kernel, dim3((cols + COARSE_COLS - 1) / COARSE_COLS), dim3(256), sc, h->stream, C,
+                       h->c_a, h->active);
+    hipLaunchKernelGGL((coarse_planes_kernel<T, false>), dim3(G2), dim3(256), sp, h->stream, C, (const T*)nullptr,
+                       h->c_a, u0, h->active);
+    return check_hip(h, "coarse solve");
+  }
+  if constexpr (std::is_same<T, double>::value) {
+    return coarse_fdm(h, f0, u0);
+  } else {
+    const int64_t n = h->lv[0].n_dof;
+    // FP64 copies: input in the level-0 residual buffer (sized for doubles), result
+    // in the patch buffer (c_a, c_b and c_f are used by coarse_fdm)
+    double* tmp_in = (double*)h->buf[0].r;
+    double* res = (double*)h->patch;
+    hipLaunchKernelGGL((k_convert<float, double>), dim3(vec_blocks(n)), dim3(VEC_THREADS), 0, h->stream, f0, tmp_in, n, h->active);
+    int rc = coarse_fdm(h, tmp_in, res);
+    if (rc) return rc;
+    hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_blocks(n)), dim3(VEC_THREADS), 0, h->stream, res, u0, n, h->active);
+    return check_hip(h, "coarse convert");
+  }
 }
 
 // z = MultigridCycle(0, r) on multigrid-precision vectors (Alg. 1).
@@ -2074,13 +2121,14 @@ namespace {
 // one argument descriptor per grid.  Each grid sees the same kernels on the
 // same data in the same order as in its own solve (bitwise the same results).
 // The PCG vector operations, fills and coarse solves stay per grid.
-enum { BK_APPLY = 0, BK_FDM = 1, BK_COMB = 2, BK_XFER = 3, BK_FN = 4 };
+enum { BK_APPLY = 0, BK_FDM = 1, BK_COMB = 2, BK_XFER = 3, BK_FN = 4, BK_COARSE = 5 };
 
 struct BStep {
   std::vector<int> key;
   int kind = BK_FN, dim = 3, f32 = 0, t[4] = {0, 0, 0, 0};
   int grid = 0, nblk = 0;
   PatchBuf pb;
+  size_t shmem = 0;
   std::vector<char> args;
   std::function<int()> fn;
 };
@@ -2277,7 +2325,12 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
   {
     T* f0 = f[0];
     T* u0 = u[0];
-    fnstep({2}, [h, f0, u0]() { return k_coarse<T>(h, f0, u0); });
+    if (coarse_in_block(h)) {
+      step({2}, BK_COARSE, 3, {}, 1, arg_bytes(coarse_args<T>(h, f0, u0)));
+      out.back().shmem = coarse_block_shmem(h->cdev);
+    } else {
+      fnstep({2}, [h, f0, u0]() { return k_coarse<T>(h, f0, u0); });
+    }
   }
   for (int l = 1; l <= L; ++l) {
     const int k = L - l;
@@ -2395,6 +2448,7 @@ int batch_plan(dgmg_batch* b, bool fill) {
         st[0] = 0;
         for (size_t k = i; k < j; ++k) st[k - i + 1] = st[k - i] + v[k].nblk;
         ln.ntot = st[ln.ng];
+        for (size_t k = i; k < j; ++k) ln.shmem = std::max(ln.shmem, v[k].shmem);
         for (size_t k = i; k < j; ++k)
           if (k == i || (v[k].pb.K - 1) * v[k].pb.step > (ln.pb.K - 1) * ln.pb.step) ln.pb = v[k].pb;
       }
@@ -2430,6 +2484,11 @@ int run_launch_t(dgmg_batch* b, const dgmg_batch::Launch& ln, hipStream_t s) {
     case BK_COMB: return Kern<T, DIM>::combine_batch(ln.t[0], ln.t[1], blist<CombArgs<T>>(b, ln), ln.ntot, s);
     case BK_XFER:
       return Kern<T, DIM>::transfer_batch(ln.t[0], ln.t[1], ln.t[2] != 0, blist<XferArgs<T>>(b, ln), ln.ntot, s);
+    case BK_COARSE:
+      allow_shmem(coarse_block_kernel<T, true>, ln.shmem);
+      hipLaunchKernelGGL((coarse_block_kernel<T, true>), dim3(ln.ng), dim3(COARSE_THREADS), ln.shmem, s, CoarseArgs<T>{},
+                         blist<CoarseArgs<T>>(b, ln));
+      return 0;
     default: return -4;
   }
 }

@@ -67,33 +67,6 @@ __global__ void __launch_bounds__(VEC_THREADS) k_finalize(const double* __restri
   if (threadIdx.x == 0) out[0] = s;
 }
 
-// Phase-b scalars in one block: n = z.(r - r_old) and z.r from their partials
-// (each in a fixed order), then beta = n / delta with the previous delta, and
-// delta <- z.r; from now on r_old enters n with weight 1 (slot 6, 0 before the
-// first direction update: r_old = 0 initially).  scal slots: 0 delta, 1 beta,
-// 4 n, 5 z.r, 6 r_old weight.
-__global__ void __launch_bounds__(VEC_THREADS) k_finalize_beta(const double* __restrict__ part1,
-                                                               const double* __restrict__ part2, int np,
-                                                               double* __restrict__ scal, const int* act) {
-  if (inactive(act)) return;
-  __shared__ double red[16];
-  double s1 = 0.0, s2 = 0.0;
-  for (int i = threadIdx.x; i < np; i += blockDim.x) {
-    s1 += part1[i];
-    s2 += part2[i];
-  }
-  s1 = block_sum(s1, red);
-  __syncthreads();
-  s2 = block_sum(s2, red);
-  if (threadIdx.x == 0) {
-    scal[4] = s1;
-    scal[5] = s2;
-    scal[1] = s1 / scal[0];
-    scal[0] = s2;
-    scal[6] = 1.0;
-  }
-}
-
 // sum a_i and sum |a_i| partials.
 __global__ void __launch_bounds__(VEC_THREADS) k_sum_abs(const double* __restrict__ a, int64_t n,
                                                          double* __restrict__ part1,
@@ -114,48 +87,113 @@ __global__ void __launch_bounds__(VEC_THREADS) k_sum_abs(const double* __restric
   }
 }
 
-// z.(r - r_old) and z.r partials.  TZ = float: z is the FP32 V-cycle output,
-// widened to FP64 as it is read (here and in k_update_p).
-template <class TZ>
-__global__ void __launch_bounds__(VEC_THREADS) k_dot_zr(const TZ* __restrict__ z,
-                                                        const double* __restrict__ r,
-                                                        const double* __restrict__ ro,
-                                                        const double* __restrict__ ro_weight, int64_t n,
-                                                        double* __restrict__ part1,
-                                                        double* __restrict__ part2, const int* act) {
-  if (inactive(act)) return;
-  __shared__ double red[16];
-  const double wo = ro_weight[0];  // 0 before the first direction update (r - 0 r_old = r exactly)
-  double s1 = 0.0, s2 = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const double zi = (double)z[i], ri = r[i];
-    s1 += zi * (ri - wo * ro[i]);
-    s2 += zi * ri;
-  }
-  s1 = block_sum(s1, red);
+// ---- PCG vector updates (Alg. 2), one grid or many (work lists) per launch.
+// Scalars: delta = z.r and n = z.(r - r_old) stay partial sums (zr2, zr1) until the
+// kernels that use them add them up, every block for itself and in the same order, so
+// that no one-block launch stands between two vector kernels.  On small grids the time is
+// launches and the wait for the norm: 10 us less an iteration with two launches fewer and
+// the norm written to host memory (2D 4x4 P = 4 FP64, solve 736 -> 650 us), and one launch
+// for all grids of a batch (32 small grids, mixed: 16.5 -> 7.0 ms with the first V-cycle in
+// work lists too).  On large grids they stream their vectors.  scal: S_DELTA the
+// previous delta (written by the x, r update, read by the next direction update),
+// S_ROW the weight of r_old (0 until the first direction update).
+// Device scalar slots.
+enum { S_DELTA = 0, S_PQ = 2, S_ROW = 6 };
+struct PcgArgs {
+  double *r = nullptr, *ro = nullptr, *p = nullptr;
+  const double* q = nullptr;
+  const void* z = nullptr;  // V-cycle output (FP64, or FP32 in mixed precision)
+  float* rf = nullptr;      // mixed precision: r rounded, the V-cycle's input
+  const double* pq = nullptr;  // npq partial sums of p.q
+  double *rr = nullptr, *zr1 = nullptr, *zr2 = nullptr;  // partial sums, one per block
+  double* scal = nullptr;
+  double* norm = nullptr;  // r.r (host memory)
+  const int* active = nullptr;
+  int64_t n = 0, off = 0;  // unknowns; offset into the x of a batch
+  int npq = 0, nblk = 0;
+};
+// Blocks of a grid's vector kernels.
+inline int pcg_blocks(int64_t n) { return (int)std::min<int64_t>(RED_BLOCKS, (n + VEC_THREADS - 1) / VEC_THREADS); }
+
+// Sum of np partials in a fixed order, for every thread of the block.
+__device__ __forceinline__ double all_sum(const double* __restrict__ part, int np, double* red) {
+  double s = 0.0;
+  for (int i = threadIdx.x; i < np; i += blockDim.x) s += part[i];
+  s = block_sum(s, red);
+  if (threadIdx.x == 0) red[15] = s;
   __syncthreads();
-  s2 = block_sum(s2, red);
+  s = red[15];
+  __syncthreads();
+  return s;
+}
+// Arguments and block index of a vector kernel; false: nothing to do.
+template <bool BATCH>
+__device__ __forceinline__ bool pcg_pick(const PcgArgs& a0, const BatchList<PcgArgs>& bl, int ntot, PcgArgs* slot,
+                                         const PcgArgs*& ap, int& blk) {
+  if constexpr (BATCH) {
+    const int b = xcd_block(ntot);
+    if (b < 0) return false;
+    blk = batch_pick(bl, b, slot);
+    ap = slot;
+  } else {
+    blk = blockIdx.x;
+    ap = &a0;
+  }
+  return !inactive(ap->active);
+}
+#define DGMG_PCG_PROLOGUE                                                             \
+  __shared__ double red[16];                                                          \
+  __shared__ __align__(16) int slot[BATCH ? sizeof(PcgArgs) / sizeof(int) : 1];       \
+  const PcgArgs* ap;                                                                  \
+  int blk;                                                                            \
+  if (!pcg_pick<BATCH>(a0, bl, ntot, reinterpret_cast<PcgArgs*>(slot), ap, blk)) return; \
+  const int64_t n = ap->n, step = (int64_t)ap->nblk * VEC_THREADS;                    \
+  const int64_t i0 = (int64_t)blk * VEC_THREADS + threadIdx.x;
+
+// partial sums of r.r, r rounded to FP32 for the next V-cycle; first: r_old gets weight 0
+template <bool BATCH>
+__global__ void __launch_bounds__(VEC_THREADS) k_pcg_norm(PcgArgs a0, BatchList<PcgArgs> bl, int ntot, int first) {
+  DGMG_PCG_PROLOGUE
+  const double* __restrict__ r = ap->r;
+  float* __restrict__ rf = ap->rf;
+  double s = 0.0;
+  for (int64_t i = i0; i < n; i += step) {
+    const double ri = r[i];
+    if (rf) rf[i] = (float)ri;
+    s += ri * ri;
+  }
+  s = block_sum(s, red);
   if (threadIdx.x == 0) {
-    part1[blockIdx.x] = s1;
-    part2[blockIdx.x] = s2;
+    ap->rr[blk] = s;
+    if (first && blk == 0) ap->scal[S_ROW] = 0.0;
   }
 }
 
-// alpha = delta / (p.q); x += alpha p; r_old = r; r -= alpha q; partial r.r;
-// rf (if not null) = r rounded to FP32, the input of the mixed-precision V-cycle
-__global__ void __launch_bounds__(VEC_THREADS) k_update_xr(double* __restrict__ x, double* __restrict__ r,
-                                                           double* __restrict__ ro,
-                                                           const double* __restrict__ p,
-                                                           const double* __restrict__ q,
-                                                           const double* __restrict__ delta,
-                                                           const double* __restrict__ pq, int64_t n,
-                                                           double* __restrict__ part, float* __restrict__ rf,
-                                                           const int* act) {
-  if (inactive(act)) return;
+// norm = the sum of the partials of r.r (one block per grid)
+template <bool BATCH>
+__global__ void __launch_bounds__(VEC_THREADS) k_pcg_total(PcgArgs a0, BatchList<PcgArgs> bl) {
   __shared__ double red[16];
-  const double alpha = delta[0] / pq[0];
+  const PcgArgs* __restrict__ ap = BATCH ? bl.descs + blockIdx.x : &a0;
+  if (inactive(ap->active)) return;
+  const double s = all_sum(ap->rr, ap->nblk, red);
+  if (threadIdx.x == 0) *ap->norm = s;
+}
+
+// alpha = delta / (p.q); x += alpha p; r_old = r; r -= alpha q; partial sums of r.r
+template <bool BATCH>
+__global__ void __launch_bounds__(VEC_THREADS) k_pcg_update_xr(PcgArgs a0, BatchList<PcgArgs> bl, int ntot,
+                                                               double* __restrict__ xs) {
+  DGMG_PCG_PROLOGUE
+  const double delta = all_sum(ap->zr2, ap->nblk, red), alpha = delta / all_sum(ap->pq, ap->npq, red);
+  if (blk == 0 && threadIdx.x == 0) ap->scal[S_DELTA] = delta;
+  double* __restrict__ x = xs + ap->off;
+  double* __restrict__ r = ap->r;
+  double* __restrict__ ro = ap->ro;
+  const double* __restrict__ p = ap->p;
+  const double* __restrict__ q = ap->q;
+  float* __restrict__ rf = ap->rf;
   double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t i = i0; i < n; i += step) {
     x[i] += alpha * p[i];
     const double r0 = r[i];
     ro[i] = r0;
@@ -165,19 +203,45 @@ __global__ void __launch_bounds__(VEC_THREADS) k_update_xr(double* __restrict__ 
     s += ri * ri;
   }
   s = block_sum(s, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
+  if (threadIdx.x == 0) ap->rr[blk] = s;
 }
 
-// p = z + beta p (z FP64, or the FP32 V-cycle output widened)
-template <class TZ>
-__global__ void __launch_bounds__(VEC_THREADS) k_update_p(double* __restrict__ p, const TZ* __restrict__ z,
-                                                          const double* __restrict__ beta_p,
-                                                          int64_t n, const int* act) {
-  if (inactive(act)) return;
-  const double beta = beta_p[0];
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    p[i] = (double)z[i] + beta * p[i];
+// partial sums of z.(r - r_old) and z.r (r_old not read while its weight is 0)
+template <class TZ, bool BATCH>
+__global__ void __launch_bounds__(VEC_THREADS) k_pcg_dot_zr(PcgArgs a0, BatchList<PcgArgs> bl, int ntot) {
+  DGMG_PCG_PROLOGUE
+  const bool old = ap->scal[S_ROW] != 0.0;
+  const TZ* __restrict__ z = (const TZ*)ap->z;
+  const double* __restrict__ r = ap->r;
+  const double* __restrict__ ro = ap->ro;
+  double s1 = 0.0, s2 = 0.0;
+  for (int64_t i = i0; i < n; i += step) {
+    const double zi = (double)z[i], ri = r[i];
+    s1 += zi * (old ? ri - ro[i] : ri);
+    s2 += zi * ri;
   }
+  s1 = block_sum(s1, red);
+  __syncthreads();
+  s2 = block_sum(s2, red);
+  if (threadIdx.x == 0) {
+    ap->zr1[blk] = s1;
+    ap->zr2[blk] = s2;
+  }
+}
+
+// p = z + beta p with beta = z.(r - r_old) / delta (first: p = z); from now on r_old counts
+template <class TZ, bool BATCH>
+__global__ void __launch_bounds__(VEC_THREADS) k_pcg_update_p(PcgArgs a0, BatchList<PcgArgs> bl, int ntot, int first) {
+  DGMG_PCG_PROLOGUE
+  const TZ* __restrict__ z = (const TZ*)ap->z;
+  double* __restrict__ p = ap->p;
+  if (first) {
+    for (int64_t i = i0; i < n; i += step) p[i] = (double)z[i];
+    return;
+  }
+  const double beta = all_sum(ap->zr1, ap->nblk, red) / ap->scal[S_DELTA];
+  for (int64_t i = i0; i < n; i += step) p[i] = (double)z[i] + beta * p[i];
+  if (blk == 0 && threadIdx.x == 0) ap->scal[S_ROW] = 1.0;
 }
 
 template <class A, class B>
@@ -377,12 +441,12 @@ struct dgmg_handle {
   CoarseDev cdev{};
   // PCG (top level, FP64)
   double *pr = nullptr, *pro = nullptr, *pp = nullptr, *pq = nullptr, *pz = nullptr;
-  double *part = nullptr, *part2 = nullptr;  // reduction partials
-  double* scal = nullptr;                    // slots: 0 delta, 1 beta, 2 p.q, 3 r.r, 4 z.(r-r_old), 5 z.r, 6 r_old weight
+  double *part = nullptr, *part2 = nullptr, *zr1 = nullptr, *zr2 = nullptr;  // reduction partials
+  double* scal = nullptr;                    // device scalars (S_DELTA ...)
   double* host_scal = nullptr;               // pinned
   // batched use: device flag (kernels return when 0) and the slot receiving r.r
   const int* active = nullptr;
-  double* rr_out = nullptr;
+  double* rr_out = nullptr;  // (host memory of the batch)
   // hipGraph replay of the PCG phases
   bool use_graphs = false;
   hipGraphExec_t gexec[2] = {nullptr, nullptr};
@@ -425,7 +489,6 @@ struct dgmg_batch {
   char* ws = nullptr;
   hipStream_t stream = nullptr;
   int* flags_dev = nullptr;
-  double* rr_dev = nullptr;
   int* flags_host = nullptr;
   double* rr_host = nullptr;
   bool bound = false;
@@ -450,7 +513,7 @@ struct dgmg_batch {
     std::vector<int> key;      // plan position (launches of one position touch disjoint grids)
   };
   bool planned = false;
-  std::vector<Launch> plan[2];
+  std::vector<Launch> plan[3];  // phases a and b; norm of the initial residual
   // the per-grid steps of one plan position run on NSIDE side streams at once
   // (forked from and joined back into the phase's stream with events)
   // Used when the batch holds a grid whose top level fills the GPU alone
@@ -792,6 +855,8 @@ void layout(dgmg_handle* h, char* base, Upload* up) {
   const size_t np1 = std::max<size_t>(RED_BLOCKS, top.n_elem * per_elem + 8);
   h->part = (double*)cv.take(np1 * 8);
   h->part2 = (double*)cv.take(RED_BLOCKS * 8);
+  h->zr1 = (double*)cv.take(RED_BLOCKS * 8);
+  h->zr2 = (double*)cv.take(RED_BLOCKS * 8);
   h->scal = (double*)cv.take(64 * 8);
   h->ws_need = cv.off + 256;
   for (int l = 0; l < nl; ++l) {
@@ -1199,112 +1264,98 @@ int k_vcycle(dgmg_handle* h, const T* r, T* z) {
   return DGMG_OK;
 }
 
-// Preconditioner z = MG(r) on FP64 top-level vectors.
-// widen = false (mixed precision only): the FP32 result stays in the top
-// level's u buffer and z is not written (the caller widens it itself).
-// narrow = false: the FP32 copy of r is already in the top level's f buffer.
-int precond(dgmg_handle* h, const double* r, double* z, bool widen = true, bool narrow = true) {
-  const int L = (int)h->lv.size() - 1;
-  const int64_t n = h->lv[L].n_dof;
-  if (!mixed(h)) return k_vcycle<double>(h, r, z);
-  float* rf = (float*)h->buf[L].f;
-  float* zf = (float*)h->buf[L].u;
-  if (narrow)
-    hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_blocks(n)), dim3(VEC_THREADS), 0, h->stream, r, rf, n, h->active);
-  int rc = k_vcycle<float>(h, rf, zf);
-  if (rc) return rc;
-  if (widen)
-    hipLaunchKernelGGL((k_convert<float, double>), dim3(vec_blocks(n)), dim3(VEC_THREADS), 0, h->stream, zf, z, n, h->active);
-  return check_hip(h, "precond convert");
-}
-
 // ---------------------------------------------------------------- MGCG phases (Alg. 2)
-// Fixed device scalar slots so that a phase can be captured once and replayed.
-enum { S_DELTA = 0, S_BETA = 1, S_PQ = 2, S_RR = 3, S_ZDR = 4, S_ZR = 5, S_ROW = 6, S_RTRUE = 7 };
+// Norms are written to pinned host memory by the kernels (no copy before the host
+// waits for the stream).
+enum { H_SCALAR = 0, H_RR = 8 };
+double* rr_slot(dgmg_handle* h) { return h->rr_out ? h->rr_out : h->host_scal + H_RR; }
 
-double* rr_slot(dgmg_handle* h) { return h->rr_out ? h->rr_out : h->scal + S_RR; }
-
-// r = g - A x; r_old = 0; r.r
-int pcg_init_a(dgmg_handle* h, const double* rhs, const double* x) {
+// npq: partial sums of p.q of the FP64 operator on the top level.
+PcgArgs pcg_args(dgmg_handle* h, int npq, int64_t off = 0) {
   const int L = (int)h->lv.size() - 1;
-  const int64_t n = h->lv[L].n_dof;
-  int rc = k_apply<double>(h, L, 1, x, rhs, h->pr, nullptr, nullptr);
-  if (rc) return rc;
-  // r_old enters with weight 0 until the first direction update (r_old = 0
-  // initially); the first phase a writes it before any read
-  k_fill_v<double>(h, h->scal + S_ROW, 1);
-  hipLaunchKernelGGL(k_dot, dim3(RED_BLOCKS), dim3(VEC_THREADS), 0, h->stream, h->pr, h->pr, n, h->part, h->active);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(VEC_THREADS), 0, h->stream, h->part, RED_BLOCKS, rr_slot(h), h->active);
-  return check_hip(h, "pcg init");
+  const bool mx = mixed(h);
+  PcgArgs a;
+  a.r = h->pr;
+  a.ro = h->pro;
+  a.p = h->pp;
+  a.q = h->pq;
+  a.z = mx ? (const void*)h->buf[L].u : (const void*)h->pz;
+  a.rf = mx ? (float*)h->buf[L].f : nullptr;
+  a.pq = h->part;
+  a.npq = npq;
+  a.rr = h->part2;
+  a.zr1 = h->zr1;
+  a.zr2 = h->zr2;
+  a.scal = h->scal;
+  a.norm = rr_slot(h);
+  a.active = h->active;
+  a.n = h->lv[L].n_dof;
+  a.off = off;
+  a.nblk = pcg_blocks(a.n);
+  return a;
+}
+const BatchList<PcgArgs> NO_LIST;
+
+// Every block of the x, r update adds up the partials of p.q itself while they are few
+// (2048: 8 loads of a thread, about 1 us against 4-5 us of a launch in the chain); true:
+// they are more, and one block adds them up first.
+bool pq_reduced(PcgArgs& a, dgmg_handle* h) {
+  if (a.npq <= 2 * RED_BLOCKS) return false;
+  a.pq = h->scal + S_PQ;
+  a.npq = 1;
+  return true;
+}
+int pcg_reduce_pq(dgmg_handle* h, int npq) {
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(VEC_THREADS), 0, h->stream, h->part, npq, h->scal + S_PQ, h->active);
+  return check_hip(h, "p.q");
 }
 
-// p = MG(r); delta = p.r
-int pcg_init_b(dgmg_handle* h) {
-  const int L = (int)h->lv.size() - 1;
-  const int64_t n = h->lv[L].n_dof;
-  int rc = precond(h, h->pr, h->pp);
+// r = g - A x, r.r; first: r_old = 0 (it enters with weight 0 until the first
+// direction update; the first phase a writes it before any read).  In mixed precision
+// r's FP32 copy, the next V-cycle's input, is written too.
+int residual_only(dgmg_handle* h, const double* rhs, const double* x) {
+  return k_apply<double>(h, (int)h->lv.size() - 1, 1, x, rhs, h->pr, nullptr, nullptr);
+}
+int pcg_residual(dgmg_handle* h, const double* rhs, const double* x, bool first) {
+  int rc = residual_only(h, rhs, x);
   if (rc) return rc;
-  hipLaunchKernelGGL(k_dot, dim3(RED_BLOCKS), dim3(VEC_THREADS), 0, h->stream, h->pp, h->pr, n, h->part, h->active);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(VEC_THREADS), 0, h->stream, h->part, RED_BLOCKS, h->scal + S_DELTA, h->active);
-  return check_hip(h, "pcg init");
+  const PcgArgs a = pcg_args(h, 0);
+  hipLaunchKernelGGL((k_pcg_norm<false>), dim3(a.nblk), dim3(VEC_THREADS), 0, h->stream, a, NO_LIST, 0, first ? 1 : 0);
+  hipLaunchKernelGGL((k_pcg_total<false>), dim3(1), dim3(VEC_THREADS), 0, h->stream, a, NO_LIST);
+  return check_hip(h, "pcg residual");
 }
 
 // q = A p; alpha = delta / p.q; x += alpha p; r_old = r; r -= alpha q; r.r
-int pcg_phase_a_tail(dgmg_handle* h, double* x, int nb);
 int pcg_phase_a(dgmg_handle* h, double* x) {
   const int L = (int)h->lv.size() - 1;
   int nb = 0;
   int rc = k_apply<double>(h, L, 2, h->pp, nullptr, h->pq, h->part, &nb);
   if (rc) return rc;
-  return pcg_phase_a_tail(h, x, nb);
-}
-
-// Phase a after q = A p (nb partial sums of p.q in part)
-int pcg_phase_a_tail(dgmg_handle* h, double* x, int nb) {
-  const int L = (int)h->lv.size() - 1;
-  const int64_t n = h->lv[L].n_dof;
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(VEC_THREADS), 0, h->stream, h->part, nb, h->scal + S_PQ, h->active);
-  float* rf = mixed(h) ? (float*)h->buf[L].f : nullptr;  // the next V-cycle's FP32 input
-  hipLaunchKernelGGL(k_update_xr, dim3(RED_BLOCKS), dim3(VEC_THREADS), 0, h->stream, x, h->pr, h->pro, h->pp, h->pq,
-                     h->scal + S_DELTA, h->scal + S_PQ, n, h->part2, rf, h->active);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(VEC_THREADS), 0, h->stream, h->part2, RED_BLOCKS, rr_slot(h), h->active);
+  PcgArgs a = pcg_args(h, nb);
+  if (pq_reduced(a, h) && (rc = pcg_reduce_pq(h, nb))) return rc;
+  hipLaunchKernelGGL((k_pcg_update_xr<false>), dim3(a.nblk), dim3(VEC_THREADS), 0, h->stream, a, NO_LIST, 0, x);
+  hipLaunchKernelGGL((k_pcg_total<false>), dim3(1), dim3(VEC_THREADS), 0, h->stream, a, NO_LIST);
   return check_hip(h, "pcg phase a");
 }
 
-// z = MG(r); beta = z.(r - r_old) / delta; p = z + beta p; delta = z.r
-int pcg_phase_b_tail(dgmg_handle* h);
-int pcg_phase_b(dgmg_handle* h) {
+// z = MG(r); beta = z.(r - r_old) / delta; p = z + beta p; delta = z.r (first: p = z).
+// Mixed precision: the V-cycle runs on r's FP32 copy, and the dot products and the
+// direction update read its FP32 output and widen it.
+int pcg_phase_b(dgmg_handle* h, bool first = false) {
   const int L = (int)h->lv.size() - 1;
-  const int64_t n = h->lv[L].n_dof;
-  // mixed precision: the dot products and the direction update read the FP32
-  // V-cycle output and widen it (no FP64 z); r's FP32 copy was written by
-  // phase a's update
   const bool mx = mixed(h);
-  int rc = precond(h, h->pr, h->pz, !mx, !mx);
+  int rc = mx ? k_vcycle<float>(h, (const float*)h->buf[L].f, (float*)h->buf[L].u) : k_vcycle<double>(h, h->pr, h->pz);
   if (rc) return rc;
-  return pcg_phase_b_tail(h);
-}
-
-// Phase b after the V-cycle
-int pcg_phase_b_tail(dgmg_handle* h) {
-  const int L = (int)h->lv.size() - 1;
-  const int64_t n = h->lv[L].n_dof;
-  const bool mx = mixed(h);
-  const float* zf = (const float*)h->buf[L].u;
-  if (mx)
-    hipLaunchKernelGGL((k_dot_zr<float>), dim3(RED_BLOCKS), dim3(VEC_THREADS), 0, h->stream, zf, h->pr, h->pro,
-                       h->scal + S_ROW, n, h->part, h->part2, h->active);
-  else
-    hipLaunchKernelGGL((k_dot_zr<double>), dim3(RED_BLOCKS), dim3(VEC_THREADS), 0, h->stream, h->pz, h->pr, h->pro,
-                       h->scal + S_ROW, n, h->part, h->part2, h->active);
-  hipLaunchKernelGGL(k_finalize_beta, dim3(1), dim3(VEC_THREADS), 0, h->stream, h->part, h->part2, RED_BLOCKS,
-                     h->scal, h->active);
-  if (mx)
-    hipLaunchKernelGGL((k_update_p<float>), dim3(RED_BLOCKS), dim3(VEC_THREADS), 0, h->stream, h->pp, zf,
-                       h->scal + S_BETA, n, h->active);
-  else
-    hipLaunchKernelGGL((k_update_p<double>), dim3(RED_BLOCKS), dim3(VEC_THREADS), 0, h->stream, h->pp,
-                       (const double*)h->pz, h->scal + S_BETA, n, h->active);
+  const PcgArgs a = pcg_args(h, 0);
+  const dim3 g(a.nblk), t(VEC_THREADS);
+  const int fi = first ? 1 : 0;
+  if (mx) {
+    hipLaunchKernelGGL((k_pcg_dot_zr<float, false>), g, t, 0, h->stream, a, NO_LIST, 0);
+    hipLaunchKernelGGL((k_pcg_update_p<float, false>), g, t, 0, h->stream, a, NO_LIST, 0, fi);
+  } else {
+    hipLaunchKernelGGL((k_pcg_dot_zr<double, false>), g, t, 0, h->stream, a, NO_LIST, 0);
+    hipLaunchKernelGGL((k_pcg_update_p<double, false>), g, t, 0, h->stream, a, NO_LIST, 0, fi);
+  }
   return check_hip(h, "pcg phase b");
 }
 
@@ -1374,6 +1425,14 @@ int run_phase(dgmg_handle* h, int which, double* x) {
   return DGMG_OK;
 }
 
+// r.r of the last residual or phase a (its kernels write it to host memory).
+int wait_norm(dgmg_handle* h, double* out) {
+  hipError_t e = hipStreamSynchronize(h->stream);
+  if (e != hipSuccess) return fail(h, DGMG_EHIP, std::string("norm: ") + hipGetErrorString(e));
+  *out = *(volatile double*)rr_slot(h);
+  return DGMG_OK;
+}
+
 int read_scalar(dgmg_handle* h, const double* dev, double* out) {
   hipError_t e = hipMemcpyAsync(h->host_scal, dev, sizeof(double), hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
@@ -1389,19 +1448,9 @@ int read_scalar(dgmg_handle* h, const double* dev, double* out) {
 // the true residual (residual replacement); in mixed precision its FP32 copy,
 // the next V-cycle's input, is refreshed as well.
 int true_residual(dgmg_handle* h, const double* rhs, const double* x, double* norm) {
-  const int L = (int)h->lv.size() - 1;
-  const int64_t n = h->lv[L].n_dof;
-  int rc = k_apply<double>(h, L, 1, x, rhs, h->pr, nullptr, nullptr);
-  if (rc) return rc;
-  hipLaunchKernelGGL(k_dot, dim3(RED_BLOCKS), dim3(VEC_THREADS), 0, h->stream, h->pr, h->pr, n, h->part, h->active);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(VEC_THREADS), 0, h->stream, h->part, RED_BLOCKS, h->scal + S_RTRUE,
-                     h->active);
-  if (mixed(h))
-    hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_blocks(n)), dim3(VEC_THREADS), 0, h->stream, h->pr,
-                       (float*)h->buf[L].f, n, h->active);
-  if ((rc = check_hip(h, "true residual"))) return rc;
+  int rc = pcg_residual(h, rhs, x, false);
   double rr;
-  if ((rc = read_scalar(h, h->scal + S_RTRUE, &rr))) return rc;
+  if (rc || (rc = wait_norm(h, &rr))) return rc;
   *norm = std::sqrt(rr);
   return DGMG_OK;
 }
@@ -1791,9 +1840,9 @@ int dgmg_solve(dgmg_handle* h, const double* rhs, double* x, double tol, dgmg_st
   if (h->active) return fail(h, DGMG_EINVAL, "handle belongs to a batch");
   if (st) std::memset(st, 0, sizeof(*st));
   if ((rc = check_rhs_consistent(h, rhs))) return rc;
-  if ((rc = pcg_init_a(h, rhs, x))) return rc;
+  if ((rc = pcg_residual(h, rhs, x, true))) return rc;
   double rr;
-  if ((rc = read_scalar(h, rr_slot(h), &rr))) return rc;
+  if ((rc = wait_norm(h, &rr))) return rc;
   const double r0 = std::sqrt(rr);
   if (!std::isfinite(r0)) return fail(h, DGMG_ENONFINITE, "initial residual is not finite");
   if (st) {
@@ -1804,12 +1853,12 @@ int dgmg_solve(dgmg_handle* h, const double* rhs, double* x, double tol, dgmg_st
   }
   if (r0 == 0.0) return DGMG_OK;
   const double rmax = tol * r0;
-  if ((rc = pcg_init_b(h))) return rc;
+  if ((rc = pcg_phase_b(h, true))) return rc;
   double rn = r0;
   bool conv = false;
   for (int it = 1; it <= h->opts.max_iter; ++it) {
     if ((rc = run_phase(h, 0, x))) return rc;
-    if ((rc = read_scalar(h, rr_slot(h), &rr))) return rc;
+    if ((rc = wait_norm(h, &rr))) return rc;
     rn = std::sqrt(rr);
     if (st) {
       st->iterations = it;
@@ -2121,7 +2170,8 @@ namespace {
 // one argument descriptor per grid.  Each grid sees the same kernels on the
 // same data in the same order as in its own solve (bitwise the same results).
 // The PCG vector operations, fills and coarse solves stay per grid.
-enum { BK_APPLY = 0, BK_FDM = 1, BK_COMB = 2, BK_XFER = 3, BK_FN = 4, BK_COARSE = 5 };
+enum { BK_APPLY = 0, BK_FDM = 1, BK_COMB = 2, BK_XFER = 3, BK_FN = 4, BK_COARSE = 5, BK_PCG = 6 };
+enum { PCG_UPDATE_XR = 0, PCG_TOTAL = 1, PCG_DOT_ZR = 2, PCG_UPDATE_P = 3, PCG_NORM = 4 };
 
 struct BStep {
   std::vector<int> key;
@@ -2353,6 +2403,7 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
 int batch_plan(dgmg_batch* b, bool fill) {
   b->plan[0].clear();
   b->plan[1].clear();
+  b->plan[2].clear();
   b->planned = batch_plannable(b);
   b->concurrent = false;
   for (const dgmg_handle* h : b->h) b->concurrent = b->concurrent || h->lv.back().n_dof >= SOLO_DOF;
@@ -2360,12 +2411,23 @@ int batch_plan(dgmg_batch* b, bool fill) {
     b->plan_bytes = 0;
     return DGMG_OK;
   }
-  std::vector<BStep> steps[2];
+  std::vector<BStep> steps[3];
   const int n = (int)b->h.size();
   for (int gi = 0; gi < n; ++gi) {
     dgmg_handle* h = b->h[gi];
     const int L = (int)h->lv.size() - 1;
-    // phase a: q = A p (top level, FP64), then the grid's own updates
+    auto pcg = [&](int ph, int key, int which, const PcgArgs& a) {
+      BStep st;
+      st.key = {key};
+      st.kind = BK_PCG;
+      st.f32 = mixed(h) ? 1 : 0;
+      st.t[0] = which;
+      st.grid = gi;
+      st.nblk = which == PCG_TOTAL ? 1 : a.nblk;
+      st.args = arg_bytes(a);
+      steps[ph].push_back(std::move(st));
+    };
+    // phase a: q = A p (top level, FP64), then the updates
     const LevelDev<double>& Lt = h->Ld[L];
     if (h->lv[L].n_dof >= SOLO_DOF) {
       BStep st;
@@ -2393,22 +2455,26 @@ int batch_plan(dgmg_batch* b, bool fill) {
     st.nblk = a.nblk;
     st.args = arg_bytes(a);
     steps[0].push_back(std::move(st));
-    BStep tail;
-    tail.key = {1};
-    tail.grid = gi;
-    const int nb = a.nblk;
-    const int64_t off = b->dof_off[gi];
-    tail.fn = [b, h, nb, off]() { return pcg_phase_a_tail(h, b->x_cur + off, nb); };
-    steps[0].push_back(std::move(tail));
+    PcgArgs pa = pcg_args(h, a.nblk, b->dof_off[gi]);
+    if (pq_reduced(pa, h)) {
+      BStep tail;
+      tail.key = {1};
+      tail.grid = gi;
+      const int nb = a.nblk;
+      tail.fn = [h, nb]() { return pcg_reduce_pq(h, nb); };
+      steps[0].push_back(std::move(tail));
     }
+    pcg(0, 2, PCG_UPDATE_XR, pa);
+    pcg(0, 3, PCG_TOTAL, pa);
+    }
+    const PcgArgs pv = pcg_args(h, 0);
+    pcg(2, 0, PCG_NORM, pv);
+    pcg(2, 1, PCG_TOTAL, pv);
     // phase b: the V-cycle (mixed: on the FP32 copies of r and z), then the direction update
     if (mixed(h)) vcycle_steps<float>(h, gi, (const float*)h->buf[L].f, (float*)h->buf[L].u, steps[1]);
     else vcycle_steps<double>(h, gi, h->pr, h->pz, steps[1]);
-    BStep tb;
-    tb.key = {9};
-    tb.grid = gi;
-    tb.fn = [h]() { return pcg_phase_b_tail(h); };
-    steps[1].push_back(std::move(tb));
+    pcg(1, 9, PCG_DOT_ZR, pv);
+    pcg(1, 10, PCG_UPDATE_P, pv);
   }
   std::vector<char> host;
   auto alloc = [&](size_t bytes) {
@@ -2416,7 +2482,7 @@ int batch_plan(dgmg_batch* b, bool fill) {
     host.resize(o + bytes);
     return o;
   };
-  for (int ph = 0; ph < 2; ++ph) {
+  for (int ph = 0; ph < 3; ++ph) {
     auto& v = steps[ph];
     auto sig = [](const BStep& s) { return std::make_tuple(s.kind, s.dim, s.f32, s.t[0], s.t[1], s.t[2], s.t[3]); };
     std::stable_sort(v.begin(), v.end(), [&](const BStep& x, const BStep& y) {
@@ -2475,6 +2541,28 @@ BatchList<A> blist(dgmg_batch* b, const dgmg_batch::Launch& ln) {
   return bl;
 }
 
+int run_pcg(dgmg_batch* b, const dgmg_batch::Launch& ln, hipStream_t s, bool first) {
+  const BatchList<PcgArgs> bl = blist<PcgArgs>(b, ln);
+  const PcgArgs none;
+  const dim3 g(xcd_grid(ln.ntot)), t(VEC_THREADS);
+  const int nt = ln.ntot, fi = first ? 1 : 0;
+  switch (ln.t[0]) {
+    case PCG_NORM: hipLaunchKernelGGL((k_pcg_norm<true>), g, t, 0, s, none, bl, nt, fi); break;
+    case PCG_TOTAL: hipLaunchKernelGGL((k_pcg_total<true>), dim3(ln.ng), t, 0, s, none, bl); break;
+    case PCG_UPDATE_XR: hipLaunchKernelGGL((k_pcg_update_xr<true>), g, t, 0, s, none, bl, nt, b->x_cur); break;
+    case PCG_DOT_ZR:
+      if (ln.f32) hipLaunchKernelGGL((k_pcg_dot_zr<float, true>), g, t, 0, s, none, bl, nt);
+      else hipLaunchKernelGGL((k_pcg_dot_zr<double, true>), g, t, 0, s, none, bl, nt);
+      break;
+    case PCG_UPDATE_P:
+      if (ln.f32) hipLaunchKernelGGL((k_pcg_update_p<float, true>), g, t, 0, s, none, bl, nt, fi);
+      else hipLaunchKernelGGL((k_pcg_update_p<double, true>), g, t, 0, s, none, bl, nt, fi);
+      break;
+    default: return -4;
+  }
+  return 0;
+}
+
 template <class T, int DIM>
 int run_launch_t(dgmg_batch* b, const dgmg_batch::Launch& ln, hipStream_t s) {
   switch (ln.kind) {
@@ -2495,7 +2583,8 @@ int run_launch_t(dgmg_batch* b, const dgmg_batch::Launch& ln, hipStream_t s) {
 
 // skip_done: leave out the per-grid operations of grids that have converged
 // (eager runs; a recorded graph keeps them, and their kernels return at once)
-int run_plan(dgmg_batch* b, int which, hipStream_t s, bool skip_done) {
+// first: the first direction of a solve (p = z)
+int run_plan(dgmg_batch* b, int which, hipStream_t s, bool skip_done, bool first = false) {
   const auto& plan = b->plan[which];
   std::vector<int> act;
   for (size_t i0 = 0; i0 < plan.size();) {
@@ -2538,7 +2627,8 @@ int run_plan(dgmg_batch* b, int which, hipStream_t s, bool skip_done) {
       const auto& ln = plan[li];
       if (ln.kind == BK_FN) continue;
       int rc;
-      if (ln.f32) rc = ln.dim == 3 ? run_launch_t<float, 3>(b, ln, s) : run_launch_t<float, 2>(b, ln, s);
+      if (ln.kind == BK_PCG) rc = run_pcg(b, ln, s, first);
+      else if (ln.f32) rc = ln.dim == 3 ? run_launch_t<float, 3>(b, ln, s) : run_launch_t<float, 2>(b, ln, s);
       else rc = ln.dim == 3 ? run_launch_t<double, 3>(b, ln, s) : run_launch_t<double, 2>(b, ln, s);
       if (rc) return DGMG_EUNSUPPORTED;
       hipError_t e = hipGetLastError();
@@ -2564,7 +2654,6 @@ int dgmg_batch_setup(int count, const dgmg_grid* grids, const dgmg_opts* opts, d
   dgmg_batch* b = new dgmg_batch();
   Carver cv{nullptr};
   cv.take(count * sizeof(int));
-  cv.take(count * sizeof(double));
   b->dof_off.push_back(0);
   for (int i = 0; i < count; ++i) {
     dgmg_handle* h = nullptr;
@@ -2650,7 +2739,6 @@ int dgmg_batch_bind_workspace(dgmg_batch* b, void* dev, size_t bytes, void* stre
   const int n = (int)b->h.size();
   Carver cv{b->ws};
   b->flags_dev = (int*)cv.take(n * sizeof(int));
-  b->rr_dev = (double*)cv.take(n * sizeof(double));
   if (!b->flags_host) {
     if (hipHostMalloc((void**)&b->flags_host, n * sizeof(int), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void**)&b->rr_host, n * sizeof(double), hipHostMallocDefault) != hipSuccess) {
@@ -2669,7 +2757,7 @@ int dgmg_batch_bind_workspace(dgmg_batch* b, void* dev, size_t bytes, void* stre
     prev_end = hi;
   }
   for (int i = 0; i < n; ++i) {
-    int rc = bind_batch_member(b->h[i], b->ws + b->sub_off[i], b->stream, b->flags_dev + i, b->rr_dev + i);
+    int rc = bind_batch_member(b->h[i], b->ws + b->sub_off[i], b->stream, b->flags_dev + i, b->rr_host + i);
     if (rc) {
       b->err = "grid " + std::to_string(i) + ": " + b->h[i]->err;
       return rc;
@@ -2712,11 +2800,10 @@ static int batch_flags_upload(dgmg_batch* b) {
   return e == hipSuccess ? DGMG_OK : batch_fail(b, DGMG_EHIP, std::string("flag upload: ") + hipGetErrorString(e));
 }
 
-static int batch_rr_download(dgmg_batch* b) {
-  hipError_t e = hipMemcpyAsync(b->rr_host, b->rr_dev, b->h.size() * sizeof(double), hipMemcpyDeviceToHost,
-                                b->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-  return e == hipSuccess ? DGMG_OK : batch_fail(b, DGMG_EHIP, std::string("norm readback: ") + hipGetErrorString(e));
+// The norms of every grid (the kernels write them to host memory).
+static int batch_wait_norms(dgmg_batch* b) {
+  hipError_t e = hipStreamSynchronize(b->stream);
+  return e == hipSuccess ? DGMG_OK : batch_fail(b, DGMG_EHIP, std::string("norms: ") + hipGetErrorString(e));
 }
 
 int dgmg_batch_autotune(dgmg_batch* b) {
@@ -2900,10 +2987,13 @@ int dgmg_batch_solve(dgmg_batch* b, const double* rhs, double* x, double tol, dg
   for (int i = 0; i < n; ++i)
     if ((rc = check_rhs_consistent(b->h[i], rhs + b->dof_off[i])))
       return batch_fail(b, rc, "grid " + std::to_string(i) + ": " + b->h[i]->err);
-  for (int i = 0; i < n; ++i)
-    if ((rc = pcg_init_a(b->h[i], rhs + b->dof_off[i], x + b->dof_off[i])))
+  for (int i = 0; i < n; ++i) {
+    const double *fi = rhs + b->dof_off[i], *xi = x + b->dof_off[i];
+    if ((rc = b->planned ? residual_only(b->h[i], fi, xi) : pcg_residual(b->h[i], fi, xi, true)))
       return batch_fail(b, rc, "grid " + std::to_string(i) + ": " + b->h[i]->err);
-  if ((rc = batch_rr_download(b))) return rc;
+  }
+  if (b->planned && (rc = run_plan(b, 2, b->stream, true, true))) return batch_fail(b, rc, "batched launch failed");
+  if ((rc = batch_wait_norms(b))) return rc;
   int maxit = 0;
   for (int i = 0; i < n; ++i) {
     r0[i] = std::sqrt(b->rr_host[i]);
@@ -2921,15 +3011,20 @@ int dgmg_batch_solve(dgmg_batch* b, const double* rhs, double* x, double tol, dg
     }
   }
   if ((rc = batch_flags_upload(b))) return rc;
-  for (int i = 0; i < n; ++i)
-    if ((rc = pcg_init_b(b->h[i]))) return batch_fail(b, rc, "grid " + std::to_string(i) + ": " + b->h[i]->err);
+  if (b->planned) {
+    if ((rc = run_plan(b, 1, b->stream, true, true))) return batch_fail(b, rc, "batched launch failed");
+  } else {
+    for (int i = 0; i < n; ++i)
+      if ((rc = pcg_phase_b(b->h[i], true))) return batch_fail(b, rc, "grid " + std::to_string(i) + ": " + b->h[i]->err);
+  }
   for (int it = 1; it <= maxit; ++it) {
     bool any = false;
     for (int i = 0; i < n; ++i) any = any || b->flags_host[i];
     if (!any) break;
     if ((rc = batch_phase(b, 0, x))) return rc;
-    if ((rc = batch_rr_download(b))) return rc;
+    if ((rc = batch_wait_norms(b))) return rc;
     any = false;
+    bool check = false;
     for (int i = 0; i < n; ++i) {
       if (!b->flags_host[i]) continue;
       its[i] = it;
@@ -2940,13 +3035,23 @@ int dgmg_batch_solve(dgmg_batch* b, const double* rhs, double* x, double tol, dg
         if (it < 256) st[i].history[it] = rn[i];
       }
       if (!std::isfinite(rn[i])) return batch_fail(b, DGMG_ENONFINITE, "grid " + std::to_string(i) + ": residual not finite");
+      check = check || rn[i] <= rmax[i];
+    }
+    if (check) {
+      // exit confirmation on the true residuals, as for a single solve (the grids'
+      // device flags are still set, so their kernels run)
+      for (int i = 0; i < n; ++i) {
+        if (!b->flags_host[i] || !(rn[i] <= rmax[i])) continue;
+        if ((rc = pcg_residual(b->h[i], rhs + b->dof_off[i], x + b->dof_off[i], false)))
+          return batch_fail(b, rc, "grid " + std::to_string(i) + ": " + b->h[i]->err);
+      }
+      if ((rc = batch_wait_norms(b))) return rc;
+    }
+    for (int i = 0; i < n; ++i) {
+      if (!b->flags_host[i]) continue;
       bool done = false;
       if (rn[i] <= rmax[i]) {
-        // exit confirmation on the true residual, as for a single solve (the
-        // grid's device flag is still set, so its kernels run)
-        double rt;
-        if ((rc = true_residual(b->h[i], rhs + b->dof_off[i], x + b->dof_off[i], &rt)))
-          return batch_fail(b, rc, "grid " + std::to_string(i) + ": " + b->h[i]->err);
+        const double rt = std::sqrt(b->rr_host[i]);
         if (st) st[i].r_true = rt;
         done = rt <= rmax[i];
         if (!done && st) st[i].replacements++;

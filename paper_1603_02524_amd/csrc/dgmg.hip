@@ -14,6 +14,7 @@
 
 #include "../../include/dgmg.h"
 #include "kernels.hpp"
+#include "kernels_apply.hpp"
 #include "kernels_big.hpp"
 #include "kernels_coarse.hpp"
 #include "kernels_fdm3.hpp"
@@ -2256,15 +2257,6 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
   auto blocks_apply = [&](const LevelDev<T>& Lv) {
     return Lv.dim == 3 ? Kern<T, 3>::apply_blocks_of(Lv.NP, Lv.n_elem) : Kern<T, 2>::apply_blocks_of(Lv.NP, Lv.n_elem);
   };
-  auto apply_args = [&](const LevelDev<T>& Lv, const T* x, const T* fv, T* y) {
-    ApplyArgs<T> a;
-    a.L = Lv;
-    a.x = x;
-    a.f = fv;
-    a.y = y;
-    a.nblk = blocks_apply(Lv);
-    return a;
-  };
   // one smoothing call: steps s, sweeps i (EA: one, FA: one per direction);
   // keys {major, depthkey, s, i, sub-step}
   auto smooth = [&](int major, int depthkey, int l, int steps, bool u_zero) {
@@ -2284,7 +2276,7 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
           continue;
         }
         if (!uz) {
-          ApplyArgs<T> a = apply_args(Lv, u[l], f[l], rl);
+          ApplyArgs<T> a = apply_args<T>(Lv, u[l], f[l], rl, nullptr, blocks_apply(Lv));
           step({major, depthkey, s, i, 0}, BK_APPLY, lv.dim, {lv.NP, 1}, a.nblk, arg_bytes(a));
         }
         int np[3], NA, NL;
@@ -2363,10 +2355,10 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
       T* fc = f[l - 1];
       fnstep({1, k, 1000, 0, 0}, [h, l, ul, fl, rl, fc]() { return k_residual_restrict<T>(h, l, ul, fl, rl, fc); });
     } else if (m3) {
-      ApplyArgs<T> a = apply_args(Lv, u[l], f[l], f[l - 1]);
+      ApplyArgs<T> a = apply_args<T>(Lv, u[l], f[l], f[l - 1], nullptr, blocks_apply(Lv));
       step({1, k, 1000, 0, 0}, BK_APPLY, lv.dim, {lv.NP, 3}, a.nblk, arg_bytes(a));
     } else {
-      ApplyArgs<T> a = apply_args(Lv, u[l], f[l], rl);
+      ApplyArgs<T> a = apply_args<T>(Lv, u[l], f[l], rl, nullptr, blocks_apply(Lv));
       step({1, k, 1000, 0, 0}, BK_APPLY, lv.dim, {lv.NP, 1}, a.nblk, arg_bytes(a));
       XferArgs<T> x = xfer_args(Lv, rl, f[l - 1]);
       step({1, k, 1000, 0, 1}, BK_XFER, lv.dim, {lv.NP, lv.NPc, 1}, xfer_blocks(Lv), arg_bytes(x));
@@ -2437,13 +2429,9 @@ int batch_plan(dgmg_batch* b, bool fill) {
       st.fn = [b, h, off]() { return pcg_phase_a(h, b->x_cur + off); };
       steps[0].push_back(std::move(st));
     } else {
-    ApplyArgs<double> a;
-    a.L = Lt;
-    a.x = h->pp;
-    a.y = h->pq;
-    a.part = h->part;
-    a.nblk = Lt.dim == 3 ? Kern<double, 3>::apply_blocks_of(Lt.NP, Lt.n_elem)
-                         : Kern<double, 2>::apply_blocks_of(Lt.NP, Lt.n_elem);
+    const ApplyArgs<double> a = apply_args<double>(
+        Lt, h->pp, nullptr, h->pq, h->part,
+        Lt.dim == 3 ? Kern<double, 3>::apply_blocks_of(Lt.NP, Lt.n_elem) : Kern<double, 2>::apply_blocks_of(Lt.NP, Lt.n_elem));
     BStep st;
     st.key = {0};
     st.kind = BK_APPLY;

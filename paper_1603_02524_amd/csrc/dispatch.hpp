@@ -3,6 +3,7 @@
 #pragma once
 
 #include "kernels.hpp"
+#include "kernels_apply.hpp"
 #include "kernels_big.hpp"
 #include "kernels_fdm3.hpp"
 #include "kernels_se.hpp"

@@ -165,32 +165,13 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return s;  // valid in thread 0
 }
 
-// ================================================================ operator apply
-// y = A x (MODE 0), y = f - A x (MODE 1), y = A x plus per-block partial x.y (MODE 2),
-// or the restriction of f - A x to the next coarser level, y = (J^T x J^T x J^T)(f - A x)
-// per element (MODE 3: the V-cycle's residual and restriction in one pass; the
-// fine residual stays in LDS and the transfer's contraction passes run on it).
-// One thread owns one line of one element in one direction, and the lines of
-// all directions run at once (their global loads overlap instead of forming
-// one latency chain per direction).  Each node receives exactly one
-// contribution per direction, stored in that direction's LDS tile; the tiles
-// are summed in direction order at the end.  Neighbour traces and normal
-// derivatives are read from the neighbour's line (eq. (L:generic)).
-// Elements per block: lines of all directions fill about DGMG_APPLY_LINES threads.
-#ifndef DGMG_APPLY_LINES
-#define DGMG_APPLY_LINES 256
-#endif
-// Rows of the line product unrolled together (independent accumulation chains).
-#ifndef DGMG_APPLY_ROWS
-#define DGMG_APPLY_ROWS 1
-#endif
-template <int NP, int DIM>
-constexpr int apply_epb() {
-  return imax(1, DGMG_APPLY_LINES / (DIM * ipow(NP, DIM - 1)));
+// Quotient by a divisor known to the host: m = ceil(2^32 / d) where the product
+// fits (every n up to n_max is then exact), 0 otherwise.
+inline uint32_t div_magic(int64_t n_max, int d) {
+  return n_max * d < (int64_t(1) << 32) && d > 1 ? (uint32_t)(((uint64_t(1) << 32) + d - 1) / d) : 0;
 }
-template <int NP, int DIM>
-constexpr int apply_threads() {
-  return imin(1024, round64(apply_epb<NP, DIM>() * DIM * ipow(NP, DIM - 1)));
+__device__ __forceinline__ int div_by(int n, int d, uint32_t m) {
+  return m ? (int)__umulhi((uint32_t)n, m) : (d == 1 ? n : n / d);
 }
 
 // A kernel-argument pointer pinned in scalar registers: selecting between such
@@ -223,388 +204,6 @@ __device__ __forceinline__ void staged_copy(Ld ld, St st, int n = N) {
     const int e = tid + c * NT;
     if (e < n) st(e, v[c]);
   }
-}
-
-// Own elements staged in LDS (coalesced loads) when the tiles are small: the
-// lines of the block's own elements are then read from LDS and only the
-// neighbours' lines from global memory.  A line along direction 0 is contiguous,
-// so the lanes of a wave (one line each) are NP values apart and a load touches
-// about one cache line per lane: staging removes the costliest third of the line
-// loads.
-template <int NP, int DIM>
-constexpr bool apply_stage_own() {
-  return NP <= 9 && apply_epb<NP, DIM>() * DIM * ipow(NP, DIM - 1) <= 1024;
-}
-template <class T, int DIM, int NP>
-constexpr size_t apply_shmem() {
-  return (size_t)(DIM + (apply_stage_own<NP, DIM>() ? 1 : 0)) * apply_epb<NP, DIM>() * ipow(NP, DIM) * sizeof(T);
-}
-
-// Everything one line needs besides its own values: indices, the neighbours'
-// lines (masks ml, mr), the face coefficients and the mass factor.
-template <class T, int NP>
-struct ApplyLine {
-  int d, el, base, stride;
-  T ml, mr, mo;
-  T c_two_dx, c_cl, c_cnl, c_bl, c_cr, c_cnr, c_br;
-  T wlv[NP], wrv[NP];
-};
-
-template <class T, int DIM, int NIN, int NOUT, int NEF, int D, bool RESTRICT, int NPC>
-__device__ __forceinline__ void xfer_pass(const T* __restrict__ sJ, const T* __restrict__ src,
-                                          T* __restrict__ dst, int ne);
-
-template <class T>
-struct ApplyArgs {
-  LevelDev<T> L;
-  const T* x = nullptr;
-  const T* f = nullptr;
-  T* y = nullptr;
-  double* part = nullptr;
-  int nblk = 0;
-};
-
-// BATCH: the arguments come from the work list bl (ntot logical blocks in all)
-template <class T, int DIM, int NP, int MODE, bool BATCH = false>
-__global__ void __launch_bounds__(1024) apply_kernel(ApplyArgs<T> a0, BatchList<ApplyArgs<T>> bl, int ntot) {
-  constexpr int NE = ipow(NP, DIM), NLN = ipow(NP, DIM - 1), EPB = apply_epb<NP, DIM>();
-  constexpr int P = NP - 1;
-  constexpr bool STAGE = apply_stage_own<NP, DIM>();
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  // per-direction contribution tiles, then (STAGE) the block's own elements
-  T* sy = reinterpret_cast<T*>(smem_raw);
-  T* sx = sy + DIM * EPB * NE;
-  __shared__ double red[16];
-  __shared__ __align__(16) int sargs_raw[BATCH ? sizeof(ApplyArgs<T>) / sizeof(int) : 1];
-  ApplyArgs<T>* sargs = reinterpret_cast<ApplyArgs<T>*>(sargs_raw);
-  const ApplyArgs<T>* ap;
-  int blk;
-  if constexpr (BATCH) {
-    const int b = xcd_block(ntot);
-    if (b < 0) return;
-    blk = batch_pick(bl, b, sargs);
-    ap = sargs;
-  } else {
-    blk = xcd_block(a0.nblk);
-    if (blk < 0) return;
-    ap = &a0;
-  }
-  const LevelDev<T>& L = ap->L;
-  const T* __restrict__ x = ap->x;
-  const T* __restrict__ f = ap->f;
-  T* __restrict__ y = ap->y;
-  double* __restrict__ part = ap->part;
-  if (inactive(L.active)) return;
-  const int e0 = blk * EPB;
-  const int ne = imin(EPB, L.n_elem - e0);
-  const int tid = threadIdx.x, nth = blockDim.x;
-  const int64_t g0 = (int64_t)e0 * NE;
-  const int N1 = L.dir[0].N, N2 = L.dir[1].N;
-  // stiffness matrix rows: uniform addresses in the constant address space,
-  // so the row loop reads them with scalar loads into SGPR operands; rows
-  // longer than 72 bytes (2D, large P) would not fit the scalar registers and
-  // are staged in LDS instead (uniform-address reads)
-  constexpr bool SLS = NP * sizeof(T) <= 72;
-  __shared__ T sLsL[SLS ? 1 : NP * NP];
-  if constexpr (!SLS) {
-    for (int q = tid; q < NP * NP; q += nth) sLsL[q] = L.Ls[q];
-    __syncthreads();
-  }
-  // MODE 3: the interpolation matrix J (NP x NPC, row-major) of the restriction
-  constexpr int NPC = (NP - 1) / 2 + 1;  // N_P of the next coarser level, P_c = floor(P / 2)
-  static_assert(MODE != 3 || STAGE, "the fused restriction needs the own-element LDS buffer");
-  __shared__ T sJx[MODE == 3 ? NP * NPC : 1];
-  if constexpr (MODE == 3)
-    for (int q = tid; q < NP * NPC; q += nth) sJx[q] = L.J[q];
-  using CT = const __attribute__((address_space(4))) T;
-  CT* __restrict__ Ls = (CT*)L.Ls;
-  CT* __restrict__ D0 = (CT*)L.D;
-  CT* __restrict__ DP = (CT*)(L.D + P * NP);
-  const T* __restrict__ rho = L.rho;
-  const int per_dir = ne * NLN;
-  // per-direction kernel arguments in scalar registers; the per-lane choice
-  // below is arithmetic with 0/1 flags (a select chain over them gets turned
-  // into a small scratch array or into per-lane loads of the arguments)
-  using GT = const __attribute__((address_space(1))) T;  // global memory
-  GT* ec0 = (GT*)sgpr_ptr(L.dir[0].ecoef);
-  GT* ec1 = (GT*)sgpr_ptr(L.dir[1].ecoef);
-  GT* ec2 = (GT*)sgpr_ptr(L.dir[DIM - 1].ecoef);
-  const int64_t eo1 = ec1 - ec0, eo2 = ec2 - ec0;
-  const int per0 = __builtin_amdgcn_readfirstlane(L.dir[0].periodic);
-  const int per1 = __builtin_amdgcn_readfirstlane(L.dir[1].periodic);
-  const int per2 = __builtin_amdgcn_readfirstlane(L.dir[DIM - 1].periodic);
-  const int N3 = __builtin_amdgcn_readfirstlane(L.dir[DIM - 1].N);
-  // The vector the epilogue reads besides the tiles (f for the residual, x for
-  // the dot product) is fetched now, so that its latency overlaps the line work
-  // (launches use apply_threads() threads, so FQ values per thread cover the block).
-  constexpr int TH = apply_threads<NP, DIM>(), FQ = (EPB * NE + TH - 1) / TH;
-  constexpr bool PREF = MODE != 0 && NP <= 9;
-  T pre[PREF ? FQ : 1];
-  if constexpr (PREF) {
-    const T* __restrict__ src = (MODE == 1 || MODE == 3) ? f : x;
-#pragma unroll
-    for (int j = 0; j < FQ; ++j) {
-      const int q = tid + j * nth;
-      pre[j] = q < ne * NE ? src[g0 + q] : T(0);
-    }
-  }
-  // Loads of line q (all issued as one group): neighbours' lines (unconditional
-  // loads at a valid address, masked later), coefficients, mass factors and,
-  // unless staged, the own line into v.
-  auto prep = [&](int q, ApplyLine<T, NP>& A, T* v, bool own) {
-    const int d = q / per_dir;
-    const int ln = q - d * per_dir;
-    const int el = ln / NLN, t = ln - el * NLN;
-    const int e = e0 + el;
-    int m[3];
-    m[0] = e % N1;
-    m[1] = DIM == 3 ? (e / N1) % N2 : e / N1;
-    m[2] = DIM == 3 ? e / (N1 * N2) : 0;
-    // per-direction fields chosen per lane (the direction varies inside a wave)
-    const int f0 = d == 0, f1 = d == 1, f2 = d == 2;
-    const int md = f0 * m[0] + f1 * m[1] + f2 * m[2];
-    const int Nd = f0 * N1 + f1 * N2 + f2 * N3;
-    const int perd = f0 * per0 + f1 * per1 + f2 * per2;
-    GT* __restrict__ ecoef = ec0 + (f1 * eo1 + f2 * eo2);
-    const int estride = f0 + f1 * N1 + f2 * (N1 * N2);
-    // line base and stride inside the element; indices of the other directions
-    const int ia = t % NP, ib = t / NP;  // local indices of the other directions (in order)
-    int base, stride;
-    if (d == 0) {
-      base = t * NP; stride = 1;
-    } else if (d == 1) {
-      base = ia + ib * NP * NP; stride = NP;
-    } else {
-      base = t; stride = NP * NP;
-    }
-    A.d = d;
-    A.el = el;
-    A.base = base;
-    A.stride = stride;
-    // neighbours along d: m -/+ 1, wrapped when periodic, none (-1) at a
-    // Dirichlet end (the element neighbour table of the setup, computed here so
-    // that no load depends on another)
-    const int nl = md > 0 ? md - 1 : (perd ? Nd - 1 : -1);
-    const int nr = md < Nd - 1 ? md + 1 : (perd ? 0 : -1);
-    A.ml = nl >= 0 ? T(1) : T(0);
-    A.mr = nr >= 0 ? T(1) : T(0);
-    if (own) {
-#pragma unroll
-      for (int k = 0; k < NP; ++k) v[k] = x[g0 + el * NE + base + k * stride];
-    }
-    GT* c = ecoef + md * ECOEF_N;
-    A.c_two_dx = c[E_TWO_DX];
-    A.c_cl = c[E_CL];
-    A.c_cnl = c[E_CNL];
-    A.c_bl = c[E_BL];
-    A.c_cr = c[E_CR];
-    A.c_cnr = c[E_CNR];
-    A.c_br = c[E_BR];
-    const T ra = rho[ia], rb = DIM == 3 ? rho[ib] : T(1);
-    T ha, hb;  // half element sizes of the other directions
-    if (DIM == 2) {
-      ha = d == 0 ? ec1[m[1] * ECOEF_N + E_HALF_DX] : ec0[m[0] * ECOEF_N + E_HALF_DX];
-      hb = T(1);
-    } else {
-      const T h0 = ec0[m[0] * ECOEF_N + E_HALF_DX];
-      const T h1 = ec1[m[1] * ECOEF_N + E_HALF_DX];
-      const T h2 = ec2[m[2] * ECOEF_N + E_HALF_DX];
-      ha = d == 0 ? h1 : h0;
-      hb = d == 2 ? h1 : h2;
-    }
-    // mass factor of the other directions at this line
-    A.mo = DIM == 2 ? ha * ra : ha * ra * hb * rb;
-    const T* wl = x + (int64_t)(e + (nl >= 0 ? nl - md : 0) * estride) * NE + base;
-    const T* wr = x + (int64_t)(e + (nr >= 0 ? nr - md : 0) * estride) * NE + base;
-#pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      A.wlv[k] = wl[k * stride];
-      A.wrv[k] = wr[k * stride];
-    }
-  };
-  // the line's contribution mo * (L_d-row terms) into its direction's tile
-  auto finish = [&](const ApplyLine<T, NP>& A, const T* v) {
-    T d0 = 0, dP = 0, dL = 0, dR = 0;
-#pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      d0 += D0[k] * v[k];
-      dP += DP[k] * v[k];
-      dL += DP[k] * A.wlv[k];
-      dR += D0[k] * A.wrv[k];
-    }
-    const T uL = A.ml * A.wlv[P], uR = A.mr * A.wrv[0];
-    dL *= A.ml;
-    dR *= A.mr;
-    const T jl = v[0] - uL, jr = v[P] - uR;
-    const T fl = A.c_cl * d0 + A.c_cnl * dL + A.c_bl * jl;
-    const T fr = -A.c_cr * dP - A.c_cnr * dR + A.c_br * jr;
-    const T cl = A.c_cl * jl, cr = A.c_cr * jr, tdx = A.c_two_dx;
-    T* __restrict__ syd = sy + (A.d * ne + A.el) * NE + A.base;
-#pragma unroll DGMG_APPLY_ROWS  // a few rows of Ls live at a time (registers for the line data)
-    for (int i = 0; i < NP; ++i) {
-      T s = 0;
-#pragma unroll
-      for (int k = 0; k < NP; ++k) {
-        if constexpr (SLS) s += Ls[__builtin_amdgcn_readfirstlane(i) * NP + k] * v[k];
-        else s += sLsL[i * NP + k] * v[k];
-      }
-      const int iu = __builtin_amdgcn_readfirstlane(i);
-      T o = tdx * s + cl * D0[iu] - cr * DP[iu];
-      if (i == 0) o += fl;
-      if (i == P) o += fr;
-      syd[i * A.stride] = A.mo * o;
-    }
-  };
-  if constexpr (STAGE) {
-    // one line per thread (the launch covers all lines of the block)
-    constexpr int SQ = (EPB * NE + TH - 1) / TH;
-    T st[SQ];
-#pragma unroll
-    for (int j = 0; j < SQ; ++j) {
-      const int q = tid + j * nth;
-      st[j] = q < ne * NE ? x[g0 + q] : T(0);
-    }
-    const bool has = tid < DIM * per_dir;
-    ApplyLine<T, NP> A;
-    T v[NP];
-    prep(has ? tid : 0, A, v, false);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int j = 0; j < SQ; ++j) {
-      const int q = tid + j * nth;
-      if (q < ne * NE) sx[q] = st[j];
-    }
-    __syncthreads();
-    if (has) {
-#pragma unroll
-      for (int k = 0; k < NP; ++k) v[k] = sx[A.el * NE + A.base + k * A.stride];
-      finish(A, v);
-    }
-  } else {
-    for (int q = tid; q < DIM * per_dir; q += nth) {
-      ApplyLine<T, NP> A;
-      T v[NP];
-      prep(q, A, v, true);
-      if constexpr (NP <= 9) __builtin_amdgcn_sched_barrier(0);
-      finish(A, v);
-    }
-  }
-  __syncthreads();
-  double acc = 0.0;
-  const int dstride = ne * NE;
-  auto out = [&](int q, T other) {
-    T val = sy[q] + sy[dstride + q];
-    if (DIM == 3) val += sy[2 * dstride + q];
-    if (MODE == 0) {
-      y[g0 + q] = val;
-    } else if (MODE == 1) {
-      y[g0 + q] = other - val;
-    } else if (MODE == 3) {
-      sx[q] = other - val;  // the own elements' x are no longer needed
-    } else {
-      y[g0 + q] = val;
-      acc += (double)other * (double)val;
-    }
-  };
-  if constexpr (PREF) {
-#pragma unroll
-    for (int j = 0; j < FQ; ++j) {
-      const int q = tid + j * nth;
-      if (q < ne * NE) out(q, pre[j]);
-    }
-  } else if constexpr (MODE == 0) {
-    for (int q = tid; q < ne * NE; q += nth) out(q, T(0));
-  } else {
-    // every load of f (x) issued before the sums that use them
-    const T* __restrict__ src = (MODE == 1 || MODE == 3) ? f : x;
-    staged_copy<T, TH, EPB * NE>([&](int q) { return src[g0 + q]; }, [&](int q, T v) { out(q, v); }, ne * NE);
-  }
-  if (MODE == 2) {
-    const double s = block_sum(acc, red);
-    if (tid == 0) part[blk] = s;
-  }
-  if constexpr (MODE == 3) {
-    // the transfer kernel's restriction passes, on the residual in LDS (the
-    // direction tiles serve as the two pass buffers); y is the coarse vector
-    constexpr int NEC = ipow(NPC, DIM);
-    __syncthreads();
-    T* bA = sy;
-    T* bB = sy + EPB * NE;
-    xfer_pass<T, DIM, NP, NPC, NE, 0, true, NPC>(sJx, sx, bA, ne);
-    __syncthreads();
-    xfer_pass<T, DIM, NP, NPC, NE, 1, true, NPC>(sJx, bA, bB, ne);
-    __syncthreads();
-    const T* res = bB;
-    if constexpr (DIM == 3) {
-      xfer_pass<T, DIM, NP, NPC, NE, 2, true, NPC>(sJx, bB, bA, ne);
-      __syncthreads();
-      res = bA;
-    }
-    T* yc = y + (int64_t)e0 * NEC;
-    for (int q = tid; q < ne * NEC; q += nth) {
-      const int el = q / NEC;
-      yc[q] = res[el * NE + q - el * NEC];
-    }
-  }
-}
-
-template <class T, int DIM, int NP, int MODE, bool BATCH>
-void apply_go(const ApplyArgs<T>& a, const BatchList<ApplyArgs<T>>& bl, int nlog, hipStream_t s) {
-  constexpr int TH = apply_threads<NP, DIM>();
-  const size_t shm = apply_shmem<T, DIM, NP>();
-  if (shm > 65536)
-    (void)hipFuncSetAttribute((const void*)apply_kernel<T, DIM, NP, MODE, BATCH>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
-  hipLaunchKernelGGL((apply_kernel<T, DIM, NP, MODE, BATCH>), dim3(xcd_grid(nlog)), dim3(TH), shm, s, a, bl, nlog);
-}
-
-// Blocks of one grid's apply: groups of apply_epb elements.
-template <int DIM, int NP>
-int apply_blocks(int n_elem) {
-  constexpr int EPB = apply_epb<NP, DIM>();
-  return (n_elem + EPB - 1) / EPB;
-}
-
-// The fused residual + restriction (mode 3) is built where the own elements are
-// staged in LDS and the coarse level's order follows P_c = floor(P / 2).
-template <class T, int DIM, int NP>
-bool apply_mode3_ok(const LevelDev<T>& L) {
-  if constexpr (apply_stage_own<NP, DIM>()) return L.NPc == (NP - 1) / 2 + 1 && L.J != nullptr;
-  return false;
-}
-
-template <class T, int DIM, int NP, bool BATCH>
-int apply_mode(int mode, const ApplyArgs<T>& a, const BatchList<ApplyArgs<T>>& bl, int nlog, hipStream_t s) {
-  if (mode == 0) apply_go<T, DIM, NP, 0, BATCH>(a, bl, nlog, s);
-  else if (mode == 1) apply_go<T, DIM, NP, 1, BATCH>(a, bl, nlog, s);
-  else if (mode == 2) apply_go<T, DIM, NP, 2, BATCH>(a, bl, nlog, s);
-  else if constexpr (apply_stage_own<NP, DIM>()) apply_go<T, DIM, NP, 3, BATCH>(a, bl, nlog, s);
-  else return -4;
-  return 0;
-}
-
-template <class T, int DIM, int NP>
-int apply_launch(const LevelDev<T>& L, int mode, const T* x, const T* f, T* y, double* part,
-                 int* nblk_out, hipStream_t s) {
-  const int nblk = apply_blocks<DIM, NP>(L.n_elem);
-  if (nblk_out) *nblk_out = nblk;
-  // fused residual + restriction: otherwise the caller runs the two steps
-  if (mode == 3 && !apply_mode3_ok<T, DIM, NP>(L)) return -4;
-  ApplyArgs<T> a;
-  a.L = L;
-  a.x = x;
-  a.f = f;
-  a.y = y;
-  a.part = part;
-  a.nblk = nblk;
-  return apply_mode<T, DIM, NP, false>(mode, a, BatchList<ApplyArgs<T>>{}, nblk, s);
-}
-
-// One launch over the applies of many grids (same NP and mode): ntot logical
-// blocks, grid g's apply_blocks in the range of bl.
-template <class T, int DIM, int NP>
-int apply_batch_launch(int mode, const BatchList<ApplyArgs<T>>& bl, int ntot, hipStream_t s) {
-  return apply_mode<T, DIM, NP, true>(mode, ApplyArgs<T>{}, bl, ntot, s);
 }
 
 // ================================================================ FDM patch solve
@@ -1461,6 +1060,8 @@ int transfer_batch_launch(bool restrict_, const BatchList<XferArgs<T>>& bl, int 
 template <class T>
 struct Fdm3Args;  // kernels_fdm3.hpp
 
+template <class T>
+struct ApplyArgs;  // kernels_apply.hpp
 template <class T, int DIM>
 struct Kern {
   // scratch: apply_big_scratch(n_elem, NP) elements (3D levels with NP = 33 only).

@@ -1,0 +1,604 @@
+// Operator apply on DG levels (compiled orders).
+// y = A x (MODE 0), y = f - A x (MODE 1), y = A x plus per-block partial x.y (MODE 2),
+// or the restriction of f - A x to the next coarser level, y = (J^T x J^T x J^T)(f - A x)
+// per element (MODE 3: the V-cycle's residual and restriction in one pass; the
+// fine residual stays in LDS and the transfer's contraction passes run on it).
+//
+// 3D: a block takes apply_epb consecutive elements and goes through the directions one
+// after the other; in each, a thread owns one line of one element: its values from LDS,
+// the two neighbours' lines (traces and normal derivatives, eq. (L:generic)), the rows of
+// the 1D matrix from scalar registers.  Each node receives one contribution per
+// direction, added up in LDS in direction order; the last direction's lanes run along
+// the vector, so they read f and write y themselves.
+// Bound: memory in FP32, the vector instructions and their waits in FP64.  The form
+// before (lines of all directions at once, the direction chosen per lane, every
+// neighbour line from global memory at the line's stride) issued more than twice the
+// instructions, and its lines along direction 0 touched one cache line per lane and load;
+// here the direction and so every stride is a constant, direction 0 sees its neighbours
+// through LDS (coalesced loads), and a block loads its arguments in one group.  Residual,
+// before and after: 32^3 P = 8 FP32 132 -> 86 us (3.3 TB/s), 16^3 P = 8 FP64 27.6 -> 22.3 us
+// (3.2 TB/s), 9x7x11 P = 12 FP32 16.3 -> 11.8 and FP64 30 -> 18.3 us, 7x9x6 P = 16 FP64
+// 53.5 -> 42 us.
+// 2D: a thread per node (apply2_kernel).
+#pragma once
+
+#include "kernels.hpp"
+
+namespace dgmg {
+
+// Elements per block.  3D: the lines of one direction fill whole waves (P = 8: 243 of 256
+// lanes; one element per block, 81 of 128, 32 instead of 22 us, two, 162 of 192, 27 us).
+// 2D: about 256 nodes.
+template <int NP, int DIM>
+constexpr int apply_epb() {
+  return DIM == 3 ? imax(1, (NP < 7 ? 128 : 256) / (NP * NP)) : imax(1, 256 / (NP * NP));
+}
+template <int NP, int DIM>
+constexpr int apply_threads() {
+  return DIM == 3 ? round64(apply_epb<NP, DIM>() * NP * NP) : imin(576, round64(apply_epb<NP, DIM>() * NP * NP));
+}
+// 3D: the neighbours along direction 0 outside the block are staged in the tile of
+// contributions, left and right at once, or (one large element per block, where LDS
+// bounds the blocks of a CU) one after the other.
+template <int NP>
+constexpr bool apply_two_halos() {
+  return NP < 12;
+}
+template <class T, int DIM, int NP>
+size_t apply_shmem(bool periodic0) {
+  constexpr int EPB = apply_epb<NP, DIM>();
+  if (DIM == 2) return (size_t)5 * EPB * NP * NP * sizeof(T);
+  const int halos = apply_two_halos<NP>() ? (EPB > 1 && periodic0 ? 4 : 2) : 1;
+  return (size_t)(EPB + imax(EPB, halos)) * ipow(NP, 3) * sizeof(T);
+}
+// Waves per SIMD that the registers have to leave room for (P = 16 FP64: two blocks of
+// five waves fit the LDS, and with room for three the lines spilled: 53 instead of 42 us).
+template <class T, int NP>
+constexpr int apply_occupancy() {
+  return sizeof(T) == 8 ? (NP <= 9 ? 4 : (NP <= 13 ? 3 : 2)) : (NP <= 9 ? 6 : 4);
+}
+
+template <class T>
+struct ApplyArgs {
+  const T* x = nullptr;
+  const T* f = nullptr;
+  T* y = nullptr;
+  double* part = nullptr;
+  const T* Ls = nullptr;
+  const T* D = nullptr;
+  const T* rho = nullptr;
+  const T* J = nullptr;
+  const T* ec[3] = {nullptr, nullptr, nullptr};  // ECOEF_N coefficients per element of a direction
+  const int* active = nullptr;
+  int n_elem = 0, nblk = 0;
+  int N0 = 1, N1 = 1, N2 = 1;
+  int per = 0;              // bit d: periodic in direction d
+  uint32_t mg0 = 0, mg1 = 0;  // divisions by N0 and N1
+};
+template <class T>
+ApplyArgs<T> apply_args(const LevelDev<T>& L, const T* x, const T* f, T* y, double* part, int nblk) {
+  ApplyArgs<T> a;
+  a.x = x;
+  a.f = f;
+  a.y = y;
+  a.part = part;
+  a.Ls = L.Ls;
+  a.D = L.D;
+  a.rho = L.rho;
+  a.J = L.J;
+  for (int d = 0; d < L.dim; ++d) {
+    a.ec[d] = L.dir[d].ecoef;
+    a.per |= L.dir[d].periodic ? 1 << d : 0;
+  }
+  a.active = L.active;
+  a.n_elem = L.n_elem;
+  a.nblk = nblk;
+  a.N0 = L.dir[0].N;
+  a.N1 = L.dir[1].N;
+  a.N2 = L.dim == 3 ? L.dir[2].N : 1;
+  a.mg0 = div_magic(L.n_elem, a.N0);
+  a.mg1 = div_magic(L.n_elem, a.N1);
+  return a;
+}
+
+// a b rounded by itself, not as a part of a fused multiply-add: each direction's
+// contribution is a value of its own, the same wherever it is added up
+template <class T>
+__device__ __forceinline__ T mul_alone(T a, T b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
+// BATCH: the arguments come from the work list bl (ntot logical blocks in all)
+template <class T, int NP, int MODE, bool BATCH = false>
+__global__ void __launch_bounds__((apply_threads<NP, 3>()))
+    __attribute__((amdgpu_waves_per_eu((apply_occupancy<T, NP>()))))
+    apply_kernel(ApplyArgs<T> a0, BatchList<ApplyArgs<T>> bl, int ntot) {
+  constexpr int NE = NP * NP * NP, NLN = NP * NP, EPB = apply_epb<NP, 3>(), TH = apply_threads<NP, 3>();
+  constexpr int P = NP - 1, NPC = (NP - 1) / 2 + 1;  // NPC: N_P of the next coarser level, P_c = floor(P / 2)
+  constexpr bool TWO = apply_two_halos<NP>();
+  static_assert(TWO || EPB == 1, "one halo at a time: one element per block");
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* sx = reinterpret_cast<T*>(smem_raw);  // the block's own elements
+  T* tile = sx + EPB * NE;                 // contributions (first the halo elements of direction 0)
+  __shared__ T sC[EPB * 3 * ECOEF_N];
+  __shared__ T sJx[MODE == 3 ? NP * NPC : 1];
+  __shared__ double red[16];
+  __shared__ __align__(16) int sargs_raw[BATCH ? sizeof(ApplyArgs<T>) / sizeof(int) : 1];
+  const ApplyArgs<T>* ap;
+  int blk = 0;
+  if constexpr (BATCH) {
+    const int b = xcd_block(ntot);
+    if (b < 0) return;
+    ApplyArgs<T>* sargs = reinterpret_cast<ApplyArgs<T>*>(sargs_raw);
+    blk = batch_pick(bl, b, sargs);
+    ap = sargs;
+  } else {
+    ap = &a0;
+  }
+  // every argument into scalar registers by one group of loads
+  const auto uni = [](int v) { return BATCH ? __builtin_amdgcn_readfirstlane(v) : v; };
+  const auto ptr = [](auto* q) { return BATCH ? sgpr_ptr(q) : q; };
+  const T *px = ptr(ap->x), *pf = ptr(ap->f), *pLs = ptr(ap->Ls), *pD = ptr(ap->D), *prho = ptr(ap->rho);
+  const T *pe0 = ptr(ap->ec[0]), *pe1 = ptr(ap->ec[1]), *pe2 = ptr(ap->ec[2]);
+  T* py = ptr(ap->y);
+  const int* act = ptr(ap->active);
+  int n_elem = uni(ap->n_elem), nblk = uni(ap->nblk), N0 = uni(ap->N0), N1 = uni(ap->N1), N2 = uni(ap->N2);
+  int per = uni(ap->per);
+  uint32_t mg0 = uni(ap->mg0), mg1 = uni(ap->mg1);
+  if constexpr (!BATCH) {
+    asm volatile("" : "+s"(px), "+s"(pf), "+s"(pLs), "+s"(pD), "+s"(prho), "+s"(pe0), "+s"(pe1), "+s"(pe2), "+s"(py),
+                 "+s"(act), "+s"(n_elem), "+s"(nblk), "+s"(N0), "+s"(N1), "+s"(N2), "+s"(per), "+s"(mg0), "+s"(mg1));
+    blk = xcd_block(nblk);
+    if (blk < 0) return;
+  }
+  using G = const __attribute__((address_space(1))) T;   // global memory
+  using CT = const __attribute__((address_space(4))) T;  // constant: scalar loads
+  G *x = (G*)px, *f = (G*)pf, *rho = (G*)prho, *ec0 = (G*)pe0, *ec1 = (G*)pe1, *ec2 = (G*)pe2;
+  auto* y = (__attribute__((address_space(1))) T*)py;
+  CT *Ls = (CT*)pLs, *D0 = (CT*)pD, *DP = (CT*)(pD + P * NP);
+  if (act != nullptr && *(const __attribute__((address_space(1))) int*)act == 0) return;
+  const int e0 = uni(blk) * EPB, ne = imin(EPB, n_elem - e0), e_end = e0 + ne - 1;
+  const int tid = threadIdx.x;
+  const int64_t g0 = (int64_t)e0 * NE;
+  G* xb = x + g0;
+  const bool per0 = per & 1, per1 = per & 2, per2 = per & 4;
+
+  // the own elements and the elements beside the block along direction 0: left of its first
+  // and right of its last element; on a periodic row cut by the block also the other ends
+  const int row0 = uni(div_by(e0, N0, mg0)) * N0, row1 = uni(div_by(e_end, N0, mg0)) * N0;
+  const int hl = e0 > row0 ? e0 - 1 : (per0 ? row0 + N0 - 1 : e0);
+  const int hr = e_end < row1 + N0 - 1 ? e_end + 1 : (per0 ? row1 : e_end);
+  const int hl1 = row1 + N0 - 1, hr1 = row0;  // (used when per0 and the block spans rows)
+  constexpr int CO = (EPB * NE + TH - 1) / TH, CH = (NE + TH - 1) / TH;
+  T so[CO], sl[CH], sr[CH];
+#pragma unroll
+  for (int c = 0; c < CO; ++c) so[c] = xb[imin(tid + c * TH, ne * NE - 1)];
+  auto load_halo = [&](T* s, int e) {
+    G* xe = x + (int64_t)e * NE;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) s[c] = xe[c + 1 < CH || NE % TH == 0 ? tid + c * TH : imin(tid + c * TH, NE - 1)];
+  };
+  auto store_halo = [&](const T* s, int slot) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int q = tid + c * TH;
+      if (c + 1 < CH || NE % TH == 0 || q < NE) tile[slot * NE + q] = s[c];
+    }
+  };
+  load_halo(sl, hl);
+  load_halo(sr, hr);
+  // coefficients of the block's elements
+  for (int q = tid; q < ne * 3 * ECOEF_N; q += TH) {
+    const int c = q % ECOEF_N, ed = q / ECOEF_N, el = ed / 3, d = ed - el * 3;
+    const int e = e0 + el, r = div_by(e, N0, mg0), r2 = div_by(r, N1, mg1);
+    G* ec = d == 0 ? ec0 + (e - r * N0) * ECOEF_N : (d == 1 ? ec1 + (r - r2 * N1) * ECOEF_N : ec2 + r2 * ECOEF_N);
+    sC[q] = ec[c];
+  }
+  if constexpr (MODE == 3) {
+    G* J = (G*)ptr(ap->J);
+    for (int q = tid; q < NP * NPC; q += TH) sJx[q] = J[q];
+  }
+  // this thread's lines: element el, position (ia, ib) in the other directions, in order
+  const bool has = tid < ne * NLN;
+  const int el = has ? tid / NLN : 0, t = has ? tid - el * NLN : 0;
+  const int ia = t % NP, ib = t / NP;
+  const int e = e0 + el, rw = div_by(e, N0, mg0), m0 = e - rw * N0;
+  const int m2 = div_by(rw, N1, mg1), m1 = rw - m2 * N1;
+  const T ra = rho[ia], rb = rho[ib];
+  // neighbours along d: m -/+ 1, wrapped when periodic, none (the element itself, masked) at a
+  // Dirichlet end
+  const bool l0 = m0 > 0 || per0, r0 = m0 < N0 - 1 || per0;
+  const bool l1 = m1 > 0 || per1, r1 = m1 < N1 - 1 || per1;
+  const bool l2 = m2 > 0 || per2, r2 = m2 < N2 - 1 || per2;
+  const int st2 = N0 * N1;
+  const int b1 = ia + ib * NP * NP;
+  auto load_lines = [&](int nl, int nr, int base, auto stride, T* wl, T* wr) {
+    G *pl = x + ((int64_t)nl * NE + base), *pr = x + ((int64_t)nr * NE + base);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      wl[k] = pl[k * stride];
+      wr[k] = pr[k * stride];
+    }
+  };
+  using S0 = std::integral_constant<int, 1>;
+  using S1 = std::integral_constant<int, NP>;
+  using S2 = std::integral_constant<int, NP * NP>;
+  T wl[NP], wr[NP];
+  load_lines(m1 > 0 ? e - N0 : (per1 ? e + (N1 - 1) * N0 : e), m1 < N1 - 1 ? e + N0 : (per1 ? e - (N1 - 1) * N0 : e), b1,
+             S1{}, wl, wr);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int c = 0; c < CO; ++c) {
+    const int q = tid + c * TH;
+    if (q < ne * NE) sx[q] = so[c];
+  }
+  store_halo(sl, 0);
+  if constexpr (TWO) {
+    store_halo(sr, 1);
+    if constexpr (EPB > 1) {
+      if (per0 && row1 != row0) {
+        load_halo(sl, hl1);
+        load_halo(sr, hr1);
+        store_halo(sl, 2);
+        store_halo(sr, 3);
+      }
+    }
+  }
+  __syncthreads();
+
+  // The line's contribution mo * (L_d-row terms), row i handed to st(i, value).
+  auto trace = [&](CT* row, const T* w, T& der) {
+    der = 0;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) der += row[k] * w[k];
+  };
+  auto line = [&](int d, const T* v, T dL, T uL, T dR, T uR, bool hasl, bool hasr, T mo, auto st) {
+    const T* c = sC + (el * 3 + d) * ECOEF_N;
+    T d0, dP;
+    trace(D0, v, d0);
+    trace(DP, v, dP);
+    const T ml = hasl ? T(1) : T(0), mr = hasr ? T(1) : T(0);
+    const T jl = v[0] - ml * uL, jr = v[P] - mr * uR;
+    const T fl = c[E_CL] * d0 + c[E_CNL] * (ml * dL) + c[E_BL] * jl;
+    const T fr = -c[E_CR] * dP - c[E_CNR] * (mr * dR) + c[E_BR] * jr;
+    const T cl = c[E_CL] * jl, cr = c[E_CR] * jr, tdx = c[E_TWO_DX];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      T s = 0;
+#pragma unroll
+      for (int k = 0; k < NP; ++k) s += Ls[i * NP + k] * v[k];
+      T o = tdx * s + cl * D0[i] - cr * DP[i];
+      if (i == 0) o += fl;
+      if (i == P) o += fr;
+      st(i, mul_alone(mo, o));
+    }
+  };
+  auto half = [&](int d) { return sC[(el * 3 + d) * ECOEF_N + E_HALF_DX]; };
+
+  // ---- direction 0: neighbours in the block or in the halo slots
+  {
+    const int nl = m0 > 0 ? e - 1 : (per0 ? e + N0 - 1 : e), nr = m0 < N0 - 1 ? e + 1 : (per0 ? e - (N0 - 1) : e);
+    const bool il = nl >= e0 && nl <= e_end, ir = nr >= e0 && nr <= e_end;
+    const int ol = il ? (nl - e0) * NE : (EPB + (EPB == 1 || el == 0 ? 0 : 2)) * NE;
+    const int orr = ir ? (nr - e0) * NE : (EPB + (TWO ? (EPB == 1 || el == ne - 1 ? 1 : 3) : 0)) * NE;
+    T v[NP], dL, dR, uL, uR;
+    const T* pv = sx + el * NE + t * NP;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) v[k] = pv[k];
+    {
+      const T* p = sx + ol + t * NP;
+      T w[NP];
+#pragma unroll
+      for (int k = 0; k < NP; ++k) w[k] = p[k];
+      trace(DP, w, dL);
+      uL = w[P];
+    }
+    if constexpr (!TWO) {
+      __syncthreads();
+      store_halo(sr, 0);
+      __syncthreads();
+    }
+    {
+      const T* p = sx + orr + t * NP;
+      T w[NP];
+#pragma unroll
+      for (int k = 0; k < NP; ++k) w[k] = p[k];
+      trace(D0, w, dR);
+      uR = w[0];
+    }
+    __syncthreads();  // the halos are read, the tile may be written
+    const T mo = half(1) * ra * half(2) * rb;
+    T* o = tile + el * NE + t * NP;
+    line(0, v, dL, uL, dR, uR, l0, r0, mo, [&](int i, T val) {
+      if (has) o[i] = val;
+    });
+  }
+  __syncthreads();
+
+  // ---- direction 1; the next direction's lines are on the way meanwhile
+  T dL, dR, uL, uR;
+  trace(DP, wl, dL);
+  trace(D0, wr, dR);
+  uL = wl[P];
+  uR = wr[0];
+  load_lines(m2 > 0 ? e - st2 : (per2 ? e + (N2 - 1) * st2 : e), m2 < N2 - 1 ? e + st2 : (per2 ? e - (N2 - 1) * st2 : e),
+             t, S2{}, wl, wr);
+  __builtin_amdgcn_sched_barrier(0);
+  {
+    T v[NP];
+    const T* pv = sx + el * NE + b1;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) v[k] = pv[k * NP];
+    const T mo = half(0) * ra * half(2) * rb;
+    T* o = tile + el * NE + b1;
+    line(1, v, dL, uL, dR, uR, l1, r1, mo, [&](int i, T val) {
+      if (has) o[i * NP] += val;
+    });
+  }
+  __syncthreads();
+
+  // ---- direction 2 (f is not loaded before: its registers made FP64 lines spill)
+  const int bz = el * NE + t;
+  constexpr int SZ = NP * NP;
+  T other[NP];
+  if constexpr (MODE == 1 || MODE == 3) {
+#pragma unroll
+    for (int k = 0; k < NP; ++k) other[k] = (f + g0)[bz + k * SZ];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  trace(DP, wl, dL);
+  trace(D0, wr, dR);
+  uL = wl[P];
+  uR = wr[0];
+  double acc = 0.0;
+  {
+    T v[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) v[k] = sx[bz + k * SZ];
+    const T mo = half(0) * ra * half(1) * rb;
+    const T* o = tile + bz;
+    line(2, v, dL, uL, dR, uR, l2, r2, mo, [&](int i, T c) {
+      const T val = o[i * SZ] + c;
+      if (!has) return;
+      if constexpr (MODE == 3) {
+        sx[bz + i * SZ] = other[i] - val;  // (only this thread reads or writes the line now)
+      } else {
+        (y + g0)[bz + i * SZ] = MODE == 1 ? other[i] - val : val;
+        if constexpr (MODE == 2) acc += (double)v[i] * (double)val;
+      }
+    });
+  }
+  if constexpr (MODE == 2) {
+    const double s = block_sum(acc, red);
+    if (tid == 0) ptr(ap->part)[blk] = s;
+  }
+  if constexpr (MODE == 3) {
+    // the transfer kernel's restriction passes on the residual; y is the coarse vector
+    constexpr int NEC = NPC * NPC * NPC;
+    __syncthreads();
+    xfer_pass<T, 3, NP, NPC, NE, 0, true, NPC>(sJx, sx, tile, ne);
+    __syncthreads();
+    xfer_pass<T, 3, NP, NPC, NE, 1, true, NPC>(sJx, tile, sx, ne);
+    __syncthreads();
+    xfer_pass<T, 3, NP, NPC, NE, 2, true, NPC>(sJx, sx, tile, ne);
+    __syncthreads();
+    for (int q = tid; q < ne * NEC; q += TH) {
+      const int ec = q / NEC;
+      (y + (int64_t)e0 * NEC)[q] = tile[ec * NE + q - ec * NEC];
+    }
+  }
+}
+
+// 2D.  Grids are small (256 elements of P = 16 fill a block per CU), so the length of one
+// thread's work is the time: a thread per node instead of one per line.  An element and
+// its four neighbours come to LDS by coalesced loads, a thread per line and side takes the
+// face terms (17 instead of 289 products in a row at P = 16), then every node adds up its
+// two rows, matrix and values from LDS.
+// Residual of 16x16 P = 16 FP64: 14.5 -> 5.3 us (a launch alone: 2-3 us).
+template <class T, int NP, int MODE, bool BATCH = false>
+__global__ void __launch_bounds__((apply_threads<NP, 2>()))
+    apply2_kernel(ApplyArgs<T> a0, BatchList<ApplyArgs<T>> bl, int ntot) {
+  constexpr int NE = NP * NP, EPB = apply_epb<NP, 2>(), TH = apply_threads<NP, 2>();
+  constexpr int P = NP - 1, NPC = (NP - 1) / 2 + 1, C = (EPB * NE + TH - 1) / TH;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* sx = reinterpret_cast<T*>(smem_raw);  // own elements, then left, right, below, above
+  __shared__ T sLs[NP * NP], sD[2 * NP], srho[NP];
+  __shared__ T sC[EPB * 2 * ECOEF_N];
+  __shared__ T sF[EPB * 4 * NP * 2];
+  __shared__ T sJx[MODE == 3 ? NP * NPC : 1];
+  __shared__ double red[16];
+  __shared__ __align__(16) int sargs_raw[BATCH ? sizeof(ApplyArgs<T>) / sizeof(int) : 1];
+  const ApplyArgs<T>* ap;
+  int blk = 0;
+  if constexpr (BATCH) {
+    const int b = xcd_block(ntot);
+    if (b < 0) return;
+    ApplyArgs<T>* sargs = reinterpret_cast<ApplyArgs<T>*>(sargs_raw);
+    blk = batch_pick(bl, b, sargs);
+    ap = sargs;
+  } else {
+    ap = &a0;
+  }
+  // every argument into scalar registers by one group of loads
+  const auto uni = [](int v) { return BATCH ? __builtin_amdgcn_readfirstlane(v) : v; };
+  const auto ptr = [](auto* q) { return BATCH ? sgpr_ptr(q) : q; };
+  const T *px = ptr(ap->x), *pf = ptr(ap->f), *pLs = ptr(ap->Ls), *pD = ptr(ap->D), *prho = ptr(ap->rho);
+  const T *pe0 = ptr(ap->ec[0]), *pe1 = ptr(ap->ec[1]), *pJ = ptr(ap->J);
+  T* py = ptr(ap->y);
+  const int* act = ptr(ap->active);
+  int n_elem = uni(ap->n_elem), nblk = uni(ap->nblk), N0 = uni(ap->N0), N1 = uni(ap->N1), per = uni(ap->per);
+  uint32_t mg0 = uni(ap->mg0);
+  if constexpr (!BATCH) {
+    asm volatile("" : "+s"(px), "+s"(pf), "+s"(pLs), "+s"(pD), "+s"(prho), "+s"(pe0), "+s"(pe1), "+s"(pJ), "+s"(py),
+                 "+s"(act), "+s"(n_elem), "+s"(nblk), "+s"(N0), "+s"(N1), "+s"(per), "+s"(mg0));
+    blk = xcd_block(nblk);
+    if (blk < 0) return;
+  }
+  using G = const __attribute__((address_space(1))) T;  // global memory
+  G *x = (G*)px, *f = (G*)pf, *ec0 = (G*)pe0, *ec1 = (G*)pe1, *gLs = (G*)pLs, *gD = (G*)pD, *grho = (G*)prho;
+  auto* y = (__attribute__((address_space(1))) T*)py;
+  if (act != nullptr && *(const __attribute__((address_space(1))) int*)act == 0) return;
+  const int e0 = uni(blk) * EPB, ne = imin(EPB, n_elem - e0), n = ne * NE;
+  const int tid = threadIdx.x;
+  const int64_t g0 = (int64_t)e0 * NE;
+  const bool per0 = per & 1, per1 = per & 2;
+  T so[C], sn[4][C], other[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int q = imin(tid + c * TH, n - 1), el = q / NE, l = q - el * NE;
+    const int e = e0 + el, m1 = div_by(e, N0, mg0), m0 = e - m1 * N0;
+    // neighbours: m -/+ 1, wrapped when periodic, the element itself (masked) at a Dirichlet end
+    const int nb[4] = {m0 > 0 ? e - 1 : (per0 ? e + N0 - 1 : e), m0 < N0 - 1 ? e + 1 : (per0 ? e - (N0 - 1) : e),
+                       m1 > 0 ? e - N0 : (per1 ? e + (N1 - 1) * N0 : e),
+                       m1 < N1 - 1 ? e + N0 : (per1 ? e - (N1 - 1) * N0 : e)};
+    so[c] = x[g0 + q];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) sn[s][c] = x[(int64_t)nb[s] * NE + l];
+    if constexpr (MODE == 1 || MODE == 3) other[c] = f[g0 + q];
+  }
+  for (int q = tid; q < NP * NP; q += TH) sLs[q] = gLs[q];
+  for (int q = tid; q < 2 * NP; q += TH) sD[q] = gD[q < NP ? q : P * NP + q - NP];
+  for (int q = tid; q < NP; q += TH) srho[q] = grho[q];
+  if constexpr (MODE == 3) {
+    G* J = (G*)pJ;
+    for (int q = tid; q < NP * NPC; q += TH) sJx[q] = J[q];
+  }
+  for (int q = tid; q < ne * 2 * ECOEF_N; q += TH) {
+    const int c = q % ECOEF_N, ed = q / ECOEF_N, e = e0 + ed / 2, m1 = div_by(e, N0, mg0);
+    sC[q] = ed & 1 ? ec1[m1 * ECOEF_N + c] : ec0[(e - m1 * N0) * ECOEF_N + c];
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int q = tid + c * TH;
+    if (q >= n) continue;
+    sx[q] = so[c];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) sx[(s + 1) * EPB * NE + q] = sn[s][c];
+  }
+  __syncthreads();
+  // face terms of line ln of element el along direction d at its left (right) end: the
+  // flux and the jump's weight
+  for (int q = tid; q < ne * 4 * NP; q += TH) {
+    const int el = q / (4 * NP), s = q / NP % 4, ln = q % NP, d = s >> 1, right = s & 1;
+    const int e = e0 + el, m1 = div_by(e, N0, mg0), m = d ? m1 : e - m1 * N0;
+    const T mask = (d ? per1 : per0) || (right ? m < (d ? N1 : N0) - 1 : m > 0) ? T(1) : T(0);
+    const int base = el * NE + (d ? ln : ln * NP), st = d ? NP : 1;
+    const T *v = sx + base, *w = sx + (s + 1) * EPB * NE + base;
+    const T *Dv = sD + (right ? NP : 0), *Dw = sD + (right ? 0 : NP);
+    T dv = 0, dw = 0;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      dv += Dv[k] * v[k * st];
+      dw += Dw[k] * w[k * st];
+    }
+    const T* c = sC + (el * 2 + d) * ECOEF_N;
+    const T j = v[right ? P * st : 0] - mask * w[right ? 0 : P * st];
+    const T cj = c[right ? E_CR : E_CL], cn = c[right ? E_CNR : E_CNL], cb = c[right ? E_BR : E_BL];
+    const T sg = right ? T(-1) : T(1);
+    sF[2 * q] = sg * cj * dv + sg * cn * (mask * dw) + cb * j;
+    sF[2 * q + 1] = sg * (cj * j);
+  }
+  __syncthreads();
+  double acc = 0.0;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int q = tid + c * TH;
+    if (q >= n) continue;
+    const int el = q / NE, l = q - el * NE, i1 = l / NP, i0 = l - i1 * NP;
+    const T* u = sx + el * NE;
+    const T *c0 = sC + el * 2 * ECOEF_N, *c1 = c0 + ECOEF_N;
+    const T *f0 = sF + 2 * (el * 4 * NP + i1), *f1 = sF + 2 * (el * 4 * NP + 2 * NP + i0);
+    T s0 = 0, s1 = 0;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      s0 += sLs[i0 * NP + k] * u[i1 * NP + k];
+      s1 += sLs[i1 * NP + k] * u[k * NP + i0];
+    }
+    T o0 = c0[E_TWO_DX] * s0 + f0[1] * sD[i0] + f0[2 * NP + 1] * sD[NP + i0];
+    T o1 = c1[E_TWO_DX] * s1 + f1[1] * sD[i1] + f1[2 * NP + 1] * sD[NP + i1];
+    if (i0 == 0) o0 += f0[0];
+    if (i0 == P) o0 += f0[2 * NP];
+    if (i1 == 0) o1 += f1[0];
+    if (i1 == P) o1 += f1[2 * NP];
+    const T val = mul_alone(c1[E_HALF_DX] * srho[i1], o0) + mul_alone(c0[E_HALF_DX] * srho[i0], o1);
+    if constexpr (MODE == 3) {
+      sx[EPB * NE + q] = other[c] - val;  // (the neighbours are no longer needed)
+    } else {
+      (y + g0)[q] = MODE == 1 ? other[c] - val : val;
+      if constexpr (MODE == 2) acc += (double)u[l] * (double)val;
+    }
+  }
+  if constexpr (MODE == 2) {
+    const double s = block_sum(acc, red);
+    if (tid == 0) ptr(ap->part)[blk] = s;
+  }
+  if constexpr (MODE == 3) {
+    // the transfer kernel's restriction passes on the residual; y is the coarse vector
+    constexpr int NEC = NPC * NPC;
+    T *r = sx + EPB * NE, *b = r + EPB * NE, *o = b + EPB * NE;
+    __syncthreads();
+    xfer_pass<T, 2, NP, NPC, NE, 0, true, NPC>(sJx, r, b, ne);
+    __syncthreads();
+    xfer_pass<T, 2, NP, NPC, NE, 1, true, NPC>(sJx, b, o, ne);
+    __syncthreads();
+    for (int q = tid; q < ne * NEC; q += TH) {
+      const int ec = q / NEC;
+      (y + (int64_t)e0 * NEC)[q] = o[ec * NE + q - ec * NEC];
+    }
+  }
+}
+
+template <class T, int DIM, int NP, int MODE, bool BATCH>
+void apply_go(const ApplyArgs<T>& a, const BatchList<ApplyArgs<T>>& bl, int nlog, hipStream_t s) {
+  const size_t shm = apply_shmem<T, DIM, NP>(BATCH || (a.per & 1));
+  const auto go = [&](auto kernel) {
+    if (shm > 65536)
+      (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+    hipLaunchKernelGGL(kernel, dim3(xcd_grid(nlog)), dim3(apply_threads<NP, DIM>()), shm, s, a, bl, nlog);
+  };
+  if constexpr (DIM == 3) go(apply_kernel<T, NP, MODE, BATCH>);
+  else go(apply2_kernel<T, NP, MODE, BATCH>);
+}
+
+// Blocks of one grid's apply: groups of apply_epb elements.
+template <int DIM, int NP>
+int apply_blocks(int n_elem) {
+  constexpr int EPB = apply_epb<NP, DIM>();
+  return (n_elem + EPB - 1) / EPB;
+}
+
+// The fused residual + restriction (mode 3) is built for coarse levels whose order
+// follows P_c = floor(P / 2).
+template <class T, int DIM, int NP>
+bool apply_mode3_ok(const LevelDev<T>& L) {
+  return !(DIM == 3 && NP > 17) && L.NPc == (NP - 1) / 2 + 1 && L.J != nullptr;
+}
+
+template <class T, int DIM, int NP, bool BATCH>
+int apply_mode(int mode, const ApplyArgs<T>& a, const BatchList<ApplyArgs<T>>& bl, int nlog, hipStream_t s) {
+  if (mode == 0) apply_go<T, DIM, NP, 0, BATCH>(a, bl, nlog, s);
+  else if (mode == 1) apply_go<T, DIM, NP, 1, BATCH>(a, bl, nlog, s);
+  else if (mode == 2) apply_go<T, DIM, NP, 2, BATCH>(a, bl, nlog, s);
+  else apply_go<T, DIM, NP, 3, BATCH>(a, bl, nlog, s);
+  return 0;
+}
+
+template <class T, int DIM, int NP>
+int apply_launch(const LevelDev<T>& L, int mode, const T* x, const T* f, T* y, double* part,
+                 int* nblk_out, hipStream_t s) {
+  const int nblk = apply_blocks<DIM, NP>(L.n_elem);
+  if (nblk_out) *nblk_out = nblk;
+  // fused residual + restriction: otherwise the caller runs the two steps
+  if (mode == 3 && !apply_mode3_ok<T, DIM, NP>(L)) return -4;
+  return apply_mode<T, DIM, NP, false>(mode, apply_args(L, x, f, y, part, nblk), BatchList<ApplyArgs<T>>{}, nblk, s);
+}
+
+// One launch over the applies of many grids (same NP and mode): ntot logical
+// blocks, grid g's apply_blocks in the range of bl.
+template <class T, int DIM, int NP>
+int apply_batch_launch(int mode, const BatchList<ApplyArgs<T>>& bl, int ntot, hipStream_t s) {
+  return apply_mode<T, DIM, NP, true>(mode, ApplyArgs<T>{}, bl, ntot, s);
+}
+
+}  // namespace dgmg

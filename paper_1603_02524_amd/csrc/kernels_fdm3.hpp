@@ -194,15 +194,6 @@ constexpr int fdm3_occupancy() {
   return imax(NA, NL) <= 9 ? 4 : (imax(NA, NL) <= 16 ? (sizeof(T) == 4 ? 4 : 3) : 2);
 }
 
-// Quotient by a divisor known to the host: m = ceil(2^32 / d) where the product
-// fits (every n up to n_max is then exact), 0 otherwise.
-inline uint32_t div_magic(int64_t n_max, int d) {
-  return n_max * d < (int64_t(1) << 32) && d > 1 ? (uint32_t)(((uint64_t(1) << 32) + d - 1) / d) : 0;
-}
-__device__ __forceinline__ int div_by(int n, int d, uint32_t m) {
-  return m ? (int)__umulhi((uint32_t)n, m) : (d == 1 ? n : n / d);
-}
-
 // Arguments of a launch, only what the kernel reads, the tables chosen by the host
 // for the sweep's normal: a block's start is a chain of scalar loads and scalar
 // arithmetic that every wave waits for, so both are kept short.

@@ -2298,6 +2298,12 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
         step({major, depthkey, s, i, 1}, BK_FDM, lv.dim, {nd, NA, NL},
              np[0] * ((np[1] + lay.K - 1) / lay.K) * np[2], std::move(fargs));
         out.back().pb = lay;
+        const int N[3] = {lv.dir[0].N, lv.dir[1].N, lv.dim == 3 ? lv.dir[2].N : 1};
+        if (combine3_fits<T>(lv.dim, lv.NP, lv.NO, nd, NA, NL, N, np[0], np[1], lay)) {
+          const Comb3Args<T> c3 = combine3_args(Lv, nd, NA, NL, (const T*)patch, u[l], np[0], np[1], np[2], lay, uz);
+          step({major, depthkey, s, i, 2}, BK_COMB, lv.dim, {lv.NP, 0}, c3.nblk, arg_bytes(c3));
+          continue;
+        }
         CombArgs<T> ca;
         ca.L = Lv;
         ca.buf = patch;
@@ -2557,7 +2563,8 @@ int run_launch_t(dgmg_batch* b, const dgmg_batch::Launch& ln, hipStream_t s) {
     case BK_APPLY: return Kern<T, DIM>::apply_batch(ln.t[0], ln.t[1], blist<ApplyArgs<T>>(b, ln), ln.ntot, s);
     case BK_FDM: return Kern<T, DIM>::fdm_batch(ln.t[0], ln.t[1], ln.t[2], blist<FdmArgs<T>>(b, ln),
                                                   blist<Fdm3Args<T>>(b, ln), ln.ntot, ln.pb, 0, s);
-    case BK_COMB: return Kern<T, DIM>::combine_batch(ln.t[0], ln.t[1], blist<CombArgs<T>>(b, ln), ln.ntot, s);
+    case BK_COMB: return Kern<T, DIM>::combine_batch(ln.t[0], ln.t[1], blist<CombArgs<T>>(b, ln), blist<Comb3Args<T>>(b, ln),
+                                                        ln.ntot, s);
     case BK_XFER:
       return Kern<T, DIM>::transfer_batch(ln.t[0], ln.t[1], ln.t[2] != 0, blist<XferArgs<T>>(b, ln), ln.ntot, s);
     case BK_COARSE:

@@ -221,10 +221,11 @@ int Kern<T, DIM>::fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>&
 }
 
 template <class T, int DIM>
-int Kern<T, DIM>::combine_batch(int NP, int maxc, const BatchList<CombArgs<T>>& bl, int ntot, hipStream_t s) {
+int Kern<T, DIM>::combine_batch(int NP, int maxc, const BatchList<CombArgs<T>>& bl,
+                                const BatchList<Comb3Args<T>>& bl3, int ntot, hipStream_t s) {
   switch (NP) {
 #define DGMG_CASE(N) \
-  case N: return combine_batch_launch<T, DIM, N>(maxc, bl, ntot, s);
+  case N: return combine_batch_launch<T, DIM, N>(maxc, bl, bl3, ntot, s);
     DGMG_NP_LIST(DGMG_CASE)
 #undef DGMG_CASE
     default: return -4;

@@ -867,13 +867,260 @@ int combine_blocks(int n_elem) {
   constexpr int EPB = combine_epb<NP, DIM>(), BPE = combine_bpe<NP, DIM>();
   return BPE > 1 ? n_elem * BPE : (n_elem + EPB - 1) / EPB;
 }
+// 3D, at most two covering patches per direction: a thread owns a line of nodes along one
+// direction C (1 or 2) of one element; the lanes run over directions 0 and B = 3 - C of a
+// layer of elements (equal index in direction C), whole blocks of lines.  What a node
+// needs in directions 0 and B (32-bit offsets, which candidates exist) is then worked out
+// once per line, and the covering patches in direction C are the same for the whole block:
+// their addresses are scalars, and where there is one no load is issued for a second.
+// C is the slower direction of the tiles, so that a wave's loads run through consecutive
+// rows; with the other choice a load took 45 cache accesses and the address unit bound the
+// kernel (32^3 P = 8 FP32: 165 us, now 133 us or 3.5 TB/s; 150 us for a thread per node with
+// table reads from LDS.  32^3 P = 4: 37 -> 24 us, 9x7x11 P = 12: 16 -> 11 us; FP64 16^3 P = 8
+// 24 us, 5.3 TB/s, either way).
+// Existing candidates are added in the same order either way (directions 2, 1, 0).
+template <class T>
+struct Comb3Args {
+  const T* buf = nullptr;
+  T* u = nullptr;
+  const int* active = nullptr;
+  int64_t psc = 0;  // elements from patch to patch along C
+  int c1 = 0;       // C is direction 1
+  int N0 = 1, NB = 1, NC = 1, per = 0, NO = 0, nd = -1;  // (per: bit 0 direction 0, 1 B, 2 C; nd: 0, 1 = B, 2 = C)
+  int ts = 0, psb = 0, ostb = 0, ostc = 0;               // tile; patches along B; positions of a tile
+  int K = 1, step = 0;
+  int eb = 0, ec = 0;                                    // element strides of the level vector along B and C
+  int nline = 0, bpl = 1, nblk = 0, assign = 0;          // lines and blocks of a layer
+  uint32_t mg0 = 0, mgb = 0;                             // divisions by N0 and bpl
+};
+constexpr int COMB3_THREADS = 256;
+
+template <class T>
+Comb3Args<T> combine3_args(const LevelDev<T>& L, int nd, int NA, int NL, const T* buf, T* u, int npx, int npy, int npz,
+                           const PatchBuf& pb, bool assign) {
+  Comb3Args<T> a;
+  const int l0 = nd == 0 ? NA : NL, l1 = nd == 1 ? NA : NL, l2 = nd == 2 ? NA : NL;
+  const int nsy = (npy + pb.K - 1) / pb.K;
+  const int64_t ps1 = (int64_t)l0 * ((pb.K - 1) * pb.step + l1) * l2 * npx, ps2 = ps1 * nsy;
+  const int ost1 = pb.swp ? l0 * l2 : l0, ost2 = pb.swp ? l0 : l0 * l1;
+  const int N1 = L.dir[1].N, N2 = L.dir[2].N;
+  const bool c1 = pb.swp && ps2 * npz * (int64_t)sizeof(T) < (int64_t(1) << 32) && ps2 * npz < (int64_t(1) << 31);
+  a.buf = buf;
+  a.u = u;
+  a.active = L.active;
+  a.c1 = c1 ? 1 : 0;
+  a.ts = (int)(ps1 / npx);
+  a.psc = c1 ? ps1 : ps2;
+  a.psb = (int)(c1 ? ps2 : ps1);
+  a.ostb = c1 ? ost2 : ost1;
+  a.ostc = c1 ? ost1 : ost2;
+  a.N0 = L.dir[0].N;
+  a.NB = c1 ? N2 : N1;
+  a.NC = c1 ? N1 : N2;
+  a.eb = c1 ? a.N0 * N1 : a.N0;
+  a.ec = c1 ? a.N0 : a.N0 * N1;
+  const int B = c1 ? 2 : 1, C = 3 - B;
+  a.per = (L.dir[0].periodic ? 1 : 0) | (L.dir[B].periodic ? 2 : 0) | (L.dir[C].periodic ? 4 : 0);
+  a.NO = L.NO;
+  a.nd = nd <= 0 ? nd : (nd == B ? 1 : 2);
+  a.K = pb.K;
+  a.step = pb.step;
+  a.nline = a.N0 * a.NB * L.NP * L.NP;
+  a.bpl = (a.nline + COMB3_THREADS - 1) / COMB3_THREADS;
+  a.nblk = a.bpl * a.NC;
+  a.assign = assign ? 1 : 0;
+  a.mg0 = div_magic((int64_t)a.N0 * a.NB, a.N0);
+  a.mgb = div_magic(a.nblk, a.bpl);
+  return a;
+}
 // Candidate slots per node and direction: three covering element-centred
 // patches in one direction only when 2 N_O > N_P.
 inline int combine_maxc(int NP, int NO) { return 2 * NO > NP ? 3 : 2; }
+// The offsets inside a layer of patches have to fit 32 bits (bytes), the lines an int; larger
+// grids and three candidates take combine_kernel.
+template <class T>
+bool combine3_fits(int dim, int NP, int NO, int nd, int NA, int NL, const int* N, int npx, int npy, const PatchBuf& pb) {
+  if (dim != 3 || combine_maxc(NP, NO) != 2) return false;
+  const int64_t l0 = nd == 0 ? NA : NL, l1 = nd == 1 ? NA : NL, l2 = nd == 2 ? NA : NL;
+  const int64_t layer = l0 * ((pb.K - 1) * (int64_t)pb.step + l1) * l2 * npx * ((npy + pb.K - 1) / pb.K);
+  const int64_t lines = (int64_t)N[0] * N[1] * N[2] * NP * NP;
+  return layer < (int64_t(1) << 31) && layer * (int64_t)sizeof(T) < (int64_t(1) << 32) && lines < (int64_t(1) << 31);
+}
+
+// BATCH: the arguments come from the work list bl (ntot logical blocks in all)
+template <class T, int NP, bool BATCH = false>
+__global__ void __launch_bounds__(COMB3_THREADS)
+    combine3_kernel(Comb3Args<T> a0, BatchList<Comb3Args<T>> bl, int ntot) {
+  constexpr int NLN = NP * NP, P = NP - 1;
+  constexpr int KC = imin(NP, 3);  // nodes of a line whose loads are issued together
+  __shared__ __align__(16) int sargs_raw[BATCH ? sizeof(Comb3Args<T>) / sizeof(int) : 1];
+  const Comb3Args<T>* ap;
+  int blk = 0;
+  if constexpr (BATCH) {
+    const int b = xcd_block(ntot);
+    if (b < 0) return;
+    Comb3Args<T>* sargs = reinterpret_cast<Comb3Args<T>*>(sargs_raw);
+    blk = batch_pick(bl, b, sargs);
+    ap = sargs;
+  } else {
+    ap = &a0;
+  }
+  // every argument into scalar registers by one group of loads
+  const auto uni = [](int v) { return BATCH ? __builtin_amdgcn_readfirstlane(v) : v; };
+  const auto ptr = [](auto* q) { return BATCH ? sgpr_ptr(q) : q; };
+  const T* pbuf = ptr(ap->buf);
+  T* pu = ptr(ap->u);
+  const int* act = ptr(ap->active);
+  int64_t psc = ap->psc;
+  if constexpr (BATCH) psc = (int64_t)(uint32_t)uni((int)psc) | ((int64_t)uni((int)(psc >> 32)) << 32);
+  int N0 = uni(ap->N0), NB = uni(ap->NB), NC = uni(ap->NC), per = uni(ap->per), NO = uni(ap->NO), nd = uni(ap->nd);
+  int ts = uni(ap->ts), psb = uni(ap->psb), ostb = uni(ap->ostb), ostc = uni(ap->ostc), K = uni(ap->K);
+  int step = uni(ap->step), eb = uni(ap->eb), ec = uni(ap->ec), c1 = uni(ap->c1);
+  int nline = uni(ap->nline), bpl = uni(ap->bpl), nblk = uni(ap->nblk), assign = uni(ap->assign);
+  uint32_t mg0 = uni(ap->mg0), mgb = uni(ap->mgb);
+  if constexpr (!BATCH) {
+    asm volatile("" : "+s"(pbuf), "+s"(pu), "+s"(act), "+s"(psc), "+s"(N0), "+s"(NB), "+s"(NC), "+s"(per), "+s"(NO),
+                 "+s"(nd), "+s"(ts), "+s"(psb), "+s"(ostb), "+s"(ostc));
+    asm volatile("" : "+s"(K), "+s"(step), "+s"(eb), "+s"(ec), "+s"(c1), "+s"(nline), "+s"(bpl), "+s"(nblk),
+                 "+s"(assign), "+s"(mg0), "+s"(mgb));
+    blk = xcd_block(nblk);
+    if (blk < 0) return;
+  }
+  using G = const __attribute__((address_space(1))) T;  // global memory
+  using GC = const __attribute__((address_space(1))) char;
+  if (act != nullptr && *(const __attribute__((address_space(1))) int*)act == 0) return;
+  blk = uni(blk);
+  const int mc = uni(div_by(blk, bpl, mgb));
+  const int ln = (blk - mc * bpl) * COMB3_THREADS + (int)threadIdx.x;
+  if (ln >= nline) return;
+  const int el = ln / NLN, t = ln - el * NLN, i = t % NP, j = t / NP;
+  const int mb = div_by(el, N0, mg0), m0 = el - mb * N0;
+  // covering patches of index i of element m: (p, o) and, if two, (p2, o2), in order
+  const auto cover = [&](int m, int N, bool wrap, bool face, int i, int& p, int& o, int& p2, int& o2) {
+    bool two;
+    if (face) {  // faces m (position P + i, i < P) and m + 1 (position i - 1, i >= 1)
+      const int q = wrap && m + 1 == N ? 0 : m + 1;
+      two = i >= 1 && i < P;
+      p = i < P ? m : q;
+      o = i < P ? P + i : i - 1;
+      p2 = q;
+      o2 = i - 1;
+    } else {  // element-centred patches m - 1, m, m + 1
+      const bool lo = i < NO && (wrap || m > 0), hi = i >= NP - NO && (wrap || m < N - 1);
+      two = lo || hi;
+      p = lo ? (m > 0 ? m - 1 : N - 1) : m;
+      o = lo ? NP + NO + i : i + NO;
+      p2 = lo ? m : (m < N - 1 ? m + 1 : 0);
+      o2 = lo ? i + NO : i - NP + NO;
+    }
+    return two;
+  };
+  const int sh = __builtin_ctz(K);
+  // strips (along direction 1): patches of one strip meet in one plane of its summed tile
+  const auto strip = [&](bool two, int& p, int& o, int& p2, int& o2) {
+    o += (p & (K - 1)) * step;
+    o2 += (p2 & (K - 1)) * step;
+    p >>= sh;
+    p2 >>= sh;
+    return two && !(p == p2 && o == o2);
+  };
+  int pa, oa, pb, ob;
+  const bool x2 = cover(m0, N0, per & 1, nd == 0, i, pa, oa, pb, ob);
+  const uint32_t ax = (uint32_t)(pa * ts + oa) * (uint32_t)sizeof(T), bx = (uint32_t)(pb * ts + ob) * (uint32_t)sizeof(T);
+  bool b2 = cover(mb, NB, per & 2, nd == 1, j, pa, oa, pb, ob);
+  if (!c1) b2 = strip(b2, pa, oa, pb, ob);
+  const uint32_t ab = (uint32_t)(pa * psb + oa * ostb) * (uint32_t)sizeof(T);
+  const uint32_t bb = (uint32_t)(pb * psb + ob * ostb) * (uint32_t)sizeof(T);
+  const bool xb = x2 && b2;
+  const int ub = c1 ? NP * NP : NP, uc = c1 ? NP : NP * NP;
+  auto* u = (__attribute__((address_space(1))) T*)pu + ((int64_t)m0 + (int64_t)mb * eb + (int64_t)mc * ec) * (NP * NLN) +
+            (i + j * ub);
+#pragma unroll
+  for (int k0 = 0; k0 < NP; k0 += KC) {
+    constexpr int LAST = (NP - 1) / KC * KC;
+    const int kn = k0 == LAST ? NP - LAST : KC;
+    T v[KC][2][4], old[KC];
+    bool two[KC], any = false;
+    int64_t z[KC][2];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      if (c >= kn) continue;
+      int p, o, p2, o2;
+      two[c] = cover(mc, NC, per & 4, nd == 2, k0 + c, p, o, p2, o2);
+      if (c1) two[c] = strip(two[c], p, o, p2, o2);
+      any = any || two[c];
+      z[c][0] = p * psc + (int64_t)o * ostc;
+      z[c][1] = two[c] ? p2 * psc + (int64_t)o2 * ostc : z[c][0];  // (repeated and unused where there is one)
+    }
+    const auto load = [&](int h, int q, uint32_t off) {
+#pragma unroll
+      for (int c = 0; c < KC; ++c)
+        if (c < kn) v[c][h][q] = *(G*)((GC*)((G*)pbuf + z[c][h]) + off);
+    };
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[c][h][q] = T(0);
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+      if (c < kn) old[c] = assign ? T(0) : u[(k0 + c) * uc];
+    load(0, 0, ab + ax);
+    if (any) load(1, 0, ab + ax);
+    if (x2) {
+      load(0, 1, ab + bx);
+      if (any) load(1, 1, ab + bx);
+    }
+    if (b2) {
+      load(0, 2, bb + ax);
+      if (any) load(1, 2, bb + ax);
+    }
+    if (xb) {
+      load(0, 3, bb + bx);
+      if (any) load(1, 3, bb + bx);
+    }
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      if (c >= kn) continue;
+      T s;
+      // (absent candidates are 0 and change nothing)
+      if (c1) {  // C = 1: directions 2 (B), 1 (C), 0
+        s = v[c][0][0] + v[c][0][1];
+        if (two[c]) s = (s + v[c][1][0]) + v[c][1][1];
+        s = (s + v[c][0][2]) + v[c][0][3];
+        if (two[c]) s = (s + v[c][1][2]) + v[c][1][3];
+      } else {   // C = 2: directions 2 (C), 1 (B), 0
+        s = ((v[c][0][0] + v[c][0][1]) + v[c][0][2]) + v[c][0][3];
+        if (two[c]) s = (((s + v[c][1][0]) + v[c][1][1]) + v[c][1][2]) + v[c][1][3];
+      }
+      u[(k0 + c) * uc] = assign ? s : old[c] + s;
+    }
+  }
+}
+
+template <class T, int NP>
+int combine3_launch(const Comb3Args<T>& a, hipStream_t s) {
+  hipLaunchKernelGGL((combine3_kernel<T, NP, false>), dim3(xcd_grid(a.nblk)), dim3(COMB3_THREADS), 0, s, a,
+                     BatchList<Comb3Args<T>>{}, a.nblk);
+  return 0;
+}
+// One launch over the overlap summations of many grids (ntot logical blocks in all).
+template <class T, int NP>
+int combine3_batch_launch(const BatchList<Comb3Args<T>>& bl, int ntot, hipStream_t s) {
+  hipLaunchKernelGGL((combine3_kernel<T, NP, true>), dim3(xcd_grid(ntot)), dim3(COMB3_THREADS), 0, s, Comb3Args<T>{}, bl,
+                     ntot);
+  return 0;
+}
 
 template <class T, int DIM, int NP>
 int combine_launch_t(const LevelDev<T>& L, int nd, int NA, int NL, const T* buf, T* u, int npx,
                      int npy, int npz, const PatchBuf& pb, bool assign, hipStream_t s) {
+  if constexpr (DIM == 3) {
+    const int N[3] = {L.dir[0].N, L.dir[1].N, L.dir[2].N};
+    if (combine3_fits<T>(3, NP, L.NO, nd, NA, NL, N, npx, npy, pb))
+      return combine3_launch<T, NP>(combine3_args(L, nd, NA, NL, buf, u, npx, npy, npz, pb, assign), s);
+  }
   CombArgs<T> a;
   a.L = L;
   a.buf = buf;
@@ -899,7 +1146,10 @@ int combine_launch_t(const LevelDev<T>& L, int nd, int NA, int NL, const T* buf,
 // One launch over the overlap summations of many grids (same NP and candidate
 // slots maxc): ntot logical blocks, grid g's combine_blocks in the range of bl.
 template <class T, int DIM, int NP>
-int combine_batch_launch(int maxc, const BatchList<CombArgs<T>>& bl, int ntot, hipStream_t s) {
+int combine_batch_launch(int maxc, const BatchList<CombArgs<T>>& bl, const BatchList<Comb3Args<T>>& bl3, int ntot,
+                         hipStream_t s) {
+  if constexpr (DIM == 3)
+    if (maxc == 0) return combine3_batch_launch<T, NP>(bl3, ntot, s);  // grids that combine3_fits
   if (maxc == 3)
     hipLaunchKernelGGL((combine_kernel<T, DIM, NP, 3, true>), dim3(xcd_grid(ntot)), dim3(256), 0, s, CombArgs<T>{},
                        bl, ntot);
@@ -1093,7 +1343,9 @@ struct Kern {
   // (arguments: bl in 2D, bl3 in 3D)
   static int fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>& bl, const BatchList<Fdm3Args<T>>& bl3,
                        int ntot, const PatchBuf& pb, int waves, hipStream_t s);
-  static int combine_batch(int NP, int maxc, const BatchList<CombArgs<T>>& bl, int ntot, hipStream_t s);
+  // maxc 0: the grids take combine3_kernel (arguments bl3), else combine_kernel (bl)
+  static int combine_batch(int NP, int maxc, const BatchList<CombArgs<T>>& bl, const BatchList<Comb3Args<T>>& bl3,
+                           int ntot, hipStream_t s);
   static int transfer_batch(int NPF, int NPC, bool restrict_, const BatchList<XferArgs<T>>& bl, int ntot,
                             hipStream_t s);
   static bool fdm_supported(int NA, int NL);

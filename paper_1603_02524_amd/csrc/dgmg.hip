@@ -2312,7 +2312,8 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
           fa.npy = np[1];
           fargs = arg_bytes(fa);
         }
-        step({major, depthkey, s, i, 1}, BK_FDM, lv.dim, {nd, NA, NL},
+        step({major, depthkey, s, i, 1}, BK_FDM, lv.dim,
+             {nd, NA, NL, lv.dim == 2 && fdm2_fits<T>(NA, NL, np[0] * np[1]) ? 1 : 0},
              np[0] * ((np[1] + lay.K - 1) / lay.K) * np[2], std::move(fargs));
         out.back().pb = lay;
         const int N[3] = {lv.dir[0].N, lv.dir[1].N, lv.dim == 3 ? lv.dir[2].N : 1};
@@ -2598,7 +2599,7 @@ int run_launch_t(dgmg_batch* b, const dgmg_batch::Launch& ln, hipStream_t s) {
   switch (ln.kind) {
     case BK_APPLY: return Kern<T, DIM>::apply_batch(ln.t[0], ln.t[1], blist<ApplyArgs<T>>(b, ln), ln.ntot, s);
     case BK_FDM: return Kern<T, DIM>::fdm_batch(ln.t[0], ln.t[1], ln.t[2], blist<FdmArgs<T>>(b, ln),
-                                                  blist<Fdm3Args<T>>(b, ln), ln.ntot, ln.pb, 0, s);
+                                                  blist<Fdm3Args<T>>(b, ln), ln.ntot, ln.pb, ln.t[3] != 0, s);
     case BK_COMB: return Kern<T, DIM>::combine_batch(ln.t[0], ln.t[1], blist<CombArgs<T>>(b, ln), blist<Comb3Args<T>>(b, ln),
                                                         ln.ntot, s);
     case BK_XFER:

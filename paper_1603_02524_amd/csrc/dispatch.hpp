@@ -123,8 +123,12 @@ int Kern<T, DIM>::fdm(const LevelDev<T>& L, int nd, int NA, int NL, const T* r, 
       return whole ? fdm_big_launch<T, A, B>(L, nd, r, out, npx, npy, npz, s) : -4;            \
     else if constexpr (DIM == 3)                                                               \
       return fdm3_go<T, A, B, false>(nd, a3, BatchList<Fdm3Args<T>>{}, a3.nblk, s);            \
-    else                                                                                       \
+    else {                                                                                     \
+      if constexpr (A * B <= FDM2_NODES)                                                       \
+        if (fdm2_fits<T>(A, B, npx * npy))                                                     \
+          return fdm2_go<T, A, B, false>(nd, a2, BatchList<FdmArgs<T>>{}, npx * npy, s);       \
       return fdm_go<T, DIM, A, B, false>(nd, a2, BatchList<FdmArgs<T>>{}, npx * npy, waves, s); \
+    }                                                                                          \
   }
   DGMG_FDM_LIST(DGMG_CASE)
   if constexpr (DIM == 2) {
@@ -201,7 +205,7 @@ int Kern<T, DIM>::apply_batch(int NP, int mode, const BatchList<ApplyArgs<T>>& b
 
 template <class T, int DIM>
 int Kern<T, DIM>::fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>& bl,
-                            const BatchList<Fdm3Args<T>>& bl3, int ntot, const PatchBuf& pb, int waves,
+                            const BatchList<Fdm3Args<T>>& bl3, int ntot, const PatchBuf& pb, bool few,
                             hipStream_t s) {
   Fdm3Args<T> a3;
   a3.K = pb.K;
@@ -212,8 +216,11 @@ int Kern<T, DIM>::fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>&
       return -4;                                                                 \
     else if constexpr (DIM == 3)                                                 \
       return fdm3_go<T, A, B, true>(nd, a3, bl3, ntot, s);                       \
-    else                                                                         \
-      return fdm_go<T, DIM, A, B, true>(nd, FdmArgs<T>{}, bl, ntot, waves, s);   \
+    else {                                                                       \
+      if constexpr (A * B <= FDM2_NODES)                                         \
+        if (few) return fdm2_go<T, A, B, true>(nd, FdmArgs<T>{}, bl, ntot, s);   \
+      return fdm_go<T, DIM, A, B, true>(nd, FdmArgs<T>{}, bl, ntot, 0, s);       \
+    }                                                                            \
   }
   DGMG_FDM_LIST(DGMG_CASE)
 #undef DGMG_CASE

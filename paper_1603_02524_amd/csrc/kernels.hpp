@@ -653,6 +653,152 @@ void fdm_launch_nd(const FdmArgs<T>& a, const BatchList<FdmArgs<T>>& bl, int nlo
   hipLaunchKernelGGL((fdm_kernel<T, DIM, NA, NL, ND, BATCH>), dim3(xcd_grid(nlog)), dim3(th), shm, s, a, bl, nlog);
 }
 
+// The same solve for sweeps of few patches, where one patch's chain of operations is the
+// time: a thread per node of the tile (or a few), matrices and tile in LDS, four passes of
+// one product row each.  256 patches, FP64: 23 x 23 10.4 -> 7.0 us, 9 x 9 6.3 -> 2.9 us
+// (a launch alone: 2 us).  Its LDS reads (two per product) bound it when the GPU is full,
+// where the matrix cores of fdm_kernel win: 1024 patches of 23 x 23 11.7 against 19.2 us.
+// The two meet at 484 (FP64) and 961 (FP32) patches of 23 x 23, 480 of 24 x 19, 1100 and
+// 2300 of 13 x 13, beyond 4096 of 9 x 9: at FDM2_BYTES of tiles or above.
+constexpr int64_t FDM2_BYTES = 3 << 19;
+constexpr int FDM2_NODES = 800;  // largest tile (a thread takes at most two nodes)
+template <int NA, int NL, int ND>
+constexpr int fdm2_threads() {
+  return imin(512, round64((ND == 0 ? NA : NL) * (ND == 1 ? NA : NL)));
+}
+template <class T, int NA, int NL, int ND, bool BATCH = false>
+__global__ void __launch_bounds__((fdm2_threads<NA, NL, ND>()))
+    fdm2_kernel(FdmArgs<T> a0, BatchList<FdmArgs<T>> bl, int ntot) {
+  constexpr int L0 = ND == 0 ? NA : NL, L1 = ND == 1 ? NA : NL, N = L0 * L1, TH = fdm2_threads<NA, NL, ND>();
+  constexpr int P0 = L0 | 1, P1 = L1 | 1, C = (N + TH - 1) / TH;  // odd pitches: rows and columns on distinct banks
+  __shared__ T S0[L0 * P0], S1[L1 * P1], A[L1 * P0], B[L1 * P0], sl[L0 + L1], sw[L0 + L1];
+  __shared__ __align__(16) int sargs_raw[BATCH ? sizeof(FdmArgs<T>) / sizeof(int) : 1];
+  const FdmArgs<T>* ap;
+  int pid = 0;
+  if constexpr (BATCH) {
+    const int b = xcd_block(ntot);
+    if (b < 0) return;
+    FdmArgs<T>* sargs = reinterpret_cast<FdmArgs<T>*>(sargs_raw);
+    pid = batch_pick(bl, b, sargs);
+    ap = sargs;
+  } else {
+    ap = &a0;
+  }
+  // every argument into scalar registers by one group of loads
+  const auto uni = [](int v) { return BATCH ? __builtin_amdgcn_readfirstlane(v) : v; };
+  const auto ptr = [](auto* q) { return BATCH ? sgpr_ptr(q) : q; };
+  const DirDev<T>&d0 = ap->L.dir[0], &d1 = ap->L.dir[1];
+  const T *pS0 = ptr(ND == 0 ? d0.S_fc : d0.S_ec), *pS1 = ptr(ND == 1 ? d1.S_fc : d1.S_ec);
+  const T *pl0 = ptr(ND == 0 ? d0.lam_fc : d0.lam_ec), *pl1 = ptr(ND == 1 ? d1.lam_fc : d1.lam_ec);
+  const T *pw0 = ptr(ND == 0 ? d0.w_fc : d0.w_ec), *pw1 = ptr(ND == 1 ? d1.w_fc : d1.w_ec);
+  const int *pg0 = ptr(ND == 0 ? d0.goff_fc : d0.goff_ec), *pg1 = ptr(ND == 1 ? d1.goff_fc : d1.goff_ec);
+  const T* pr = ptr(ap->r);
+  T* po = ptr(ap->out);
+  const int* act = ptr(ap->L.active);
+  int npx = uni(ap->npx), npy = uni(ap->npy), st0 = uni(ap->lat.start[0]), st1 = uni(ap->lat.start[1]);
+  int sr0 = uni(ap->lat.stride[0]), sr1 = uni(ap->lat.stride[1]);
+  if constexpr (!BATCH) {
+    asm volatile("" : "+s"(pS0), "+s"(pS1), "+s"(pl0), "+s"(pl1), "+s"(pw0), "+s"(pw1), "+s"(pg0), "+s"(pg1), "+s"(pr),
+                 "+s"(po), "+s"(act), "+s"(npx), "+s"(npy), "+s"(st0));
+    asm volatile("" : "+s"(st1), "+s"(sr0), "+s"(sr1));
+    pid = xcd_block(npx * npy);
+    if (pid < 0) return;
+  }
+  using G = const __attribute__((address_space(1))) T;  // global memory
+  using GI = const __attribute__((address_space(1))) int;
+  if (act != nullptr && *(GI*)act == 0) return;
+  pid = uni(pid);
+  const int tid = threadIdx.x, p0 = st0 + sr0 * (pid % npx), p1 = st1 + sr1 * (pid / npx);
+  G *gS0 = (G*)pS0 + (int64_t)p0 * L0 * L0, *gS1 = (G*)pS1 + (int64_t)p1 * L1 * L1, *r = (G*)pr;
+  GI *g0 = (GI*)pg0 + p0 * L0, *g1 = (GI*)pg1 + p1 * L1;
+  // nodes q = tid + c TH: position (x, y); positions outside a Dirichlet domain read r[0] and take 0
+  int x[C], y[C], off[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int q = imin(tid + c * TH, N - 1);
+    y[c] = q / L0;
+    x[c] = q - y[c] * L0;
+    const int a = g0[x[c]], b = g1[y[c]];
+    off[c] = (a | b) < 0 ? -1 : a + b;
+  }
+  constexpr int M0 = (L0 * L0 + TH - 1) / TH, M1 = (L1 * L1 + TH - 1) / TH;
+  T m0[M0], m1[M1];
+#pragma unroll
+  for (int c = 0; c < M0; ++c) m0[c] = gS0[imin(tid + c * TH, L0 * L0 - 1)];
+#pragma unroll
+  for (int c = 0; c < M1; ++c) m1[c] = gS1[imin(tid + c * TH, L1 * L1 - 1)];
+  for (int q = tid; q < L0 + L1; q += TH) {
+    const bool f = q < L0;
+    const int64_t at = f ? (int64_t)p0 * L0 + q : (int64_t)p1 * L1 + (q - L0);
+    sl[q] = f ? ((G*)pl0)[at] : ((G*)pl1)[at];
+    sw[q] = f ? ((G*)pw0)[at] : ((G*)pw1)[at];
+  }
+  T v[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) v[c] = r[off[c] < 0 ? 0 : off[c]];
+#pragma unroll
+  for (int c = 0; c < M0; ++c) {
+    const int q = tid + c * TH;
+    if (q < L0 * L0) S0[q / L0 * P0 + q % L0] = m0[c];
+  }
+#pragma unroll
+  for (int c = 0; c < M1; ++c) {
+    const int q = tid + c * TH;
+    if (q < L1 * L1) S1[q / L1 * P1 + q % L1] = m1[c];
+  }
+  const auto each = [&](auto f) {
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      if (c + 1 < C || N % TH == 0 || tid + c * TH < N) f(c, x[c], y[c]);
+  };
+  each([&](int c, int i, int j) { A[j * P0 + i] = off[c] < 0 ? T(0) : v[c]; });
+  __syncthreads();
+  each([&](int, int i, int j) {
+    T s = 0;
+#pragma unroll
+    for (int k = 0; k < L0; ++k) s += S0[k * P0 + i] * A[j * P0 + k];
+    B[j * P0 + i] = s;
+  });
+  __syncthreads();
+  each([&](int, int i, int j) {
+    T s = 0;
+#pragma unroll
+    for (int k = 0; k < L1; ++k) s += S1[k * P1 + j] * B[k * P0 + i];
+    A[j * P0 + i] = div_nr(s, sl[i] + sl[L0 + j]);
+  });
+  __syncthreads();
+  each([&](int, int i, int j) {
+    T s = 0;
+#pragma unroll
+    for (int k = 0; k < L1; ++k) s += S1[j * P1 + k] * A[k * P0 + i];
+    B[j * P0 + i] = s;
+  });
+  __syncthreads();
+  auto* out = (__attribute__((address_space(1))) T*)po + (int64_t)pid * N;
+  each([&](int, int i, int j) {
+    T s = 0;
+#pragma unroll
+    for (int k = 0; k < L0; ++k) s += S0[i * P0 + k] * B[j * P0 + k];
+    out[j * L0 + i] = (sw[i] * sw[L0 + j]) * s;
+  });
+}
+// The form of a grid's 2D sweep (patches: of the grid, also when grids share a launch, so
+// that a batch gives what its grids give alone).
+template <class T>
+bool fdm2_fits(int NA, int NL, int patches) {
+  return NA * NL <= FDM2_NODES && (int64_t)patches * NA * NL * (int64_t)sizeof(T) <= FDM2_BYTES;
+}
+
+template <class T, int NA, int NL, bool BATCH>
+int fdm2_go(int nd, const FdmArgs<T>& a, const BatchList<FdmArgs<T>>& bl, int nlog, hipStream_t s) {
+  const auto go = [&](auto kernel, int th) { hipLaunchKernelGGL(kernel, dim3(xcd_grid(nlog)), dim3(th), 0, s, a, bl, nlog); };
+  if (nd == 0) go(fdm2_kernel<T, NA, NL, 0, BATCH>, fdm2_threads<NA, NL, 0>());
+  else if (nd == 1) go(fdm2_kernel<T, NA, NL, 1, BATCH>, fdm2_threads<NA, NL, 1>());
+  else if constexpr (NA == NL) go(fdm2_kernel<T, NA, NL, -1, BATCH>, fdm2_threads<NA, NL, -1>());
+  else return -4;
+  return 0;
+}
+
 // waves: wavefronts per block (1 .. 8; 0 = default), the shape the autotuner picks.
 template <class T, int DIM, int NA, int NL, bool BATCH>
 int fdm_go(int nd, const FdmArgs<T>& a, const BatchList<FdmArgs<T>>& bl, int nlog, int waves, hipStream_t s) {
@@ -1342,7 +1488,7 @@ struct Kern {
   // pb: the longest strip of the launch's grids
   // (arguments: bl in 2D, bl3 in 3D)
   static int fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>& bl, const BatchList<Fdm3Args<T>>& bl3,
-                       int ntot, const PatchBuf& pb, int waves, hipStream_t s);
+                       int ntot, const PatchBuf& pb, bool few, hipStream_t s);
   // maxc 0: the grids take combine3_kernel (arguments bl3), else combine_kernel (bl)
   static int combine_batch(int NP, int maxc, const BatchList<CombArgs<T>>& bl, const BatchList<Comb3Args<T>>& bl3,
                            int ntot, hipStream_t s);

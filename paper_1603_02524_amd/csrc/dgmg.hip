@@ -2271,6 +2271,9 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
   auto blocks_apply = [&](const LevelDev<T>& Lv) {
     return Lv.dim == 3 ? Kern<T, 3>::apply_blocks_of(Lv.NP, Lv.n_elem) : Kern<T, 2>::apply_blocks_of(Lv.NP, Lv.n_elem);
   };
+  auto lines = [&](const LevelDev<T>& Lv) {
+    return (Lv.dim == 3 ? Kern<T, 3>::apply_in_lines(Lv.NP, Lv.n_elem) : Kern<T, 2>::apply_in_lines(Lv.NP, Lv.n_elem)) ? 1 : 0;
+  };
   // one smoothing call: steps s, sweeps i (EA: one, FA: one per direction);
   // keys {major, depthkey, s, i, sub-step}; depthkey is the level's order, falling on the
   // way down and rising on the way up, not its depth: the P = 4 level of a P = 8 grid then
@@ -2294,7 +2297,7 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
         }
         if (!uz) {
           ApplyArgs<T> a = apply_args<T>(Lv, u[l], f[l], rl, nullptr, blocks_apply(Lv));
-          step({major, depthkey, s, i, 0}, BK_APPLY, lv.dim, {lv.NP, 1}, a.nblk, arg_bytes(a));
+          step({major, depthkey, s, i, 0}, BK_APPLY, lv.dim, {lv.NP, 1, lines(Lv)}, a.nblk, arg_bytes(a));
         }
         int np[3], NA, NL;
         sweep_shape(lv, nd, np, NA, NL);
@@ -2380,10 +2383,10 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
       fnstep({1, k, 1000, 0, 0}, [h, l, ul, fl, rl, fc]() { return k_residual_restrict<T>(h, l, ul, fl, rl, fc); });
     } else if (m3) {
       ApplyArgs<T> a = apply_args<T>(Lv, u[l], f[l], f[l - 1], nullptr, blocks_apply(Lv));
-      step({1, k, 1000, 0, 0}, BK_APPLY, lv.dim, {lv.NP, 3}, a.nblk, arg_bytes(a));
+      step({1, k, 1000, 0, 0}, BK_APPLY, lv.dim, {lv.NP, 3, lines(Lv)}, a.nblk, arg_bytes(a));
     } else {
       ApplyArgs<T> a = apply_args<T>(Lv, u[l], f[l], rl, nullptr, blocks_apply(Lv));
-      step({1, k, 1000, 0, 0}, BK_APPLY, lv.dim, {lv.NP, 1}, a.nblk, arg_bytes(a));
+      step({1, k, 1000, 0, 0}, BK_APPLY, lv.dim, {lv.NP, 1, lines(Lv)}, a.nblk, arg_bytes(a));
       XferArgs<T> x = xfer_args(Lv, rl, f[l - 1]);
       step({1, k, 1000, 0, 1}, BK_XFER, lv.dim, {lv.NP, lv.NPc, 1}, xfer_blocks(Lv), arg_bytes(x));
     }
@@ -2476,6 +2479,8 @@ int batch_plan(dgmg_batch* b, bool fill) {
     st.f32 = 0;
     st.t[0] = Lt.NP;
     st.t[1] = 2;
+    st.t[2] = (Lt.dim == 3 ? Kern<double, 3>::apply_in_lines(Lt.NP, Lt.n_elem)
+                           : Kern<double, 2>::apply_in_lines(Lt.NP, Lt.n_elem)) ? 1 : 0;
     st.grid = gi;
     st.nblk = a.nblk;
     st.args = arg_bytes(a);
@@ -2597,7 +2602,7 @@ int run_pcg(dgmg_batch* b, const dgmg_batch::Launch& ln, hipStream_t s, bool fir
 template <class T, int DIM>
 int run_launch_t(dgmg_batch* b, const dgmg_batch::Launch& ln, hipStream_t s) {
   switch (ln.kind) {
-    case BK_APPLY: return Kern<T, DIM>::apply_batch(ln.t[0], ln.t[1], blist<ApplyArgs<T>>(b, ln), ln.ntot, s);
+    case BK_APPLY: return Kern<T, DIM>::apply_batch(ln.t[0], ln.t[1], ln.t[2] != 0, blist<ApplyArgs<T>>(b, ln), ln.ntot, s);
     case BK_FDM: return Kern<T, DIM>::fdm_batch(ln.t[0], ln.t[1], ln.t[2], blist<FdmArgs<T>>(b, ln),
                                                   blist<Fdm3Args<T>>(b, ln), ln.ntot, ln.pb, ln.t[3] != 0, s);
     case BK_COMB: return Kern<T, DIM>::combine_batch(ln.t[0], ln.t[1], blist<CombArgs<T>>(b, ln), blist<Comb3Args<T>>(b, ln),

@@ -148,7 +148,7 @@ template <class T, int DIM>
 int Kern<T, DIM>::apply_blocks_of(int NP, int n_elem) {
   switch (NP) {
 #define DGMG_CASE(N) \
-  case N: return (DIM == 3 && N == BIG_NP) ? -4 : apply_blocks<DIM, N>(n_elem);
+  case N: return (DIM == 3 && N == BIG_NP) ? -4 : apply_blocks<T, DIM, N>(n_elem);
     DGMG_NP_LIST(DGMG_CASE)
 #undef DGMG_CASE
     default: return -4;
@@ -178,6 +178,17 @@ int Kern<T, DIM>::xfer_blocks_of(int NPF, int n_elem) {
 }
 
 template <class T, int DIM>
+bool Kern<T, DIM>::apply_in_lines(int NP, int n_elem) {
+  switch (NP) {
+#define DGMG_CASE(N) \
+  case N: return apply_lines<T, DIM, N>(n_elem);
+    DGMG_NP_LIST(DGMG_CASE)
+#undef DGMG_CASE
+    default: return false;
+  }
+}
+
+template <class T, int DIM>
 bool Kern<T, DIM>::mode3_ok(const LevelDev<T>& L) {
   switch (L.NP) {
 #define DGMG_CASE(N) \
@@ -189,14 +200,14 @@ bool Kern<T, DIM>::mode3_ok(const LevelDev<T>& L) {
 }
 
 template <class T, int DIM>
-int Kern<T, DIM>::apply_batch(int NP, int mode, const BatchList<ApplyArgs<T>>& bl, int ntot, hipStream_t s) {
+int Kern<T, DIM>::apply_batch(int NP, int mode, bool lines, const BatchList<ApplyArgs<T>>& bl, int ntot, hipStream_t s) {
   switch (NP) {
 #define DGMG_CASE(N)                                                   \
   case N:                                                              \
     if constexpr (DIM == 3 && N == BIG_NP)                             \
       return -4;                                                       \
     else                                                               \
-      return apply_batch_launch<T, DIM, N>(mode, bl, ntot, s);
+      return apply_batch_launch<T, DIM, N>(mode, lines, bl, ntot, s);
     DGMG_NP_LIST(DGMG_CASE)
 #undef DGMG_CASE
     default: return -4;

@@ -1595,8 +1595,9 @@ struct Kern {
   static int apply_blocks_of(int NP, int n_elem);
   static int combine_blocks_of(int NP, int n_elem);
   static int xfer_blocks_of(int NPF, int n_elem);
+  static bool apply_in_lines(int NP, int n_elem);  // the form of a grid's apply
   static bool mode3_ok(const LevelDev<T>& L);
-  static int apply_batch(int NP, int mode, const BatchList<ApplyArgs<T>>& bl, int ntot, hipStream_t s);
+  static int apply_batch(int NP, int mode, bool lines, const BatchList<ApplyArgs<T>>& bl, int ntot, hipStream_t s);
   // pb: the longest strip of the launch's grids
   // (arguments: bl in 2D, bl3 in 3D)
   static int fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>& bl, const BatchList<Fdm3Args<T>>& bl3,

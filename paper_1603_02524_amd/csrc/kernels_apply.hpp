@@ -10,16 +10,17 @@
 // the 1D matrix from scalar registers.  Each node receives one contribution per
 // direction, added up in LDS in direction order; the last direction's lanes run along
 // the vector, so they read f and write y themselves.
-// Bound: memory in FP32, the vector instructions and their waits in FP64.  The form
-// before (lines of all directions at once, the direction chosen per lane, every
+// Bound: memory in FP32, the vector instructions and their waits in FP64.  The line
+// form below (lines of all directions at once, the direction chosen per lane, every
 // neighbour line from global memory at the line's stride) issued more than twice the
 // instructions, and its lines along direction 0 touched one cache line per lane and load;
 // here the direction and so every stride is a constant, direction 0 sees its neighbours
 // through LDS (coalesced loads), and a block loads its arguments in one group.  Residual,
-// before and after: 32^3 P = 8 FP32 132 -> 86 us (3.3 TB/s), 16^3 P = 8 FP64 27.6 -> 22.3 us
+// line form and this: 32^3 P = 8 FP32 132 -> 86 us (3.3 TB/s), 16^3 P = 8 FP64 27.6 -> 22.3 us
 // (3.2 TB/s), 9x7x11 P = 12 FP32 16.3 -> 11.8 and FP64 30 -> 18.3 us, 7x9x6 P = 16 FP64
 // 53.5 -> 42 us.
-// 2D: a thread per node (apply2_kernel).
+// 2D: a thread per node (apply2_kernel).  Large 2D and small 3D grids take the line form
+// (apply_lines).
 #pragma once
 
 #include "kernels.hpp"
@@ -390,8 +391,8 @@ __global__ void __launch_bounds__((apply_threads<NP, 3>()))
   }
 }
 
-// 2D.  Grids are small (256 elements of P = 16 fill a block per CU), so the length of one
-// thread's work is the time: a thread per node instead of one per line.  An element and
+// 2D grids that leave the GPU mostly idle, where the length of one thread's work is the
+// time: a thread per node instead of one per line.  An element and
 // its four neighbours come to LDS by coalesced loads, a thread per line and side takes the
 // face terms (17 instead of 289 products in a row at P = 16), then every node adds up its
 // two rows, matrix and values from LDS.
@@ -549,56 +550,402 @@ __global__ void __launch_bounds__((apply_threads<NP, 2>()))
   }
 }
 
+// The form for 2D grids that fill the GPU and for 3D grids that leave it mostly idle: a
+// thread per line of one element in one direction, the lines of all directions at once
+// (their loads overlap instead of forming one chain per direction), one LDS tile of
+// contributions per direction.
+// Elements per block: lines of all directions fill about 256 threads.
+template <int NP, int DIM>
+constexpr int lines_epb() {
+  return imax(1, 256 / (DIM * ipow(NP, DIM - 1)));
+}
+template <int NP, int DIM>
+constexpr int lines_threads() {
+  return imin(1024, round64(lines_epb<NP, DIM>() * DIM * ipow(NP, DIM - 1)));
+}
+// Own elements staged in LDS (coalesced loads) when the tiles are small: the
+// lines of the block's own elements are then read from LDS and only the
+// neighbours' lines from global memory.  A line along direction 0 is contiguous,
+// so the lanes of a wave (one line each) are NP values apart and a load touches
+// about one cache line per lane: staging removes the costliest third of the line
+// loads.
+template <int NP, int DIM>
+constexpr bool lines_stage_own() {
+  return NP <= 9 && lines_epb<NP, DIM>() * DIM * ipow(NP, DIM - 1) <= 1024;
+}
+template <class T, int DIM, int NP>
+constexpr size_t lines_shmem() {
+  return (size_t)(DIM + (lines_stage_own<NP, DIM>() ? 1 : 0)) * lines_epb<NP, DIM>() * ipow(NP, DIM) * sizeof(T);
+}
+
+// Everything one line needs besides its own values: indices, the neighbours'
+// lines (masks ml, mr), the face coefficients and the mass factor.
+template <class T, int NP>
+struct ApplyLine {
+  int d, el, base, stride;
+  T ml, mr, mo;
+  T c_two_dx, c_cl, c_cnl, c_bl, c_cr, c_cnr, c_br;
+  T wlv[NP], wrv[NP];
+};
+
+// BATCH: the arguments come from the work list bl (ntot logical blocks in all)
+template <class T, int DIM, int NP, int MODE, bool BATCH = false>
+__global__ void __launch_bounds__(1024) apply_lines_kernel(ApplyArgs<T> a0, BatchList<ApplyArgs<T>> bl, int ntot) {
+  constexpr int NE = ipow(NP, DIM), NLN = ipow(NP, DIM - 1), EPB = lines_epb<NP, DIM>();
+  constexpr int P = NP - 1;
+  constexpr bool STAGE = lines_stage_own<NP, DIM>();
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  // per-direction contribution tiles, then (STAGE) the block's own elements
+  T* sy = reinterpret_cast<T*>(smem_raw);
+  T* sx = sy + DIM * EPB * NE;
+  __shared__ double red[16];
+  __shared__ __align__(16) int sargs_raw[BATCH ? sizeof(ApplyArgs<T>) / sizeof(int) : 1];
+  ApplyArgs<T>* sargs = reinterpret_cast<ApplyArgs<T>*>(sargs_raw);
+  const ApplyArgs<T>* ap;
+  int blk;
+  if constexpr (BATCH) {
+    const int b = xcd_block(ntot);
+    if (b < 0) return;
+    blk = batch_pick(bl, b, sargs);
+    ap = sargs;
+  } else {
+    blk = xcd_block(a0.nblk);
+    if (blk < 0) return;
+    ap = &a0;
+  }
+  const T* __restrict__ x = ap->x;
+  const T* __restrict__ f = ap->f;
+  T* __restrict__ y = ap->y;
+  double* __restrict__ part = ap->part;
+  if (inactive(ap->active)) return;
+  const int e0 = blk * EPB;
+  const int ne = imin(EPB, ap->n_elem - e0);
+  const int tid = threadIdx.x, nth = blockDim.x;
+  const int64_t g0 = (int64_t)e0 * NE;
+  const int N1 = ap->N0, N2 = ap->N1;
+  // stiffness matrix rows: uniform addresses in the constant address space,
+  // so the row loop reads them with scalar loads into SGPR operands; rows
+  // longer than 72 bytes (2D, large P) would not fit the scalar registers and
+  // are staged in LDS instead (uniform-address reads)
+  constexpr bool SLS = NP * sizeof(T) <= 72;
+  __shared__ T sLsL[SLS ? 1 : NP * NP];
+  if constexpr (!SLS) {
+    for (int q = tid; q < NP * NP; q += nth) sLsL[q] = ap->Ls[q];
+    __syncthreads();
+  }
+  // MODE 3: the interpolation matrix J (NP x NPC, row-major) of the restriction
+  constexpr int NPC = (NP - 1) / 2 + 1;  // N_P of the next coarser level, P_c = floor(P / 2)
+  static_assert(MODE != 3 || STAGE, "the fused restriction needs the own-element LDS buffer");
+  __shared__ T sJx[MODE == 3 ? NP * NPC : 1];
+  if constexpr (MODE == 3)
+    for (int q = tid; q < NP * NPC; q += nth) sJx[q] = ap->J[q];
+  using CT = const __attribute__((address_space(4))) T;
+  CT* __restrict__ Ls = (CT*)ap->Ls;
+  CT* __restrict__ D0 = (CT*)ap->D;
+  CT* __restrict__ DP = (CT*)(ap->D + P * NP);
+  const T* __restrict__ rho = ap->rho;
+  const int per_dir = ne * NLN;
+  // per-direction kernel arguments in scalar registers; the per-lane choice
+  // below is arithmetic with 0/1 flags (a select chain over them gets turned
+  // into a small scratch array or into per-lane loads of the arguments)
+  using GT = const __attribute__((address_space(1))) T;  // global memory
+  GT* ec0 = (GT*)sgpr_ptr(ap->ec[0]);
+  GT* ec1 = (GT*)sgpr_ptr(ap->ec[1]);
+  GT* ec2 = (GT*)sgpr_ptr(ap->ec[DIM - 1]);
+  const int64_t eo1 = ec1 - ec0, eo2 = ec2 - ec0;
+  const int per0 = __builtin_amdgcn_readfirstlane(ap->per & 1);
+  const int per1 = __builtin_amdgcn_readfirstlane(ap->per & 2);
+  const int per2 = __builtin_amdgcn_readfirstlane(ap->per & (1 << (DIM - 1)));
+  const int N3 = __builtin_amdgcn_readfirstlane(DIM == 3 ? ap->N2 : ap->N1);
+  // The vector the epilogue reads besides the tiles (f for the residual, x for
+  // the dot product) is fetched now, so that its latency overlaps the line work
+  // (launches use lines_threads() threads, so FQ values per thread cover the block).
+  constexpr int TH = lines_threads<NP, DIM>(), FQ = (EPB * NE + TH - 1) / TH;
+  constexpr bool PREF = MODE != 0 && NP <= 9;
+  T pre[PREF ? FQ : 1];
+  if constexpr (PREF) {
+    const T* __restrict__ src = (MODE == 1 || MODE == 3) ? f : x;
+#pragma unroll
+    for (int j = 0; j < FQ; ++j) {
+      const int q = tid + j * nth;
+      pre[j] = q < ne * NE ? src[g0 + q] : T(0);
+    }
+  }
+  // Loads of line q (all issued as one group): neighbours' lines (unconditional
+  // loads at a valid address, masked later), coefficients, mass factors and,
+  // unless staged, the own line into v.
+  auto prep = [&](int q, ApplyLine<T, NP>& A, T* v, bool own) {
+    const int d = q / per_dir;
+    const int ln = q - d * per_dir;
+    const int el = ln / NLN, t = ln - el * NLN;
+    const int e = e0 + el;
+    int m[3];
+    m[0] = e % N1;
+    m[1] = DIM == 3 ? (e / N1) % N2 : e / N1;
+    m[2] = DIM == 3 ? e / (N1 * N2) : 0;
+    // per-direction fields chosen per lane (the direction varies inside a wave)
+    const int f0 = d == 0, f1 = d == 1, f2 = d == 2;
+    const int md = f0 * m[0] + f1 * m[1] + f2 * m[2];
+    const int Nd = f0 * N1 + f1 * N2 + f2 * N3;
+    const int perd = f0 * per0 + f1 * per1 + f2 * per2;
+    GT* __restrict__ ecoef = ec0 + (f1 * eo1 + f2 * eo2);
+    const int estride = f0 + f1 * N1 + f2 * (N1 * N2);
+    // line base and stride inside the element; indices of the other directions
+    const int ia = t % NP, ib = t / NP;  // local indices of the other directions (in order)
+    int base, stride;
+    if (d == 0) {
+      base = t * NP; stride = 1;
+    } else if (d == 1) {
+      base = ia + ib * NP * NP; stride = NP;
+    } else {
+      base = t; stride = NP * NP;
+    }
+    A.d = d;
+    A.el = el;
+    A.base = base;
+    A.stride = stride;
+    // neighbours along d: m -/+ 1, wrapped when periodic, none (-1) at a
+    // Dirichlet end (the element neighbour table of the setup, computed here so
+    // that no load depends on another)
+    const int nl = md > 0 ? md - 1 : (perd ? Nd - 1 : -1);
+    const int nr = md < Nd - 1 ? md + 1 : (perd ? 0 : -1);
+    A.ml = nl >= 0 ? T(1) : T(0);
+    A.mr = nr >= 0 ? T(1) : T(0);
+    if (own) {
+#pragma unroll
+      for (int k = 0; k < NP; ++k) v[k] = x[g0 + el * NE + base + k * stride];
+    }
+    GT* c = ecoef + md * ECOEF_N;
+    A.c_two_dx = c[E_TWO_DX];
+    A.c_cl = c[E_CL];
+    A.c_cnl = c[E_CNL];
+    A.c_bl = c[E_BL];
+    A.c_cr = c[E_CR];
+    A.c_cnr = c[E_CNR];
+    A.c_br = c[E_BR];
+    const T ra = rho[ia], rb = DIM == 3 ? rho[ib] : T(1);
+    T ha, hb;  // half element sizes of the other directions
+    if (DIM == 2) {
+      ha = d == 0 ? ec1[m[1] * ECOEF_N + E_HALF_DX] : ec0[m[0] * ECOEF_N + E_HALF_DX];
+      hb = T(1);
+    } else {
+      const T h0 = ec0[m[0] * ECOEF_N + E_HALF_DX];
+      const T h1 = ec1[m[1] * ECOEF_N + E_HALF_DX];
+      const T h2 = ec2[m[2] * ECOEF_N + E_HALF_DX];
+      ha = d == 0 ? h1 : h0;
+      hb = d == 2 ? h1 : h2;
+    }
+    // mass factor of the other directions at this line
+    A.mo = DIM == 2 ? ha * ra : ha * ra * hb * rb;
+    const T* wl = x + (int64_t)(e + (nl >= 0 ? nl - md : 0) * estride) * NE + base;
+    const T* wr = x + (int64_t)(e + (nr >= 0 ? nr - md : 0) * estride) * NE + base;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      A.wlv[k] = wl[k * stride];
+      A.wrv[k] = wr[k * stride];
+    }
+  };
+  // the line's contribution mo * (L_d-row terms) into its direction's tile
+  auto finish = [&](const ApplyLine<T, NP>& A, const T* v) {
+    T d0 = 0, dP = 0, dL = 0, dR = 0;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      d0 += D0[k] * v[k];
+      dP += DP[k] * v[k];
+      dL += DP[k] * A.wlv[k];
+      dR += D0[k] * A.wrv[k];
+    }
+    const T uL = A.ml * A.wlv[P], uR = A.mr * A.wrv[0];
+    dL *= A.ml;
+    dR *= A.mr;
+    const T jl = v[0] - uL, jr = v[P] - uR;
+    const T fl = A.c_cl * d0 + A.c_cnl * dL + A.c_bl * jl;
+    const T fr = -A.c_cr * dP - A.c_cnr * dR + A.c_br * jr;
+    const T cl = A.c_cl * jl, cr = A.c_cr * jr, tdx = A.c_two_dx;
+    T* __restrict__ syd = sy + (A.d * ne + A.el) * NE + A.base;
+#pragma unroll 1  // one row of Ls live at a time (registers for the line data)
+    for (int i = 0; i < NP; ++i) {
+      T s = 0;
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        if constexpr (SLS) s += Ls[__builtin_amdgcn_readfirstlane(i) * NP + k] * v[k];
+        else s += sLsL[i * NP + k] * v[k];
+      }
+      const int iu = __builtin_amdgcn_readfirstlane(i);
+      T o = tdx * s + cl * D0[iu] - cr * DP[iu];
+      if (i == 0) o += fl;
+      if (i == P) o += fr;
+      syd[i * A.stride] = A.mo * o;
+    }
+  };
+  if constexpr (STAGE) {
+    // one line per thread (the launch covers all lines of the block)
+    constexpr int SQ = (EPB * NE + TH - 1) / TH;
+    T st[SQ];
+#pragma unroll
+    for (int j = 0; j < SQ; ++j) {
+      const int q = tid + j * nth;
+      st[j] = q < ne * NE ? x[g0 + q] : T(0);
+    }
+    const bool has = tid < DIM * per_dir;
+    ApplyLine<T, NP> A;
+    T v[NP];
+    prep(has ? tid : 0, A, v, false);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < SQ; ++j) {
+      const int q = tid + j * nth;
+      if (q < ne * NE) sx[q] = st[j];
+    }
+    __syncthreads();
+    if (has) {
+#pragma unroll
+      for (int k = 0; k < NP; ++k) v[k] = sx[A.el * NE + A.base + k * A.stride];
+      finish(A, v);
+    }
+  } else {
+    for (int q = tid; q < DIM * per_dir; q += nth) {
+      ApplyLine<T, NP> A;
+      T v[NP];
+      prep(q, A, v, true);
+      if constexpr (NP <= 9) __builtin_amdgcn_sched_barrier(0);
+      finish(A, v);
+    }
+  }
+  __syncthreads();
+  double acc = 0.0;
+  const int dstride = ne * NE;
+  auto out = [&](int q, T other) {
+    T val = sy[q] + sy[dstride + q];
+    if (DIM == 3) val += sy[2 * dstride + q];
+    if (MODE == 0) {
+      y[g0 + q] = val;
+    } else if (MODE == 1) {
+      y[g0 + q] = other - val;
+    } else if (MODE == 3) {
+      sx[q] = other - val;  // the own elements' x are no longer needed
+    } else {
+      y[g0 + q] = val;
+      acc += (double)other * (double)val;
+    }
+  };
+  if constexpr (PREF) {
+#pragma unroll
+    for (int j = 0; j < FQ; ++j) {
+      const int q = tid + j * nth;
+      if (q < ne * NE) out(q, pre[j]);
+    }
+  } else if constexpr (MODE == 0) {
+    for (int q = tid; q < ne * NE; q += nth) out(q, T(0));
+  } else {
+    // every load of f (x) issued before the sums that use them
+    const T* __restrict__ src = (MODE == 1 || MODE == 3) ? f : x;
+    staged_copy<T, TH, EPB * NE>([&](int q) { return src[g0 + q]; }, [&](int q, T v) { out(q, v); }, ne * NE);
+  }
+  if (MODE == 2) {
+    const double s = block_sum(acc, red);
+    if (tid == 0) part[blk] = s;
+  }
+  if constexpr (MODE == 3) {
+    // the transfer kernel's restriction passes, on the residual in LDS (the
+    // direction tiles serve as the two pass buffers); y is the coarse vector
+    constexpr int NEC = ipow(NPC, DIM);
+    __syncthreads();
+    T* bA = sy;
+    T* bB = sy + EPB * NE;
+    xfer_pass<T, DIM, NP, NPC, NE, 0, true, NPC>(sJx, sx, bA, ne);
+    __syncthreads();
+    xfer_pass<T, DIM, NP, NPC, NE, 1, true, NPC>(sJx, bA, bB, ne);
+    __syncthreads();
+    const T* res = bB;
+    if constexpr (DIM == 3) {
+      xfer_pass<T, DIM, NP, NPC, NE, 2, true, NPC>(sJx, bB, bA, ne);
+      __syncthreads();
+      res = bA;
+    }
+    T* yc = y + (int64_t)e0 * NEC;
+    for (int q = tid; q < ne * NEC; q += nth) {
+      const int el = q / NEC;
+      yc[q] = res[el * NE + q - el * NEC];
+    }
+  }
+}
+
+// The form of a grid's apply (of the grid, also when grids share a launch, so that a batch
+// gives what its grids give alone).  2D: a thread per node up to 1.5 MB of level vector,
+// where the line form's chain of products is the time (16x16 P = 16 FP64 11.9 against
+// 4.6 us); beyond, its LDS reads bind it (128x128 P = 16 FP64 199 against 60 us; the two
+// meet at 200000 to 300000 nodes in FP64, twice that in FP32).  P <= 2: lines (3.6 against
+// 4.0 us).  3D: lines up to 1 MB and P <= 8, where the directions in turn are the longer
+// chain (4^3 P = 8 FP64 5.8 against 6.8 us, 8^3 P = 2 FP32 3.4 against 3.9); the two meet
+// near 8^3 elements of P = 8, and at 20^3 the directions in turn take 22 against 35 us (FP32).
+template <class T, int DIM, int NP>
+constexpr bool apply_lines(int n_elem) {
+  const int64_t bytes = (int64_t)n_elem * ipow(NP, DIM) * (int64_t)sizeof(T);
+  return DIM == 2 ? NP <= 3 || bytes > (3 << 19) : NP <= 9 && bytes <= (1 << 20);
+}
+template <int DIM, int NP>
+constexpr bool apply_lines_built() {
+  return DIM == 2 || NP <= 9;
+}
+
 template <class T, int DIM, int NP, int MODE, bool BATCH>
-void apply_go(const ApplyArgs<T>& a, const BatchList<ApplyArgs<T>>& bl, int nlog, hipStream_t s) {
-  const size_t shm = apply_shmem<T, DIM, NP>(BATCH || (a.per & 1));
-  const auto go = [&](auto kernel) {
+void apply_go(const ApplyArgs<T>& a, const BatchList<ApplyArgs<T>>& bl, int nlog, bool lines, hipStream_t s) {
+  const auto go = [&](auto kernel, int th, size_t shm) {
     if (shm > 65536)
       (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
-    hipLaunchKernelGGL(kernel, dim3(xcd_grid(nlog)), dim3(apply_threads<NP, DIM>()), shm, s, a, bl, nlog);
+    hipLaunchKernelGGL(kernel, dim3(xcd_grid(nlog)), dim3(th), shm, s, a, bl, nlog);
   };
-  if constexpr (DIM == 3) go(apply_kernel<T, NP, MODE, BATCH>);
-  else go(apply2_kernel<T, NP, MODE, BATCH>);
+  if constexpr (apply_lines_built<DIM, NP>() && (MODE != 3 || lines_stage_own<NP, DIM>())) {
+    if (lines)
+      return go(apply_lines_kernel<T, DIM, NP, MODE, BATCH>, lines_threads<NP, DIM>(), lines_shmem<T, DIM, NP>());
+  }
+  const size_t shm = apply_shmem<T, DIM, NP>(BATCH || (a.per & 1));
+  if constexpr (DIM == 3) go(apply_kernel<T, NP, MODE, BATCH>, apply_threads<NP, DIM>(), shm);
+  else if constexpr (NP > 3) go(apply2_kernel<T, NP, MODE, BATCH>, apply_threads<NP, DIM>(), shm);
 }
 
-// Blocks of one grid's apply: groups of apply_epb elements.
-template <int DIM, int NP>
+// Blocks of one grid's apply.
+template <class T, int DIM, int NP>
 int apply_blocks(int n_elem) {
-  constexpr int EPB = apply_epb<NP, DIM>();
-  return (n_elem + EPB - 1) / EPB;
+  const int epb = apply_lines<T, DIM, NP>(n_elem) ? lines_epb<NP, DIM>() : apply_epb<NP, DIM>();
+  return (n_elem + epb - 1) / epb;
 }
 
-// The fused residual + restriction (mode 3) is built for coarse levels whose order
-// follows P_c = floor(P / 2).
+// The fused residual + restriction (mode 3) is built for coarse levels whose order follows
+// P_c = floor(P / 2), in the line form where it stages the own elements in LDS.
 template <class T, int DIM, int NP>
 bool apply_mode3_ok(const LevelDev<T>& L) {
-  return !(DIM == 3 && NP > 17) && L.NPc == (NP - 1) / 2 + 1 && L.J != nullptr;
+  return !(DIM == 3 && NP > 17) && L.NPc == (NP - 1) / 2 + 1 && L.J != nullptr &&
+         (!apply_lines<T, DIM, NP>(L.n_elem) || lines_stage_own<NP, DIM>());
 }
 
 template <class T, int DIM, int NP, bool BATCH>
-int apply_mode(int mode, const ApplyArgs<T>& a, const BatchList<ApplyArgs<T>>& bl, int nlog, hipStream_t s) {
-  if (mode == 0) apply_go<T, DIM, NP, 0, BATCH>(a, bl, nlog, s);
-  else if (mode == 1) apply_go<T, DIM, NP, 1, BATCH>(a, bl, nlog, s);
-  else if (mode == 2) apply_go<T, DIM, NP, 2, BATCH>(a, bl, nlog, s);
-  else apply_go<T, DIM, NP, 3, BATCH>(a, bl, nlog, s);
+int apply_mode(int mode, const ApplyArgs<T>& a, const BatchList<ApplyArgs<T>>& bl, int nlog, bool lines, hipStream_t s) {
+  if (mode == 0) apply_go<T, DIM, NP, 0, BATCH>(a, bl, nlog, lines, s);
+  else if (mode == 1) apply_go<T, DIM, NP, 1, BATCH>(a, bl, nlog, lines, s);
+  else if (mode == 2) apply_go<T, DIM, NP, 2, BATCH>(a, bl, nlog, lines, s);
+  else if (lines && !lines_stage_own<NP, DIM>()) return -4;
+  else apply_go<T, DIM, NP, 3, BATCH>(a, bl, nlog, lines, s);
   return 0;
 }
 
 template <class T, int DIM, int NP>
 int apply_launch(const LevelDev<T>& L, int mode, const T* x, const T* f, T* y, double* part,
                  int* nblk_out, hipStream_t s) {
-  const int nblk = apply_blocks<DIM, NP>(L.n_elem);
+  const int nblk = apply_blocks<T, DIM, NP>(L.n_elem);
   if (nblk_out) *nblk_out = nblk;
   // fused residual + restriction: otherwise the caller runs the two steps
   if (mode == 3 && !apply_mode3_ok<T, DIM, NP>(L)) return -4;
-  return apply_mode<T, DIM, NP, false>(mode, apply_args(L, x, f, y, part, nblk), BatchList<ApplyArgs<T>>{}, nblk, s);
+  return apply_mode<T, DIM, NP, false>(mode, apply_args(L, x, f, y, part, nblk), BatchList<ApplyArgs<T>>{}, nblk,
+                                       apply_lines<T, DIM, NP>(L.n_elem), s);
 }
 
-// One launch over the applies of many grids (same NP and mode): ntot logical
+// One launch over the applies of many grids (same NP, mode and form): ntot logical
 // blocks, grid g's apply_blocks in the range of bl.
 template <class T, int DIM, int NP>
-int apply_batch_launch(int mode, const BatchList<ApplyArgs<T>>& bl, int ntot, hipStream_t s) {
-  return apply_mode<T, DIM, NP, true>(mode, ApplyArgs<T>{}, bl, ntot, s);
+int apply_batch_launch(int mode, bool lines, const BatchList<ApplyArgs<T>>& bl, int ntot, hipStream_t s) {
+  return apply_mode<T, DIM, NP, true>(mode, ApplyArgs<T>{}, bl, ntot, lines, s);
 }
 
 }  // namespace dgmg

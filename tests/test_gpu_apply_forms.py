@@ -1,4 +1,5 @@
-"""Operator apply at the edges of its blocks: element counts that leave a ragged last
+"""Operator apply in its forms (3D: directions in turn, lines of all directions at once on
+small grids; 2D: a thread per node, lines on large grids) at the edges of its blocks: element counts that leave a ragged last
 block, rows along direction 0 shorter than a block or cut by one, periodic and Dirichlet
 ends (three, four and five elements around), every compiled order, 2D and 3D, against the
 oracle's operator; and the V-cycle with the residual and restriction in one launch
@@ -26,6 +27,10 @@ CASES = [((n, 3, 2), (per, per, False), 8) for n in (3, 4, 5) for per in (False,
     ((2, 3, 1), (False, True, False), 16), ((1, 3, 2), False, 16), ((7, 5), True, 2), ((5, 3), False, 3), ((3, 7), True, 4),
     ((1, 1), False, 4), ((4, 5), True, 6), ((3, 5), True, 8), ((3, 2), False, 12), ((4, 3), True, 16),
     ((1, 3), (False, True), 32), ((3, 2), False, 32),
+    # large enough for the directions in turn (3D) and for lines (2D) in both precisions
+    ((3, 12, 11), True, 8), ((4, 10, 10), (True, False, True), 8), ((5, 9, 9), False, 8), ((1, 20, 20), False, 8),
+    ((2, 14, 15), (False, True, True), 8), ((7, 8, 7), True, 8), ((9, 9, 10), (True, True, False), 6), ((13, 13, 13), True, 4),
+    ((17, 16, 16), False, 3), ((22, 21, 22), True, 2), ((37, 38), False, 16), ((70, 71), True, 8), ((127, 126), False, 4),
 ]
 
 

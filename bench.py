@@ -102,7 +102,7 @@ def _top_kernel(S, m):
     f64 = m.precision == "fp64"
     t = "double" if f64 else "float"
     big = S.grid.dim == 3 and P == 32
-    name = (f"fdm_big_{{a,b,c}}<{t},{na},{nl}>" if big else f"fdm_kernel<{t},3,{na},{nl}>") + \
+    name = (f"fdm_big_{{a,b,c}}<{t},{na},{nl}>" if big else f"fdm3_kernel<{t},{na},{nl}>") + \
         f" ({'face' if m.smoother == 'FA' else 'element'}-centred patch solve, P={P}, N_O={n_o})"
     return name, (FP64_VALU_PEAK_TFLOPS if f64 else FP32_MFMA_PEAK_TFLOPS)
 

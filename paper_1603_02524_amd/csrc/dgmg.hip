@@ -520,7 +520,9 @@ struct dgmg_batch {
   // (forked from and joined back into the phase's stream with events)
   // Used when the batch holds a grid whose top level fills the GPU alone
   // (measured: the 64-grid workload 376 -> 364 ms; a batch of small grids only
-  // slowed down, 38.0 -> 41.4 ms, its steps too short for the fork and join).
+  // slowed down, 38.0 -> 41.4 ms, its steps too short for the fork and join at
+  // every position: its order families run side by side instead, forked and
+  // joined once a V-cycle).
   static constexpr int NSIDE = 3;
   hipStream_t side[NSIDE] = {};
   hipEvent_t ev_fork = nullptr, ev_join[NSIDE] = {};

@@ -16,7 +16,6 @@ namespace dgmg {
 // Transfer pairs (NP fine, NP coarse) for P -> floor(P / 2).
 #define DGMG_XFER_LIST(X) X(3, 2) X(4, 2) X(5, 3) X(7, 4) X(9, 5) X(13, 7) X(17, 9) X(33, 17)
 // 3D elements with NP = BIG_NP and patch tiles beyond LDS use kernels_big.hpp.
-constexpr size_t LDS_BYTES = 160 * 1024;  // gfx950 LDS per workgroup
 // Patch tiles (NA, NL): element-centred (n, n) with n = NP + 2 N_O and
 // face-centred (2P, NP + 2 N_O) for the overlaps N_O the level rules produce
 // (and N_O = 0, 1 for the zero-overlap variants).
@@ -71,7 +70,7 @@ bool Kern<T, DIM>::fdm_supported(int NA, int NL) {
 template <class T, int DIM>
 bool Kern<T, DIM>::fdm_in_lds(int NA, int NL) {
 #define DGMG_CASE(A, B) \
-  if (NA == A && NL == B) return !(DIM == 3 && fdm_lds_total<T, A, B, DIM>() > LDS_BYTES);
+  if (NA == A && NL == B) return DIM == 2 || fdm3_fits<T, A, B>();
   DGMG_FDM_LIST(DGMG_CASE)
   if constexpr (DIM == 2) {
     DGMG_FDM_LIST_2D(DGMG_CASE)
@@ -86,7 +85,7 @@ PatchBuf Kern<T, DIM>::patch_buf(int NP, int nd, int NA, int NL, const int* np, 
   if constexpr (DIM == 3) {
 #define DGMG_CASE(A, B)                                            \
   if (NA == A && NL == B) {                                        \
-    if constexpr (fdm_lds_total<T, A, B, DIM>() <= LDS_BYTES) {    \
+    if constexpr (fdm3_fits<T, A, B>()) {                          \
       pb.swp = 1;                                                  \
       pb.step = step;                                              \
       if (whole && order_compiled(NP)) pb.K = fdm3_strip<T>(A, B, nd, np, step); \
@@ -119,7 +118,7 @@ int Kern<T, DIM>::fdm(const LevelDev<T>& L, int nd, int NA, int NL, const T* r, 
   }
 #define DGMG_CASE(A, B)                                                                        \
   if (NA == A && NL == B) {                                                                    \
-    if constexpr (DIM == 3 && fdm_lds_total<T, A, B, DIM>() > LDS_BYTES)                       \
+    if constexpr (DIM == 3 && !fdm3_fits<T, A, B>())                                           \
       return whole ? fdm_big_launch<T, A, B>(L, nd, r, out, npx, npy, npz, s) : -4;            \
     else if constexpr (DIM == 3)                                                               \
       return fdm3_go<T, A, B, false>(nd, a3, BatchList<Fdm3Args<T>>{}, a3.nblk, s);            \
@@ -223,7 +222,7 @@ int Kern<T, DIM>::fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>&
   a3.step = pb.step;
 #define DGMG_CASE(A, B)                                                          \
   if (NA == A && NL == B) {                                                      \
-    if constexpr (DIM == 3 && fdm_lds_total<T, A, B, DIM>() > LDS_BYTES)         \
+    if constexpr (DIM == 3 && !fdm3_fits<T, A, B>())                             \
       return -4;                                                                 \
     else if constexpr (DIM == 3)                                                 \
       return fdm3_go<T, A, B, true>(nd, a3, bl3, ntot, s);                       \

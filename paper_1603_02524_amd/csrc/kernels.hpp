@@ -91,14 +91,22 @@ struct PatchBuf {
   int K = 1, step = 0, swp = 0;
 };
 
+constexpr size_t LDS_BYTES = 160 * 1024;  // gfx950 LDS per workgroup
+
 // A len x len matrix in LDS: rows padded with zeros to the operands' blocks, and a
 // pitch of 2 (mod 16) so that the four rows and four columns of an operand block lie
 // on distinct banks, read as M or as its transpose.  The patch matrices are kept in
 // device memory in this form (fdm3_image values each): a block copies them in 16-byte
-// pieces without index arithmetic.
+// pieces without index arithmetic.  FP32 rows beyond 32 are not padded (33 would become
+// 48, and three such matrices do not fit the LDS beside a 33^3 tile): their readers
+// mask what lies outside the matrix.
+template <class T>
+constexpr bool fdm3_padded(int len) {
+  return sizeof(T) == 8 || len <= 32;
+}
 template <class T>
 constexpr int fdm3_rows(int len) {
-  return sizeof(T) == 8 ? (len + 3) / 4 * 4 : (len + 15) / 16 * 16;
+  return sizeof(T) == 8 ? (len + 3) / 4 * 4 : (fdm3_padded<T>(len) ? (len + 15) / 16 * 16 : len);
 }
 template <class T>
 constexpr int fdm3_pitch(int len) {
@@ -106,7 +114,8 @@ constexpr int fdm3_pitch(int len) {
 }
 template <class T>
 constexpr int fdm3_image(int len) {
-  return fdm3_rows<T>(len) * fdm3_pitch<T>(len);
+  constexpr int piece = 16 / (int)sizeof(T);
+  return (fdm3_rows<T>(len) * fdm3_pitch<T>(len) + piece - 1) / piece * piece;
 }
 
 // Work list of a batched launch: one kernel over the work of many grids.  The
@@ -254,16 +263,6 @@ constexpr int fdm_threads() {
 template <class T, int NA, int NL, int DIM>
 constexpr size_t fdm_shmem() {
   return (size_t)fdm_tile_padded<NA, NL, DIM>() * sizeof(T);
-}
-
-// Whole LDS of one patch-solve block: the tile plus the per-direction and
-// per-row tables (largest over the sweep kinds) and some slack.
-template <class T, int NA, int NL, int DIM>
-constexpr size_t fdm_lds_total() {
-  constexpr int NMAX = imax(NA, NL);
-  constexpr int NROW = DIM == 3 ? imax(NL * NL, NA * NL) : imax(NL, NA);
-  return fdm_shmem<T, NA, NL, DIM>() + 3 * NMAX * (sizeof(int) + 2 * sizeof(T)) +
-         NROW * (2 * sizeof(int) + sizeof(T)) + 512;
 }
 
 // 16x16x4 matrix-core contraction (v_mfma_{f64,f32}_16x16x4): A[i][k] comes from lane

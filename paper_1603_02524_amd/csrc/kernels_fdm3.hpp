@@ -34,6 +34,7 @@
 // path was then two thirds busy).
 #pragma once
 
+#include <initializer_list>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -111,7 +112,12 @@ struct FdmOp<float, LEN> {
 #pragma unroll
       for (int ks = 0; ks < KC; ++ks) {
         const int j = 16 * nb + 4 * (li & 3) + (li >> 2), k = 4 * ks + lk;
-        a[nb][ks] = M[k * SK + j * SJ];
+        if constexpr (fdm3_padded<float>(LEN)) {
+          a[nb][ks] = M[k * SK + j * SJ];
+        } else {  // a valid index, zero outside the matrix
+          const float v = M[imin(k, LEN - 1) * SK + imin(j, LEN - 1) * SJ];
+          a[nb][ks] = k < LEN && j < LEN ? v : 0.0f;
+        }
       }
   }
   __device__ __forceinline__ void apply(const float* v, float, float* acc) const {
@@ -235,6 +241,16 @@ Fdm3Args<T> fdm3_args(const LevelDev<T>& L, int nd, const T* r, T* out, int npx,
   a.my = div_magic(a.nblk, a.nsy);
   a.lat = lat;
   return a;
+}
+
+// The tile's solve runs here: a patch, with its matrices and a work list's arguments, in LDS
+// whatever the normal (FP32 33 x 33 x 33, the largest: 158412 + 176 bytes of 163840).
+template <class T, int NA, int NL>
+constexpr bool fdm3_fits() {
+  size_t most = 0;
+  for (const size_t b : {fdm3_shmem<T, NA, NL, 0>(1, 0), fdm3_shmem<T, NA, NL, 1>(1, 0), fdm3_shmem<T, NA, NL, 2>(1, 0)})
+    most = b > most ? b : most;
+  return most + (sizeof(Fdm3Args<T>) + 15) / 16 * 16 <= LDS_BYTES;
 }
 
 // BATCH: the arguments come from the work list bl (ntot logical blocks in all)
@@ -628,13 +644,15 @@ __global__ void __launch_bounds__((64 * fdm3_waves<T, NA, NL>()))
 }
 
 template <class T, int NA, int NL, int ND, bool BATCH>
-void fdm3_launch_nd(const Fdm3Args<T>& a, const BatchList<Fdm3Args<T>>& bl, int nlog, hipStream_t s) {
+int fdm3_launch_nd(const Fdm3Args<T>& a, const BatchList<Fdm3Args<T>>& bl, int nlog, hipStream_t s) {
+  static_assert(fdm3_fits<T, NA, NL>(), "a patch and its matrices fit the LDS");
   const size_t shm = fdm3_shmem<T, NA, NL, ND>(a.K, a.step);
-  if (shm > 65536)
-    (void)hipFuncSetAttribute((const void*)fdm3_kernel<T, NA, NL, ND, BATCH>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+  if (shm > 65536 && hipFuncSetAttribute((const void*)fdm3_kernel<T, NA, NL, ND, BATCH>,
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
+    return -4;
   hipLaunchKernelGGL((fdm3_kernel<T, NA, NL, ND, BATCH>), dim3(xcd_grid(nlog)), dim3(64 * fdm3_waves<T, NA, NL>()), shm,
                      s, a, bl, nlog);
+  return 0;
 }
 
 // Batched: a's K and step are those of the longest strip of the launch (its LDS), bl
@@ -642,16 +660,12 @@ void fdm3_launch_nd(const Fdm3Args<T>& a, const BatchList<Fdm3Args<T>>& bl, int 
 template <class T, int NA, int NL, bool BATCH>
 int fdm3_go(int nd, const Fdm3Args<T>& a, const BatchList<Fdm3Args<T>>& bl, int nlog, hipStream_t s) {
   if (nd < 0) {
-    if constexpr (NA == NL) {
-      fdm3_launch_nd<T, NA, NL, -1, BATCH>(a, bl, nlog, s);
-      return 0;
-    }
-    return -4;
+    if constexpr (NA == NL) return fdm3_launch_nd<T, NA, NL, -1, BATCH>(a, bl, nlog, s);
+    else return -4;
   }
-  if (nd == 0) fdm3_launch_nd<T, NA, NL, 0, BATCH>(a, bl, nlog, s);
-  else if (nd == 1) fdm3_launch_nd<T, NA, NL, 1, BATCH>(a, bl, nlog, s);
-  else fdm3_launch_nd<T, NA, NL, 2, BATCH>(a, bl, nlog, s);
-  return 0;
+  if (nd == 0) return fdm3_launch_nd<T, NA, NL, 0, BATCH>(a, bl, nlog, s);
+  if (nd == 1) return fdm3_launch_nd<T, NA, NL, 1, BATCH>(a, bl, nlog, s);
+  return fdm3_launch_nd<T, NA, NL, 2, BATCH>(a, bl, nlog, s);
 }
 
 // Patches per strip of a whole-partition sweep (np patches per direction, `step`

@@ -1115,6 +1115,13 @@ void k_mean_sub(dgmg_handle* h, double* a, int64_t n) {
                      1.0 / (double)n, n, h->active);
 }
 
+bool periodic_all(const dgmg_handle* h) {
+  const LevelHost& l0 = h->lv[0];
+  bool all = true;
+  for (int d = 0; d < l0.dim; ++d) all = all && l0.dir[d].periodic;
+  return all;
+}
+
 // u0 = A0^+ f0 (double vectors) by global fast diagonalisation.
 int coarse_fdm(dgmg_handle* h, const double* f0, double* u0) {
   const LevelHost& l0 = h->lv[0];
@@ -1122,11 +1129,14 @@ int coarse_fdm(dgmg_handle* h, const double* f0, double* u0) {
   const unsigned nb = (unsigned)((n + VEC_THREADS - 1) / VEC_THREADS);
   const int dim = l0.dim;
   const double* src = f0;
-  bool per_all = true;
-  for (int d = 0; d < dim; ++d) per_all = per_all && l0.dir[d].periodic;
+  const bool per_all = periodic_all(h), one_block = coarse_block_fits(h->cdev);
   if (per_all) {  // make f0 orthogonal to the constants (Euclidean mean)
-    hipLaunchKernelGGL(k_copy, dim3(vec_blocks(n)), dim3(VEC_THREADS), 0, h->stream, f0, h->c_f, n, h->active);
-    k_mean_sub(h, h->c_f, n);
+    if (one_block) {
+      hipLaunchKernelGGL(coarse_mean_kernel, dim3(1), dim3(COARSE_THREADS), 0, h->stream, h->cdev, f0, h->c_f, h->active);
+    } else {
+      hipLaunchKernelGGL(k_copy, dim3(vec_blocks(n)), dim3(VEC_THREADS), 0, h->stream, f0, h->c_f, n, h->active);
+      k_mean_sub(h, h->c_f, n);
+    }
     src = h->c_f;
   }
   double* bufs[2] = {h->c_a, h->c_b};
@@ -1155,18 +1165,14 @@ int coarse_fdm(dgmg_handle* h, const double* f0, double* u0) {
     in = out;
     k ^= 1;
   }
-  if (per_all) k_mean_sub(h, u0, n);  // mean-free (minimum-norm) representative
+  if (per_all) {  // mean-free (minimum-norm) representative
+    if (one_block)
+      hipLaunchKernelGGL(coarse_mean_kernel, dim3(1), dim3(COARSE_THREADS), 0, h->stream, h->cdev, u0, u0, h->active);
+    else
+      k_mean_sub(h, u0, n);
+  }
   return check_hip(h, "coarse solve");
 }
-
-bool periodic_all(const dgmg_handle* h) {
-  const LevelHost& l0 = h->lv[0];
-  bool all = true;
-  for (int d = 0; d < l0.dim; ++d) all = all && l0.dir[d].periodic;
-  return all;
-}
-// The one-block form of the coarse solve applies.
-bool coarse_in_block(const dgmg_handle* h) { return coarse_block_shmem(h->cdev) <= COARSE_LDS; }
 
 template <class T>
 CoarseArgs<T> coarse_args(const dgmg_handle* h, const T* f0, T* u0) {
@@ -1189,19 +1195,15 @@ void allow_shmem(K kernel, size_t bytes) {
 template <class T>
 int k_coarse(dgmg_handle* h, const T* f0, T* u0) {
   const CoarseDev& C = h->cdev;
-  // the same bits either way; the three launches take over where the rate of one unit
-  // costs more than two launches (one block / planes: 1680 unknowns 15.5 us / three
-  // launches of 4.5 us, 3375 unknowns 26.4 / 15.5 us)
-  const bool planes = C.dim == 3 && !periodic_all(h) && coarse_planes_shmem(C) <= COARSE_LDS &&
-                      coarse_columns_shmem(C) <= COARSE_LDS;
-  if (coarse_in_block(h) && !(planes && h->lv[0].n_dof > 2048)) {
+  const CoarseForm form = coarse_form(C, periodic_all(h));
+  if (form == COARSE_BLOCK) {
     const size_t shm = coarse_block_shmem(C);
     allow_shmem(coarse_block_kernel<T, false>, shm);
     hipLaunchKernelGGL((coarse_block_kernel<T, false>), dim3(1), dim3(COARSE_THREADS), shm, h->stream,
                        coarse_args<T>(h, f0, u0), BatchList<CoarseArgs<T>>{});
     return check_hip(h, "coarse solve");
   }
-  if (planes) {
+  if (form == COARSE_PLANES) {
     const int G2 = coarse_nodes(C, 2), cols = coarse_nodes(C, 0) * coarse_nodes(C, 1);
     const size_t sp = coarse_planes_shmem(C), sc = coarse_columns_shmem(C);
     allow_shmem(coarse_planes_kernel<T, true>, sp);
@@ -2232,7 +2234,7 @@ constexpr int64_t SOLO_DOF = 1 << 20;
 // Steps of one grid's V-cycle (as k_vcycle, k_smooth, k_sweep,
 // k_residual_restrict and k_transfer issue them).
 template <class T>
-void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<BStep>& out) {
+void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, bool coarse_shared, std::vector<BStep>& out) {
   const int L = (int)h->lv.size() - 1;
   const int f32 = sizeof(T) == 4;
   const bool var = h->opts.vcycle == DGMG_VCYCLE_VARIABLE;
@@ -2396,7 +2398,7 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, std::vector<
   {
     T* f0 = f[0];
     T* u0 = u[0];
-    if (coarse_in_block(h)) {
+    if (coarse_shared && coarse_block_fits(h->cdev)) {
       step({2}, BK_COARSE, 3, {}, 1, arg_bytes(coarse_args<T>(h, f0, u0)));
       out.back().shmem = coarse_block_shmem(h->cdev);
     } else {
@@ -2447,6 +2449,12 @@ int batch_plan(dgmg_batch* b, bool fill) {
     if (f == odd.size()) odd.push_back(P);
     return (int)f;
   };
+  // grids whose coarse solve fits one block share a launch of a block each, even where a grid
+  // alone would take another form, if they are three or more (a block takes up to 60 us, a
+  // grid's own launches 17 to 40)
+  const bool shared = std::count_if(b->h.begin(), b->h.end(), [](const dgmg_handle* h) {
+                        return coarse_block_fits(h->cdev) && coarse_form(h->cdev, periodic_all(h)) != COARSE_BLOCK;
+                      }) >= 3;
   for (int gi = 0; gi < n; ++gi) {
     dgmg_handle* h = b->h[gi];
     const int L = (int)h->lv.size() - 1;
@@ -2504,8 +2512,9 @@ int batch_plan(dgmg_batch* b, bool fill) {
     pcg(2, 1, PCG_TOTAL, pv);
     // phase b: the V-cycle (mixed: on the FP32 copies of r and z), then the direction update
     const size_t at = steps[1].size();
-    if (mixed(h)) vcycle_steps<float>(h, gi, (const float*)h->buf[L].f, (float*)h->buf[L].u, steps[1]);
-    else vcycle_steps<double>(h, gi, h->pr, h->pz, steps[1]);
+    const bool cs = shared || coarse_form(h->cdev, periodic_all(h)) == COARSE_BLOCK;
+    if (mixed(h)) vcycle_steps<float>(h, gi, (const float*)h->buf[L].f, (float*)h->buf[L].u, cs, steps[1]);
+    else vcycle_steps<double>(h, gi, h->pr, h->pz, cs, steps[1]);
     for (size_t k = at; k < steps[1].size(); ++k) {
       steps[1][k].fam = family(h);
       steps[1][k].key.insert(steps[1][k].key.begin(), {0, steps[1][k].fam});

@@ -1,10 +1,10 @@
 // Exact coarse solve u_0 = A_0^+ f_0 (P = 1) by global fast diagonalisation, FP64:
 // one pass per direction with S_d^T, division by the sums of the eigenvalues, one pass
-// per direction with S_d.  Three forms:
+// per direction with S_d.  Three forms, with the same bits (coarse_form picks one):
 //   one block   the whole vector and the matrices in LDS, every pass in one launch (bound
 //               by LDS latency: 13 us for 2D 16 x 16, 1024 unknowns with a periodic mean,
-//               11 launches of 3 to 5 us before; 15.5 us for 7 x 5 x 6 elements, six before)
-//   planes      larger 3D grids whose planes of directions 0 and 1 fit: forward along 0 and
+//               11 launches of 3 to 5 us as passes; 13.5 us for 7 x 5 x 6 elements)
+//   planes      3D grids whose planes of directions 0 and 1 fit: forward along 0 and
 //               1 per plane, forward, scaled and back along 2 per group of columns, back
 //               along 1 and 0 per plane (three launches)
 //   passes      the rest: one launch per direction and way (in dgmg.hip)
@@ -246,6 +246,46 @@ __global__ void __launch_bounds__(256) coarse_columns_kernel(CoarseDev C, double
 inline size_t coarse_columns_shmem(const CoarseDev& C) {
   const size_t G = coarse_nodes(C, 2);
   return (2 * G * COARSE_COLS + G * coarse_pitch((int)G)) * sizeof(double);
+}
+
+// out = f less its mean (out may be f), for grids that the one-block form could take but
+// does not: the same order of the sum, so the same bits.
+__global__ void __launch_bounds__(COARSE_THREADS) coarse_mean_kernel(CoarseDev C, const double* f, double* out,
+                                                                     const int* active) {
+  __shared__ double red[COARSE_THREADS / 64], mean;
+  if (inactive(active)) return;
+  const int G0 = coarse_nodes(C, 0), G1 = coarse_nodes(C, 1), n = G0 * G1 * coarse_nodes(C, 2);
+  const auto at = [&](int q) {
+    const int r = q / G0;
+    return coarse_offset(C, q - r * G0, r % G1, r / G1);
+  };
+  double s = 0.0;
+  for (int q = threadIdx.x; q < n; q += blockDim.x) s += f[at(q)];
+  s = block_sum(s, red);
+  if (threadIdx.x == 0) mean = s / (double)n;
+  __syncthreads();
+  for (int q = threadIdx.x; q < n; q += blockDim.x) out[at(q)] = f[at(q)] - mean;
+}
+
+// The form of a grid's coarse solve.  The one block has the rate of one compute unit, some
+// 0.1 us per 1000 products of one way: it ends where the launches of the passes cost less
+// (us, block / passes: 2D 22 x 22 elements, 170 k products, 21.0 / 21.4, 24 x 24, 221 k, 24.3 /
+// 21.2; periodic, where the passes have two launches more for the means, 26 x 26, 281 k,
+// 31.9 / 33.5, 28 x 28, 351 k, 38.8 / 34.5, 9^3, 315 k, 46.7 / 41).  Planes take 3D Dirichlet grids beyond 2048 unknowns
+// (block / planes: 6^3 elements 14.7 / 13.0, 7^3 20 / 14) while a block's plane or columns
+// are short beside the six launches (planes / passes: 16^3 25 / 28, 24 x 8 x 8 22 / 28, 4 x 4 x
+// 35 26 / 27; beyond, 17^3 35 / 31, 20^3 44 / 32, 3 x 3 x 60 46 / 32), and the largest, whose
+// passes stream the vector (30^3 92 / 96, 32 x 32 x 40 105 / 128).
+enum CoarseForm { COARSE_BLOCK, COARSE_PLANES, COARSE_PASSES };
+inline bool coarse_block_fits(const CoarseDev& C) { return coarse_block_shmem(C) <= COARSE_LDS; }
+inline CoarseForm coarse_form(const CoarseDev& C, bool mean) {
+  const int64_t G0 = coarse_nodes(C, 0), G1 = coarse_nodes(C, 1), G2 = coarse_nodes(C, 2), n = G0 * G1 * G2;
+  const int64_t products = n * (G0 + G1 + (C.dim == 3 ? G2 : 0));
+  const bool planes = C.dim == 3 && !mean && coarse_planes_shmem(C) <= COARSE_LDS &&
+                      coarse_columns_shmem(C) <= COARSE_LDS &&
+                      (n >= 200000 || (G0 * G1 * (G0 + G1) <= 70000 && 32 * G2 * G2 <= 130000));
+  if (planes && n > 2048) return COARSE_PLANES;
+  return coarse_block_fits(C) && products <= (mean ? 290000 : 200000) ? COARSE_BLOCK : (planes ? COARSE_PLANES : COARSE_PASSES);
 }
 
 }  // namespace dgmg

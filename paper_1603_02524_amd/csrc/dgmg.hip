@@ -2308,7 +2308,7 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, bool coarse_
         const PatchBuf lay = sweep_buf<T>(lv, nd);
         const T* res = uz ? f[l] : rl;
         std::vector<char> fargs;
-        if (lv.dim == 3) {
+        if (lay.swp) {
           fargs = arg_bytes(fdm3_args(Lv, nd, res, patch, np[0], np[1], np[2], lay, PatchLat{}));
         } else {
           FdmArgs<T> fa;
@@ -2317,10 +2317,11 @@ void vcycle_steps(dgmg_handle* h, int gi, const T* r_top, T* z_top, bool coarse_
           fa.out = patch;
           fa.npx = np[0];
           fa.npy = np[1];
+          fa.npz = np[2];
           fargs = arg_bytes(fa);
         }
         step({major, depthkey, s, i, 1}, BK_FDM, lv.dim,
-             {nd, NA, NL, lv.dim == 2 && fdm2_fits<T>(NA, NL, np[0] * np[1]) ? 1 : 0},
+             {nd, NA, NL, lv.dim == 3 ? lay.swp : (fdm2_fits<T>(NA, NL, np[0] * np[1]) ? 1 : 0)},
              np[0] * ((np[1] + lay.K - 1) / lay.K) * np[2], std::move(fargs));
         out.back().pb = lay;
         const int N[3] = {lv.dir[0].N, lv.dir[1].N, lv.dim == 3 ? lv.dir[2].N : 1};

@@ -86,6 +86,7 @@ PatchBuf Kern<T, DIM>::patch_buf(int NP, int nd, int NA, int NL, const int* np, 
 #define DGMG_CASE(A, B)                                            \
   if (NA == A && NL == B) {                                        \
     if constexpr (fdm3_fits<T, A, B>()) {                          \
+      if (whole && fdm_short_fits<T>(A, B, (int64_t)np[0] * np[1] * np[2], (nd == 1 ? A : B) <= 2 * step)) return pb; \
       pb.swp = 1;                                                  \
       pb.step = step;                                              \
       if (whole && order_compiled(NP)) pb.K = fdm3_strip<T>(A, B, nd, np, step); \
@@ -106,7 +107,7 @@ int Kern<T, DIM>::fdm(const LevelDev<T>& L, int nd, int NA, int NL, const T* r, 
   if (pb.K > 1 && !whole) return -4;
   FdmArgs<T> a2;
   Fdm3Args<T> a3;
-  if constexpr (DIM == 3) {
+  if (DIM == 3 && pb.swp) {
     a3 = fdm3_args(L, nd, r, out, npx, npy, npz, pb, lat);
   } else {
     a2.L = L;
@@ -114,15 +115,19 @@ int Kern<T, DIM>::fdm(const LevelDev<T>& L, int nd, int NA, int NL, const T* r, 
     a2.out = out;
     a2.npx = npx;
     a2.npy = npy;
+    a2.npz = DIM == 3 ? npz : 1;
     a2.lat = lat;
   }
 #define DGMG_CASE(A, B)                                                                        \
   if (NA == A && NL == B) {                                                                    \
     if constexpr (DIM == 3 && !fdm3_fits<T, A, B>())                                           \
       return whole ? fdm_big_launch<T, A, B>(L, nd, r, out, npx, npy, npz, s) : -4;            \
-    else if constexpr (DIM == 3)                                                               \
+    else if constexpr (DIM == 3) {                                                             \
+      if constexpr (fdm_short<T>(A, B))                                                        \
+        if (!pb.swp)                                                                           \
+          return fdm_go<T, 3, A, B, false>(nd, a2, BatchList<FdmArgs<T>>{}, npx * npy * npz, waves, s); \
       return fdm3_go<T, A, B, false>(nd, a3, BatchList<Fdm3Args<T>>{}, a3.nblk, s);            \
-    else {                                                                                     \
+    } else {                                                                                   \
       if constexpr (A * B <= FDM2_NODES)                                                       \
         if (fdm2_fits<T>(A, B, npx * npy))                                                     \
           return fdm2_go<T, A, B, false>(nd, a2, BatchList<FdmArgs<T>>{}, npx * npy, s);       \
@@ -224,9 +229,11 @@ int Kern<T, DIM>::fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>&
   if (NA == A && NL == B) {                                                      \
     if constexpr (DIM == 3 && !fdm3_fits<T, A, B>())                             \
       return -4;                                                                 \
-    else if constexpr (DIM == 3)                                                 \
+    else if constexpr (DIM == 3) {                                               \
+      if constexpr (fdm_short<T>(A, B))                                          \
+        if (!pb.swp) return fdm_go<T, 3, A, B, true>(nd, FdmArgs<T>{}, bl, ntot, 0, s); \
       return fdm3_go<T, A, B, true>(nd, a3, bl3, ntot, s);                       \
-    else {                                                                       \
+    } else {                                                                     \
       if constexpr (A * B <= FDM2_NODES)                                         \
         if (few) return fdm2_go<T, A, B, true>(nd, FdmArgs<T>{}, bl, ntot, s);   \
       return fdm_go<T, DIM, A, B, true>(nd, FdmArgs<T>{}, bl, ntot, 0, s);       \

@@ -86,7 +86,7 @@ struct PatchLat {
 // Layout of the patch buffer.  K > 1: strips of K patches along direction 1 whose
 // tiles, `step` planes apart, are summed where they overlap (one tile of
 // (K - 1) step + len planes per strip); K is a power of two.  swp: tiles are stored plane by plane of
-// direction 1, [o1][o2][o0], instead of [o2][o1][o0].
+// direction 1, [o1][o2][o0] (fdm3_kernel), instead of [o2][o1][o0].
 struct PatchBuf {
   int K = 1, step = 0, swp = 0;
 };
@@ -232,13 +232,14 @@ __device__ __forceinline__ float div_nr(float v, float d) {
   const float q = v * r;
   return fmaf(fmaf(-d, q, v), r, q);
 }
-// 2D tiles (3D tiles: kernels_fdm3.hpp), one patch per block.  The LDS tile keeps the
-// normal direction fastest: tile[l1 * NAP + a], NAP = NA rounded up to an odd pitch so that
-// the lines of the fastest pass spread over the LDS banks.  NA = 2P for a
-// face-centred patch (the element-centred size otherwise), NL = NP + 2 N_O.
-// Each contraction pass runs on the matrix cores: the lines of the tile are the
-// M dimension (blocks of 16), the 1D eigenbasis is the B operand held in
-// registers, and each wave overwrites its line blocks in place.
+// 2D tiles and short 3D tiles (fdm_short; the others: kernels_fdm3.hpp), one patch per
+// block.  The LDS tile keeps the normal direction fastest: tile[(l2 * NL + l1) * NAP + a],
+// NAP = NA rounded up to an odd pitch so that the lines of the fastest pass spread over the
+// LDS banks.  NA = 2P for a face-centred patch (the element-centred size otherwise),
+// NL = NP + 2 N_O.  Passes over longer lines run on the matrix cores: the lines of the
+// tile are the M dimension (blocks of 16), the 1D eigenbasis is the B operand held in
+// registers, and each wave overwrites its line blocks in place; short lines go to the VALU,
+// a line per thread.
 template <int NA, int NL, int DIM>
 constexpr int fdm_tile() {
   return NA * ipow(NL, DIM - 1);
@@ -454,47 +455,67 @@ __device__ __forceinline__ void fdm_pass_any(T* __restrict__ tile, T* __restrict
 
 // Tile geometry of one sweep kind, all compile-time: ND = normal direction of a
 // face-centred patch (-1: element-centred).  Grid-natural order has direction 0
-// fastest with lengths L0, L1; the LDS tile keeps the normal direction
-// fastest: tile[l1 NAP + a].
+// fastest with lengths L0, L1, L2; the LDS tile keeps the normal direction
+// fastest: tile[(l2 NL + l1) NAP + a].
 template <int DIM, int ND, int NA, int NL>
 struct FdmShape {
   static constexpr int L0 = ND == 0 ? NA : NL;
   static constexpr int L1 = ND == 1 ? NA : NL;
-  static constexpr int TS = L0 * L1;
-  static constexpr int NROW = L1;  // rows of the grid-natural order
+  static constexpr int L2 = DIM == 3 ? (ND == 2 ? NA : NL) : 1;
+  static constexpr int TS = L0 * L1 * L2;
+  static constexpr int NROW = L1 * L2;  // rows of the grid-natural order (fixed o1, o2)
   static constexpr int NAP = fdm_pitch<NA>();
   // tile stride of direction 0 (the normal / fastest tile dimension unless ND > 0)
   static constexpr int C0 = ND <= 0 ? 1 : NAP;
   // grid direction of tile dimension t (t = 0: the normal / fastest one)
-  static constexpr int gd(int t) { return ND <= 0 ? t : 1 - t; }
-  static __device__ __forceinline__ int tpos(int o0, int o1) {
-    const int o[2] = {o0, o1};
-    return o[gd(1)] * NAP + o[gd(0)];
+  static constexpr int gd(int t) { return ND <= 0 ? t : (t == 0 ? ND : (t <= ND ? t - 1 : t)); }
+  static __device__ __forceinline__ int tpos(int o0, int o1, int o2) {
+    const int o[3] = {o0, o1, o2};
+    return ((DIM == 3 ? o[gd(2)] * NL : 0) + o[gd(1)]) * NAP + o[gd(0)];
   }
 };
+
+// 3D tiles that fdm_kernel solves in sweeps of many patches: lines of up to 7 values (in FP64
+// not the shortest, 3 x 3 to 4 x 4), where the matrix cores' operands (blocks of 4 lines and 4 values in FP64,
+// 16 lines and 16 values in FP32) are mostly padding.  Whole sweeps, kernels_fdm3.hpp / here,
+// us: 5 x 5 x 5 on 6156 patches FP64 16.6 / 12.4, FP32 15.1 / 9.8, on 44100 56 / 49 and 52 / 38;
+// 6 x 6 x 6 on 20412 41 / 34 and 37 / 26; 8 x 5 x 5 on 9702 23 / 21 and 22 / 15; 7 x 7 x 7 on
+// 16250 without strips FP64 58 / 40, FP32 47 / 28, on 9702 with strips FP64 27 / 31, FP32 25 /
+// 21; 4 x 4 x 4 on 20412 FP64 17 / 21, FP32 19 / 15; 6 x 4 x 4 on 6156 FP64 14.1 / 11.7.  With
+// fewer patches the chain of passes is the time: 810 patches of 5 x 5 x 5 6.1 / 6.3, 1452 of
+// 6 x 6 x 6 FP64 8.6 / 8.6, of 7 x 7 x 7 FP64 10.0 / 13.8 (2940: 15.4 / 14.4).  strips: patches can share planes along direction 1.
+template <class T>
+constexpr bool fdm_short(int NA, int NL) {
+  return NA <= 8 && NL <= 7 && (sizeof(T) == 4 || NL >= 5 || NA >= 6);
+}
+template <class T>
+bool fdm_short_fits(int NA, int NL, int64_t patches, bool strips) {
+  if (sizeof(T) == 8 && NL == 7) return fdm_short<T>(NA, NL) && !strips && patches >= 2400;
+  return fdm_short<T>(NA, NL) && patches >= 1200;
+}
 
 template <class T>
 struct FdmArgs {
   LevelDev<T> L;
   const T* r = nullptr;  // residual (level vector)
-  T* out = nullptr;      // weighted corrections, one tile per patch (strip) of the launch
-  int npx = 1, npy = 1;
+  T* out = nullptr;      // weighted corrections, one tile per patch of the launch
+  int npx = 1, npy = 1, npz = 1;
   PatchLat lat;
 };
 
 // BATCH: the arguments come from the work list bl (ntot logical blocks in all)
 template <class T, int DIM, int NA, int NL, int ND, bool BATCH = false>
 __global__ void __launch_bounds__(512) fdm_kernel(FdmArgs<T> a0, BatchList<FdmArgs<T>> bl, int ntot) {
-  static_assert(DIM == 2, "3D tiles: fdm3_kernel");
+  static_assert(DIM == 2 || fdm_short<T>(NA, NL), "other 3D tiles: fdm3_kernel");
   using S = FdmShape<DIM, ND, NA, NL>;
   constexpr int TS = S::TS;
   constexpr int NMAX = imax(NA, NL);
   constexpr int GU = 4;  // elements gathered per thread before their LDS stores (loads in flight)
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* tile = reinterpret_cast<T*>(smem_raw);
-  __shared__ int goff[2][NMAX];  // offsets into the level vector (< 2^31 unknowns), -1 outside
-  __shared__ T wv[2][NMAX];
-  __shared__ T lv[2][NMAX];
+  __shared__ int goff[3][NMAX];  // offsets into the level vector (< 2^31 unknowns), -1 outside
+  __shared__ T wv[3][NMAX];
+  __shared__ T lv[3][NMAX];
   // rowoff is dead once the gather is done: the contraction passes use it as
   // their store trash (64 values)
   __shared__ __align__(8) int rowoff[imax(S::NROW, 64 * (int)sizeof(T) / (int)sizeof(int))];
@@ -509,22 +530,23 @@ __global__ void __launch_bounds__(512) fdm_kernel(FdmArgs<T> a0, BatchList<FdmAr
     pid = batch_pick(bl, b, sargs);
     ap = sargs;
   } else {
-    pid = xcd_block(a0.npx * a0.npy);
+    pid = xcd_block(a0.npx * a0.npy * a0.npz);
     if (pid < 0) return;
     ap = &a0;
   }
   const LevelDev<T>& L = ap->L;
   const T* __restrict__ r = ap->r;
   T* __restrict__ out = ap->out;
-  const int npx = ap->npx;
+  const int npx = ap->npx, npy = ap->npy;
   const PatchLat& lat = ap->lat;
   if (inactive(L.active)) return;
   const int tid = threadIdx.x, nth = blockDim.x;
-  int p[2];
+  int p[3];
   p[0] = lat.start[0] + lat.stride[0] * (pid % npx);
-  p[1] = lat.start[1] + lat.stride[1] * (pid / npx);
-  const int* go[2] = {nullptr, nullptr};
-  const T* wg[2] = {nullptr, nullptr};
+  p[1] = lat.start[1] + lat.stride[1] * (DIM == 3 ? (pid / npx) % npy : pid / npx);
+  p[2] = DIM == 3 ? lat.start[2] + lat.stride[2] * (pid / (npx * npy)) : 0;
+  const int* go[3] = {nullptr, nullptr, nullptr};
+  const T* wg[3] = {nullptr, nullptr, nullptr};
 #pragma unroll
   for (int d = 0; d < DIM; ++d) {
     const DirDev<T>& dd = L.dir[d];
@@ -539,16 +561,18 @@ __global__ void __launch_bounds__(512) fdm_kernel(FdmArgs<T> a0, BatchList<FdmAr
       lv[d][o] = lam[o];
     }
   }
-  // per row of the grid-natural order: its offset in the level vector (-1 outside a
+  // per row (o1, o2) of the grid-natural order: its offset in the level vector (-1 outside a
   // Dirichlet domain) and its tile position
   for (int rw = tid; rw < S::NROW; rw += nth) {
-    rowoff[rw] = go[1][rw];
-    rowpos[rw] = S::tpos(0, rw);
+    const int o1 = rw % S::L1, o2 = rw / S::L1;
+    const int g1 = go[1][o1], g2 = DIM == 3 ? go[2][o2] : 0;
+    rowoff[rw] = (g1 | g2) < 0 ? -1 : g1 + g2;
+    rowpos[rw] = S::tpos(0, o1, o2);
   }
   // 1D matrices of each tile dimension: forward t_j = sum_k S_kj r_k uses S,
   // backward u_k = sum_j S_kj t_j uses S^T (both row-major)
-  const T* fwd[2] = {nullptr, nullptr};
-  const T* bwd[2] = {nullptr, nullptr};
+  const T* fwd[3] = {nullptr, nullptr, nullptr};
+  const T* bwd[3] = {nullptr, nullptr, nullptr};
 #pragma unroll
   for (int t = 0; t < DIM; ++t) {
     const int d = S::gd(t);
@@ -612,33 +636,46 @@ __global__ void __launch_bounds__(512) fdm_kernel(FdmArgs<T> a0, BatchList<FdmAr
   }
   __syncthreads();
   T* trash = reinterpret_cast<T*>(rowoff);
-  // the last forward pass divides each result by the sum of the 1D eigenvalues
-  // of its tile position: line = a, j = l1
+  // the last forward pass divides each result by the sum of the 1D eigenvalues of its tile
+  // position: line = a + NA l1 and j = l2 (2D: line = a, j = l1)
   const auto scale = [&](int line, int j, T v) -> T {
-    const int a = line % NA;
-    return div_nr(v, lv[S::gd(0)][a] + lv[S::gd(1)][j]);
+    T den = lv[S::gd(0)][line % NA] + lv[S::gd(1)][DIM == 3 ? line / NA : j];
+    if constexpr (DIM == 3) den += lv[S::gd(2)][j];
+    return div_nr(v, den);
   };
   fdm_pass_any<T, NA, NL, DIM, 0>(tile, trash, fwd[0], bwd[0]);
   __syncthreads();
-  fdm_pass_any<T, NA, NL, DIM, 1>(tile, trash, fwd[1], bwd[1], scale);
+  if constexpr (DIM == 3) {
+    fdm_pass_any<T, NA, NL, DIM, 1>(tile, trash, fwd[1], bwd[1]);
+    __syncthreads();
+  }
+  fdm_pass_any<T, NA, NL, DIM, DIM - 1>(tile, trash, fwd[DIM - 1], bwd[DIM - 1], scale);
   __syncthreads();
-  fdm_pass_any<T, NA, NL, DIM, 1>(tile, trash, bwd[1], fwd[1]);
+  fdm_pass_any<T, NA, NL, DIM, DIM - 1>(tile, trash, bwd[DIM - 1], fwd[DIM - 1]);
   __syncthreads();
+  if constexpr (DIM == 3) {
+    fdm_pass_any<T, NA, NL, DIM, 1>(tile, trash, bwd[1], fwd[1]);
+    __syncthreads();
+  }
   fdm_pass_any<T, NA, NL, DIM, 0>(tile, trash, bwd[0], fwd[0]);
   __syncthreads();
   // weighted result w_s (.) Delta u_s in grid-natural order
+  const auto row_w = [&](int rw) -> T {
+    if constexpr (DIM == 3) return wv[1][rw % S::L1] * wv[2][rw / S::L1];
+    else return wv[1][rw];
+  };
   T* dst = out + (int64_t)pid * TS;
   if constexpr (G2D) {
     const int o0 = tid & 15, rstep = nth >> 4;
     if (o0 < S::L0) {
       const T w0 = wv[0][o0];
       const int pc = o0 * S::C0;
-      for (int rw = tid >> 4; rw < S::NROW; rw += rstep) dst[rw * S::L0 + o0] = (w0 * wv[1][rw]) * tile[rowpos[rw] + pc];
+      for (int rw = tid >> 4; rw < S::NROW; rw += rstep) dst[rw * S::L0 + o0] = (w0 * row_w(rw)) * tile[rowpos[rw] + pc];
     }
   } else {
     for (int q = tid; q < TS; q += nth) {
       const int o0 = q % S::L0, rw = q / S::L0;
-      dst[q] = (wv[0][o0] * wv[1][rw]) * tile[rowpos[rw] + o0 * S::C0];
+      dst[q] = (wv[0][o0] * row_w(rw)) * tile[rowpos[rw] + o0 * S::C0];
     }
   }
 }
@@ -812,6 +849,7 @@ int fdm_go(int nd, const FdmArgs<T>& a, const BatchList<FdmArgs<T>>& bl, int nlo
   }
   if (nd == 0) fdm_launch_nd<T, DIM, NA, NL, 0, BATCH>(a, bl, nlog, th, shm, s);
   else if (nd == 1) fdm_launch_nd<T, DIM, NA, NL, 1, BATCH>(a, bl, nlog, th, shm, s);
+  else if constexpr (DIM == 3) fdm_launch_nd<T, DIM, NA, NL, 2, BATCH>(a, bl, nlog, th, shm, s);
   else return -4;
   return 0;
 }
@@ -1598,7 +1636,7 @@ struct Kern {
   static bool mode3_ok(const LevelDev<T>& L);
   static int apply_batch(int NP, int mode, bool lines, const BatchList<ApplyArgs<T>>& bl, int ntot, hipStream_t s);
   // pb: the longest strip of the launch's grids
-  // (arguments: bl in 2D, bl3 in 3D)
+  // (arguments: bl in 2D and where pb says that fdm_kernel solves the 3D tiles, else bl3)
   static int fdm_batch(int nd, int NA, int NL, const BatchList<FdmArgs<T>>& bl, const BatchList<Fdm3Args<T>>& bl3,
                        int ntot, const PatchBuf& pb, bool few, hipStream_t s);
   // maxc 0: the grids take combine3_kernel (arguments bl3), else combine_kernel (bl)

@@ -672,7 +672,8 @@ int fdm3_go(int nd, const Fdm3Args<T>& a, const BatchList<Fdm3Args<T>>& bl, int 
 // planes apart, tile NA, NL, normal nd): a power of two.  Longer strips share more
 // planes (and shrink the patch buffer) but need more LDS and leave fewer, longer blocks:
 // three blocks per compute unit have to fit (52 KB each), and the strips have to be at
-// least 512 K.  Measured (us per launch for K = 1 / 2 / 4): 16 x 13 x 13 FP64 on 4352
+// least 512 K (128 K for lines of up to 4 values, whose planes are little work: 3 x 3 x 3 FP64
+// on 6156 patches 10.0 -> 8.7 us with K = 4 instead of 2).  Measured (us per launch for K = 1 / 2 / 4): 16 x 13 x 13 FP64 on 4352
 // patches 85 / 73 / 83 (one block per unit at 4), FP32 on 33792 patches 284 / 233 / 226;
 // 8 x 9 x 9 FP64 on 4352 patches 32 / 27 / 28; 11^3 FP64 on 4096 patches 41 / 36 / 35.
 template <class T>
@@ -681,7 +682,7 @@ int fdm3_strip(int NA, int NL, int nd, const int* np, int step) {
   if (!fdm3_strips(NA, NL) || LY > 2 * step) return 1;
   int best = 1;
   for (int K : {2, 4, 8}) {
-    if (K > np[1] || (int64_t)np[0] * ((np[1] + K - 1) / K) * np[2] < 512 * (int64_t)K) break;
+    if (K > np[1] || (int64_t)np[0] * ((np[1] + K - 1) / K) * np[2] < (NL <= 4 ? 128 : 512) * (int64_t)K) break;
     const size_t lds = ((size_t)((K - 1) * step + LY) * LZ * (LX | 1) + fdm3_image<T>(LX) + fdm3_image<T>(LZ) +
                         (size_t)K * fdm3_image<T>(LY) + 2 * (LX + LZ + (size_t)K * LY)) * sizeof(T);
     if (lds > 52 * 1024) break;

@@ -2763,8 +2763,8 @@ int dgmg_batch_setup(int count, const dgmg_grid* grids, const dgmg_opts* opts, d
 int dgmg_batch_plan_info(const dgmg_batch* b, int* planned, int* kernels, int* grid_ops) {
   if (!b) return DGMG_EINVAL;
   int k = 0, g = 0;
-  for (const auto& ph : b->plan)
-    for (const auto& ln : ph) {
+  for (int ph = 0; ph < 2; ++ph)  // the phases of an iteration
+    for (const auto& ln : b->plan[ph]) {
       if (ln.kind == BK_FN) g += (int)ln.fns.size();
       else ++k;
     }

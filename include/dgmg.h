@@ -276,12 +276,17 @@ int dgmg_kernel_time(dgmg_handle* h, double* total_ms, int64_t* launches, double
  * stream or a tuning choice changes. */
 int dgmg_use_graphs(dgmg_handle* h, int enable);
 
-/* Autotuner: time the patch-solve block shapes (1, 2, 4 or 8 wavefronts per
- * patch) of every smoothing sweep on the bound workspace and keep the fastest
- * (synchronises; results are bitwise independent of the choice).
+/* Autotuner: time the patch-solve block shapes of every smoothing sweep on the
+ * bound workspace and keep the fastest (synchronises; results are bitwise
+ * independent of the choice).  The choice of 1, 2, 4 or 8 wavefronts per patch
+ * exists where a patch is solved by one block of any size: compiled 2D tiles in
+ * sweeps of more than 1.5 MB of tiles, and 3D tiles with lines of at most 7
+ * values in sweeps of 1200 patches or more.  The other patch solves are built
+ * for one block shape: they are timed as they are, and report its wavefronts.
  * dgmg_tune_get/set read or impose the choice for (level >= 1, kind), kind
  * 0..2 = face-centred sweep normal to direction kind, 3 = element-centred;
- * waves 0 = built-in default.  ms: mean time of one launch when timed. */
+ * waves 0 = built-in default; an imposed choice has no effect where there is one
+ * shape.  ms: mean time of one launch when timed. */
 int dgmg_autotune(dgmg_handle* h);
 int dgmg_tune_get(const dgmg_handle* h, int level, int kind, int* waves, double* ms);
 int dgmg_tune_set(dgmg_handle* h, int level, int kind, int waves);

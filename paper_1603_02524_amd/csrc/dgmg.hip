@@ -1529,45 +1529,52 @@ int validate_setup(const dgmg_grid* g, const dgmg_opts* o, SetupParams& sp) {
   return DGMG_OK;
 }
 
-// Time the patch-solve block shapes of every sweep and keep the fastest.
+// Time one sweep's patch solve in every block shape that its kernel takes and keep the
+// fastest; a kernel of one shape is timed as it is.
+template <class T>
+int tune_sweep(dgmg_handle* h, int l, int nd, hipEvent_t e0, hipEvent_t e1) {
+  const LevelHost& lv = h->lv[l];
+  int np[3], NA, NL;
+  sweep_shape(lv, nd, np, NA, NL);
+  const PatchBuf lay = sweep_buf<T>(lv, nd);
+  const int fixed = lv.dim == 3 ? Kern<T, 3>::fdm_waves(nd, NA, NL, np[0] * np[1] * np[2], lay)
+                                : Kern<T, 2>::fdm_waves(nd, NA, NL, np[0] * np[1], lay);
+  std::vector<int> shapes = {1, 2, 4, 8};
+  if (fixed) shapes = {fixed};
+  T* r = (T*)h->buf[l].r;
+  k_fill_v<T>(h, r, lv.n_dof);
+  float best = 1e30f;
+  int bw = 0;
+  for (int w : shapes) {
+    int rc = k_fdm<T>(h, l, nd, r, w);
+    (void)hipEventRecord(e0, h->stream);
+    for (int rep = 0; rep < 3 && !rc; ++rep) rc = k_fdm<T>(h, l, nd, r, w);
+    (void)hipEventRecord(e1, h->stream);
+    if (rc) return rc;
+    const hipError_t e = hipEventSynchronize(e1);
+    if (e != hipSuccess) return fail(h, DGMG_EHIP, std::string("autotune: ") + hipGetErrorString(e));
+    float ms = 0;
+    (void)hipEventElapsedTime(&ms, e0, e1);
+    if (ms < best) {
+      best = ms;
+      bw = w;
+    }
+  }
+  const int kind = nd < 0 ? 3 : nd;
+  h->waves[l][kind] = bw;
+  h->tune_ms[l][kind] = best / 3.0f;
+  return DGMG_OK;
+}
+
 template <class T>
 int autotune_t(dgmg_handle* h) {
-  const int nl = (int)h->lv.size();
   hipEvent_t e0, e1;
   (void)hipEventCreate(&e0);
   (void)hipEventCreate(&e1);
   int rc = DGMG_OK;
-  for (int l = 1; l < nl && !rc; ++l) {
-    T* r = (T*)h->buf[l].r;
-    k_fill_v<T>(h, r, h->lv[l].n_dof);
+  for (int l = 1; l < (int)h->lv.size() && !rc; ++l) {
     const int nkinds = ec_smoother(h) ? 1 : h->lv[l].dim;
-    for (int q = 0; q < nkinds && !rc; ++q) {
-      const int nd = ec_smoother(h) ? -1 : q;
-      const int kind = nd < 0 ? 3 : nd;
-      float best = 1e30f;
-      int bw = 0;
-      for (int w : {1, 2, 4, 8}) {
-        if ((rc = k_fdm<T>(h, l, nd, r, w))) break;
-        (void)hipEventRecord(e0, h->stream);
-        for (int rep = 0; rep < 3; ++rep)
-          if ((rc = k_fdm<T>(h, l, nd, r, w))) break;
-        (void)hipEventRecord(e1, h->stream);
-        if (rc) break;
-        hipError_t e = hipEventSynchronize(e1);
-        if (e != hipSuccess) {
-          rc = fail(h, DGMG_EHIP, std::string("autotune: ") + hipGetErrorString(e));
-          break;
-        }
-        float ms = 0;
-        (void)hipEventElapsedTime(&ms, e0, e1);
-        if (ms < best) {
-          best = ms;
-          bw = w;
-        }
-      }
-      h->waves[l][kind] = bw;
-      h->tune_ms[l][kind] = best / 3.0f;
-    }
+    for (int q = 0; q < nkinds && !rc; ++q) rc = tune_sweep<T>(h, l, ec_smoother(h) ? -1 : q, e0, e1);
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
@@ -2884,7 +2891,7 @@ int dgmg_batch_autotune(dgmg_batch* b) {
   for (size_t i = 0; i < b->h.size(); ++i) b->flags_host[i] = 1;
   int rc = batch_flags_upload(b);
   if (rc) return rc;
-  // grids whose sweeps have the same tile and patch counts share one measurement
+  // grids whose sweeps have the same order, tile and patch counts share one measurement
   std::vector<std::pair<std::vector<int64_t>, int>> seen;
   for (dgmg_handle* h : b->h) {
     for (int l = 1; l < (int)h->lv.size(); ++l) {
@@ -2893,7 +2900,7 @@ int dgmg_batch_autotune(dgmg_batch* b) {
         const int nd = ec_smoother(h) ? -1 : q;
         int np[3], NA, NL;
         sweep_shape(h->lv[l], nd, np, NA, NL);
-        std::vector<int64_t> key{(int64_t)mg_size(h), h->lv[l].dim, NA, NL, np[0], np[1], np[2]};
+        std::vector<int64_t> key{(int64_t)mg_size(h), h->lv[l].dim, h->lv[l].NP, NA, NL, np[0], np[1], np[2]};
         int found = -1;
         for (auto& s : seen)
           if (s.first == key) found = s.second;
@@ -2902,44 +2909,14 @@ int dgmg_batch_autotune(dgmg_batch* b) {
           continue;
         }
         seen.emplace_back(key, -1);
-        // tune this handle's level fully, then record the choice of this sweep
-        int keep[NKIND];
-        for (int k = 0; k < NKIND; ++k) keep[k] = h->waves[l][k];
         hipEvent_t e0, e1;
         (void)hipEventCreate(&e0);
         (void)hipEventCreate(&e1);
-        float best = 1e30f;
-        int bw = 0;
-        for (int w : {1, 2, 4, 8}) {
-          const bool f32 = mixed(h);
-          auto launch = [&]() {
-            return f32 ? k_fdm<float>(h, l, nd, (const float*)h->buf[l].r, w)
-                       : k_fdm<double>(h, l, nd, (const double*)h->buf[l].r, w);
-          };
-          if (f32) k_fill_v<float>(h, (float*)h->buf[l].r, h->lv[l].n_dof);
-          else k_fill_v<double>(h, (double*)h->buf[l].r, h->lv[l].n_dof);
-          if ((rc = launch())) break;
-          (void)hipEventRecord(e0, h->stream);
-          for (int rep = 0; rep < 3 && !rc; ++rep) rc = launch();
-          (void)hipEventRecord(e1, h->stream);
-          if (rc || hipEventSynchronize(e1) != hipSuccess) {
-            rc = rc ? rc : DGMG_EHIP;
-            break;
-          }
-          float ms = 0;
-          (void)hipEventElapsedTime(&ms, e0, e1);
-          if (ms < best) {
-            best = ms;
-            bw = w;
-          }
-        }
+        rc = mixed(h) ? tune_sweep<float>(h, l, nd, e0, e1) : tune_sweep<double>(h, l, nd, e0, e1);
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         if (rc) return batch_fail(b, rc, "autotune: " + h->err);
-        for (int k = 0; k < NKIND; ++k) h->waves[l][k] = keep[k];
-        h->waves[l][nd < 0 ? 3 : nd] = bw;
-        h->tune_ms[l][nd < 0 ? 3 : nd] = best / 3.0f;
-        seen.back().second = bw;
+        seen.back().second = h->waves[l][nd < 0 ? 3 : nd];
       }
     }
     drop_graphs(h);

@@ -100,6 +100,26 @@ PatchBuf Kern<T, DIM>::patch_buf(int NP, int nd, int NA, int NL, const int* np, 
 }
 
 template <class T, int DIM>
+int Kern<T, DIM>::fdm_waves(int nd, int NA, int NL, int patches, const PatchBuf& pb) {
+#define DGMG_CASE(A, B)                                                                          \
+  if (NA == A && NL == B) {                                                                      \
+    if constexpr (DIM == 3) {                                                                    \
+      if (!fdm3_fits<T, A, B>()) return 4;                                                       \
+      return pb.swp ? fdm3_waves<T, A, B>() : 0;                                                 \
+    } else {                                                                                     \
+      if (!fdm2_fits<T>(A, B, patches)) return 0;                                                \
+      return (nd == 0 ? fdm2_threads<A, B, 0>() : (nd == 1 ? fdm2_threads<A, B, 1>() : fdm2_threads<A, B, -1>())) / 64; \
+    }                                                                                            \
+  }
+  DGMG_FDM_LIST(DGMG_CASE)
+  if constexpr (DIM == 2) {
+    DGMG_FDM_LIST_2D(DGMG_CASE)
+  }
+#undef DGMG_CASE
+  return 4;  // run-time tile
+}
+
+template <class T, int DIM>
 int Kern<T, DIM>::fdm(const LevelDev<T>& L, int nd, int NA, int NL, const T* r, T* out, int npx,
                       int npy, int npz, const PatchBuf& pb, int waves, const PatchLat& lat, hipStream_t s) {
   const bool whole = lat.start[0] == 0 && lat.start[1] == 0 && lat.start[2] == 0 && lat.stride[0] == 1 &&

@@ -1618,6 +1618,9 @@ struct Kern {
   // (3D P = 32) take only the whole partition
   static int fdm(const LevelDev<T>& L, int nd, int NA, int NL, const T* r, T* out, int npx, int npy,
                  int npz, const PatchBuf& pb, int waves, const PatchLat& lat, hipStream_t s);
+  // wavefronts per block of a whole sweep's patch solve: 0 where the caller chooses
+  // (fdm_kernel), else the one shape that its kernel is built for
+  static int fdm_waves(int nd, int NA, int NL, int patches, const PatchBuf& pb);
   // patch-buffer layout of a level's sweep (np patches per direction, `step` node
   // positions apart along direction 1); whole = false: a launch over some of the
   // patches (strips of one patch)

@@ -151,7 +151,7 @@ __global__ void __launch_bounds__(TH) k_mlp_grad(const float* __restrict__ p, co
 #pragma unroll
         for (int o = 0; o < OUT; ++o) a += dy[s][o] * w3[o];
         const float h = h2[s][j];
-        d2[s][j] = a * (1.0f - h * h);
+        d2[s][j] = s < n ? a * (1.0f - h * h) : 0.0f;  // (the padding is 0 whatever the weights)
       }
     }
     __syncthreads();
@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(TH) k_mlp_grad(const float* __restrict__ p, co
       for (int r = 0; r < 4; ++r) {
         const int k = 16 * wave + 4 * lk + r;
         const float h = h1[s][k];
-        h1[s][k] = a[r] * (1.0f - h * h);
+        h1[s][k] = s < n ? a[r] * (1.0f - h * h) : 0.0f;
       }
     }
     __syncthreads();

@@ -876,13 +876,15 @@ __global__ void __launch_bounds__(1024) apply_lines_kernel(ApplyArgs<T> a0, Batc
 // where the line form's chain of products is the time (16x16 P = 16 FP64 11.9 against
 // 4.6 us); beyond, its LDS reads bind it (128x128 P = 16 FP64 199 against 60 us; the two
 // meet at 200000 to 300000 nodes in FP64, twice that in FP32).  P <= 2: lines (3.6 against
-// 4.0 us).  3D: lines up to 1 MB and P <= 8, where the directions in turn are the longer
-// chain (4^3 P = 8 FP64 5.8 against 6.8 us, 8^3 P = 2 FP32 3.4 against 3.9); the two meet
-// near 8^3 elements of P = 8, and at 20^3 the directions in turn take 22 against 35 us (FP32).
+// 4.0 us).  3D, P <= 8: lines while the directions in turn are the longer chain, up to
+// 1 MB in FP32, 1.25 MB in FP64, 1.75 MB (P = 6) and 3 MB (P = 8) (residual, lines / in turn, us:
+// FP32 P = 4 10^3 4.6 / 4.8, 13^3 5.4 / 4.8; FP64 P = 3 13^3 4.8 / 5.3, P = 4 12^3 5.7 / 5.2, P = 6
+// 8^3 5.5 / 6.2, 10^3 7.0 / 6.3, P = 8 6^3 5.8 / 7.3, 8^3 7.0 / 7.7, 10^3 9.6 / 9.8, 12^3 14.5 / 12.2).
 template <class T, int DIM, int NP>
 constexpr bool apply_lines(int n_elem) {
   const int64_t bytes = (int64_t)n_elem * ipow(NP, DIM) * (int64_t)sizeof(T);
-  return DIM == 2 ? NP <= 3 || bytes > (3 << 19) : NP <= 9 && bytes <= (1 << 20);
+  if (DIM == 2) return NP <= 3 || bytes > (3 << 19);
+  return NP <= 9 && bytes <= (sizeof(T) == 4 ? 1 << 20 : (NP == 9 ? 3 << 20 : (NP == 7 ? 7 << 18 : 5 << 18)));
 }
 template <int DIM, int NP>
 constexpr bool apply_lines_built() {

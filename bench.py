@@ -44,23 +44,21 @@ HBM_PEAK_GBPS = 8000.0
 # (FETCH_SIZE, then WRITE_SIZE), scaled by the same counters on a plain copy of
 # known size (bench.py --copy-calibration); the summary with commands is in
 # profiles/.  Valid only for the kernel source it was measured on: the hash of
-# the patch-solve section of kernels.hpp is compared at run time and the
-# figure dropped on any change.
-TRAFFIC = {"bytes_per_launch": 133.7e6,
-           "kernel_src_sha256": "21eeba7092ae86177bd0f64650ee51eb25155c3bbcf43ef78c7fe3c4e1f6d4cc",
+# that header's code (its comments and white space left out) is compared at run
+# time and the figure dropped on any change.
+TRAFFIC = {"bytes_per_launch": 144.5e6,
+           "kernel_src_sha256": "58cd2cd3c9022278de40569f97580c174077cfd657c779a1b92d89c8efe1bdd4",
            "profile": "profiles/fdm_p8_c2_fp64_pmc_traffic.md"}
-KERNEL_SOURCE = "paper_1603_02524_amd/csrc/kernels.hpp"
-KERNEL_SECTION = ("// ================================================================ FDM patch solve",
-                  "// ================================================================ overlap summation")
+KERNEL_SOURCE = "paper_1603_02524_amd/csrc/kernels_fdm3.hpp"
 
 
 def _kernel_src_hash():
-    """sha256 of the patch-solve section of the kernel header (the dominant kernel)."""
+    """sha256 of the code of the dominant kernel's header."""
     import hashlib
+    import re
     with open(os.path.join(ROOT, KERNEL_SOURCE), encoding="utf-8") as fh:
-        text = fh.read()
-    a, b = text.index(KERNEL_SECTION[0]), text.index(KERNEL_SECTION[1])
-    return hashlib.sha256(text[a:b].encode()).hexdigest()
+        text = re.sub(r"//[^\n]*", "", fh.read())
+    return hashlib.sha256(" ".join(text.split()).encode()).hexdigest()
 
 
 def _copy_calibration(mb, reps=5):

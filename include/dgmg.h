@@ -303,19 +303,22 @@ const char* dgmg_last_error(const dgmg_handle* h);
  * MGCG runs in lock step with one host synchronisation per iteration for all
  * grids; converged grids are masked by a device flag that every kernel
  * checks.  When all grids share the multigrid precision, the smoothing counts
- * and the V-cycle kind, use additive smoothers and have no 3D P = 32 level,
- * each phase of an iteration is a work-list plan: every step of every grid's
- * phase is keyed by its position (the top-level apply; in the V-cycle the
- * depth below the top level, smoothing step, sweep, sub-step), and the steps
- * at one position that use the same kernel instance (order, tile, mode) run as
- * ONE launch over all those grids' elements or patches, with per-grid
- * argument descriptors in the workspace; vector updates, fills and coarse
- * solves stay per grid.  When a grid's top level has at least 2^20 unknowns
- * (its levels that large keep their own launches), the per-grid steps of one
- * position run round robin on three side streams the batch creates at bind
- * (default priority; forked from and joined back into the batch stream by
- * events) and overlap that position's shared launches; results do not depend
- * on it.  Otherwise each grid's chain is issued on its own.
+ * and the V-cycle kind, use additive smoothers, have no 3D P = 32 level and only
+ * orders with compiled kernels, each phase of an iteration is a work-list plan:
+ * every step of every grid's phase is keyed by its position (the top-level
+ * apply, vector updates and norms; in the V-cycle the order of the level,
+ * smoothing step, sweep, sub-step), and the steps at one position that use the
+ * same kernel instance (order, tile, mode) run as ONE launch over all those
+ * grids' elements, patches or blocks, with per-grid argument descriptors in the
+ * workspace.  Levels of at least 2^20 unknowns keep their own launches, and so do
+ * coarse solves of more than one launch.  The batch creates three side streams at
+ * bind (default priority; forked from and joined back into the batch stream by
+ * events).  When a grid's top level has at least 2^20 unknowns, the per-grid
+ * steps of one position run on them round robin and overlap that position's
+ * shared launches; otherwise grids whose orders share no launch (halving to
+ * different odd numbers: 8, 4, 2 and 6, 3) run their V-cycles side by side.
+ * Results do not depend on it.  Without a plan each grid's chain is issued on its
+ * own.
  * Either way a phase is issued eagerly (the default; the per-grid
  * operations of converged grids are then left out) or captured once as a
  * hipGraph and replayed.  Vectors of all grids are

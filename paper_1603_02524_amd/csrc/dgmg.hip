@@ -463,7 +463,7 @@ struct dgmg_handle {
     int n[3] = {1, 1, 1};
   };
   std::vector<MultClass> mcls[MAXL][NKIND];
-  // autotuned patch-solve block shapes (waves per block), 0 = default
+  // patch-solve block shapes (waves per block, where the kernel takes more than one), 0 = default
   int waves[MAXL][NKIND] = {};
   float tune_ms[MAXL][NKIND] = {};
   // timing of the top-level patch solves: every timing_stride-th launch
@@ -2189,12 +2189,15 @@ namespace {
 // the V-cycle kind, with additive smoothers and no large (3D P = 32) levels,
 // runs each MGCG phase as one list of launches over work lists (BatchList):
 // every step of every grid's phase is keyed by its position (phase a: the
-// top-level apply q = A p; phase b: the V-cycle, steps keyed by depth below the
-// top level, smoothing step, sweep and sub-step), and the steps at one position
-// that use the same kernel instance become one launch over all their grids,
-// one argument descriptor per grid.  Each grid sees the same kernels on the
-// same data in the same order as in its own solve (bitwise the same results).
-// The PCG vector operations, fills and coarse solves stay per grid.
+// top-level apply q = A p, the x and r update, the norm; phase b: the V-cycle, steps
+// keyed by order family, way down or up, order of the level, smoothing step, sweep and
+// sub-step, then z.r and the direction update; a third list takes the norms of the
+// initial residuals), and the steps at one position that use the same kernel instance
+// become one launch over all their grids, one argument descriptor per grid.  Each grid
+// sees the same arithmetic on the same data in the same order as in its own solve
+// (bitwise the same results).  Per grid stay: levels of at least SOLO_DOF unknowns and
+// phase a of grids whose top level is one, fills of u without pre-smoothing, coarse solves
+// of several launches, and the reduction of many partial sums of p.q.
 enum { BK_APPLY = 0, BK_FDM = 1, BK_COMB = 2, BK_XFER = 3, BK_FN = 4, BK_COARSE = 5, BK_PCG = 6 };
 enum { PCG_UPDATE_XR = 0, PCG_TOTAL = 1, PCG_DOT_ZR = 2, PCG_UPDATE_P = 3, PCG_NORM = 4 };
 
@@ -2234,8 +2237,7 @@ bool batch_plannable(const dgmg_batch* b) {
 }
 
 // Levels with at least this many unknowns fill the GPU alone: their steps keep
-// the single-grid launches (autotuned block shapes, arguments in scalar
-// registers) and only the smaller levels share work-list launches.
+// the single-grid launches (arguments in scalar registers) and only the smaller levels share work-list launches.
 constexpr int64_t SOLO_DOF = 1 << 20;
 
 // Steps of one grid's V-cycle (as k_vcycle, k_smooth, k_sweep,

@@ -1454,7 +1454,10 @@ __global__ void __launch_bounds__(512) transfer_kernel(XferArgs<T> a0, BatchList
 // product from LDS.  Direction 2, whose lines' lanes run along the vector, is contracted
 // first by the restriction, from global memory, and last by the prolongation, into it.
 // 7x9x6 P = 16 FP64 (32 MB): restriction 14.6 -> 8.4 us, prolongation 18.5 -> 8.5 us;
-// 9x7x11 P = 12 FP32: 5.6 -> 3.1 and 6.9 -> 4.1 us.
+// 9x7x11 P = 12 FP32: 5.6 -> 3.1 and 6.9 -> 4.1 us.  12 is where it has been brought in, not
+// where it ends: timed in its place at lower orders it is the faster form there too
+// (transfer_kernel / this, restriction and prolongation, us: 32^3 P = 8 FP64 67 / 32 and 75 / 63,
+// FP32 42 / 18 and 51 / 34; 32^3 P = 4 FP64 13.6 / 9.7 and 16.4 / 14.8; 8^3 P = 8 3.7 / 3.6).
 template <int NPF>
 constexpr bool xfer_lines() {
   return NPF >= 12;

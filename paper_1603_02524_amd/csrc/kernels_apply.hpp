@@ -396,7 +396,7 @@ __global__ void __launch_bounds__((apply_threads<NP, 3>()))
 // its four neighbours come to LDS by coalesced loads, a thread per line and side takes the
 // face terms (17 instead of 289 products in a row at P = 16), then every node adds up its
 // two rows, matrix and values from LDS.
-// Residual of 16x16 P = 16 FP64: 14.5 -> 5.3 us (a launch alone: 2-3 us).
+// Figures: apply_lines.
 template <class T, int NP, int MODE, bool BATCH = false>
 __global__ void __launch_bounds__((apply_threads<NP, 2>()))
     apply2_kernel(ApplyArgs<T> a0, BatchList<ApplyArgs<T>> bl, int ntot) {
@@ -873,8 +873,8 @@ __global__ void __launch_bounds__(1024) apply_lines_kernel(ApplyArgs<T> a0, Batc
 
 // The form of a grid's apply (of the grid, also when grids share a launch, so that a batch
 // gives what its grids give alone).  2D: a thread per node up to 1.5 MB of level vector,
-// where the line form's chain of products is the time (16x16 P = 16 FP64 11.9 against
-// 4.6 us); beyond, its LDS reads bind it (128x128 P = 16 FP64 199 against 60 us; the two
+// where the line form's chain of products is the time (residual of 16x16 P = 16 FP64 11.8
+// against 4.9 us); beyond, its LDS reads bind it (128x128 P = 16 FP64 199 against 60 us; the two
 // meet at 200000 to 300000 nodes in FP64, twice that in FP32).  P <= 2: lines (3.6 against
 // 4.0 us).  3D, P <= 8: lines while the directions in turn are the longer chain, up to
 // 1 MB in FP32, 1.25 MB in FP64, 1.75 MB (P = 6) and 3 MB (P = 8) (residual, lines / in turn, us:

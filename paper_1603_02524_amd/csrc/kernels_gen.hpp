@@ -95,7 +95,8 @@ __global__ void __launch_bounds__(256) gen_apply_kernel(LevelDev<T> L, int mode,
 
 // Patch solve of one sweep (ND = nd, -1 element-centred) for a run-time tile:
 // the same gather, fast-diagonalisation passes, eigenvalue scaling, weights and
-// output layout (tile in grid-natural order, one tile per patch) as fdm_kernel.
+// output layout (tile in grid-natural order, one tile per patch) as fdm_kernel has for 2D
+// and short 3D tiles.
 // One LDS tile; a pass gives each thread whole lines (the line's results in a
 // private buffer until all its inputs are read).
 template <class T>

@@ -11,8 +11,8 @@
 // buffer (se_elem_kernel), then per lattice node the sum of the copies of the
 // elements sharing it, in a fixed order (se_dss_kernel).  No atomics: the
 // result does not depend on the launch order.
-// Smoother: the element-centred patch solves are the DG ones (fdm_kernel with
-// the continuous tables and lattice offsets); their weighted corrections are
+// Smoother: the element-centred patch solves are the DG ones (fdm3_kernel in 3D, fdm_kernel
+// or fdm2_kernel in 2D, with the continuous tables and lattice offsets); their weighted corrections are
 // summed per lattice node by se_combine_kernel.
 // Transfers: prolongation per element onto the nodes it owns (i_d < P in every
 // direction: each lattice node has exactly one owner); restriction per element

@@ -1,4 +1,5 @@
-// Patch solve by fast diagonalisation in 3D, tiles that fit in LDS (gfx950).
+// Patch solve by fast diagonalisation in 3D, tiles that fit in LDS (gfx950); sweeps of many
+// patches of short lines take fdm_kernel (fdm_short_fits).
 //
 // One block solves a strip of K patches that follow each other along direction
 // 1 (same indices in directions 0 and 2).  Their tiles overlap in node planes of

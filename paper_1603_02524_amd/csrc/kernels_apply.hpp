@@ -877,9 +877,10 @@ __global__ void __launch_bounds__(1024) apply_lines_kernel(ApplyArgs<T> a0, Batc
 // against 4.9 us); beyond, its LDS reads bind it (128x128 P = 16 FP64 199 against 60 us; the two
 // meet at 200000 to 300000 nodes in FP64, twice that in FP32).  P <= 2: lines (3.6 against
 // 4.0 us).  3D, P <= 8: lines while the directions in turn are the longer chain, up to
-// 1 MB in FP32, 1.25 MB in FP64, 1.75 MB (P = 6) and 3 MB (P = 8) (residual, lines / in turn, us:
-// FP32 P = 4 10^3 4.6 / 4.8, 13^3 5.4 / 4.8; FP64 P = 3 13^3 4.8 / 5.3, P = 4 12^3 5.7 / 5.2, P = 6
-// 8^3 5.5 / 6.2, 10^3 7.0 / 6.3, P = 8 6^3 5.8 / 7.3, 8^3 7.0 / 7.7, 10^3 9.6 / 9.8, 12^3 14.5 / 12.2).
+// 1 MB in FP32, 1.25 MB in FP64, 1.75 MB (P = 6) and 3 MB (P = 8).  Residual, lines / in turn,
+// us: FP64 P = 3 13^3 4.7 / 5.3, P = 6 8^3 5.4 / 6.2, P = 8 6^3 5.9 / 7.3, 8^3 6.9 / 7.7; beyond the
+// lines (these in their form before, 0.3 us slower) P = 4 12^3 6.0 / 5.3, P = 6 10^3 7.3 / 6.3,
+// P = 8 10^3 9.8 / 9.8, 12^3 14.8 / 12.2, FP32 P = 4 13^3 5.5 / 4.8, P = 8 8^3 6.6 / 6.4.
 template <class T, int DIM, int NP>
 constexpr bool apply_lines(int n_elem) {
   const int64_t bytes = (int64_t)n_elem * ipow(NP, DIM) * (int64_t)sizeof(T);

@@ -3,8 +3,8 @@
 // per direction with S_d.  Three forms, with the same bits (coarse_form picks one):
 //   one block   the whole vector and the matrices in LDS, every pass in one launch (bound
 //               by LDS latency: 13 us for 2D 16 x 16, 1024 unknowns with a periodic mean,
-//               11 launches of 3 to 5 us as passes; 15.6 us for 7 x 5 x 6 elements, six as
-//               passes)
+//               before 13 launches of 3 to 5 us; 15.6 us for 7 x 5 x 6 elements, as passes
+//               six launches)
 //   planes      3D grids whose planes of directions 0 and 1 fit: forward along 0 and
 //               1 per plane, forward, scaled and back along 2 per group of columns, back
 //               along 1 and 0 per plane (three launches)
